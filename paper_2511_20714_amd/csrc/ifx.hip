@@ -120,6 +120,18 @@ int grid_for(int64_t items, int per_block = 256, int max_blocks = 256 * 16)
     return (int)b;
 }
 
+// fp32 attention: head_dim rounded up to what the kernel is instantiated for, and that instance.
+int f32_padded_dim(int D) { return (D + 31) / 32 * 32; }
+void (*f32_kernel(int D))(const ifx::attn_f32_args)
+{
+    switch (f32_padded_dim(D)) {
+    case 32: return ifx::attn_f32_kernel<32>;
+    case 64: return ifx::attn_f32_kernel<64>;
+    case 96: return ifx::attn_f32_kernel<96>;
+    default: return ifx::attn_f32_kernel<128>;
+    }
+}
+
 // One timing sample (a pair of HIP events around what a call enqueues), taken only while
 // profiling is on and the stream is not being captured (an event recorded into a graph has no
 // time of its own to read back).  A sample that is not closed by end() - the call failed in
@@ -462,8 +474,8 @@ int ifx_kv_cache_configure(ifx_kv_cache *c, int64_t block_tokens, int dtype, flo
     if (e == hipSuccess) e = alloc_aux(c, c->stride_blocks, parts, &c->aux, &kn_bytes);
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e == hipSuccess && dtype == IFX_F32)
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(ifx::attn_f32_kernel),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)ifx::attn_f32_lds_bytes(D));
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(f32_kernel(D)), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)ifx::attn_f32_lds_bytes(f32_padded_dim(D), 8));
     if (e == hipSuccess && dtype == IFX_BF16)
         e = hipFuncSetAttribute(reinterpret_cast<const void *>(ifx::attn_bf16_kernel<false, false>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, ifx::BF_LDS_BYTES);
@@ -795,12 +807,28 @@ static int attention_impl(ifx_kv_cache *c, int layer, const void *q, const void 
         else
             hipLaunchKernelGGL((ifx::attn_bf16_kernel<true, true>), dim3(grid), dim3(ifx::BF_THREADS), ifx::BF_LDS_BYTES, s, a);
     } else {
-        dim3 grid((n + ifx::F32_BM - 1) / ifx::F32_BM, H);
-        hipLaunchKernelGGL(ifx::attn_f32_kernel, grid, dim3(256), ifx::attn_f32_lds_bytes(D), s,
-                           static_cast<const float *>(q), reinterpret_cast<const float *>(c->k_of(layer)),
-                           reinterpret_cast<const float *>(c->v_of(layer)), static_cast<const float *>(k_blk),
-                           static_cast<const float *>(v_blk), static_cast<float *>(out), lse, n, (int)cached,
-                           with_block ? n : 0, H, D, c->k_tokens, c->scale, table);
+        const int tiles = (n + ifx::F32_ROWS - 1) / ifx::F32_ROWS;
+        const int64_t groups = (int64_t)tiles * H, per_xcd = (groups + 7) / 8;
+        const int waves = ifx::attn_f32_waves(groups);
+        ifx::attn_f32_args a;
+        a.q = static_cast<const float *>(q);
+        a.kc = reinterpret_cast<const float *>(c->k_of(layer));
+        a.vc = reinterpret_cast<const float *>(c->v_of(layer));
+        a.kb = static_cast<const float *>(k_blk);
+        a.vb = static_cast<const float *>(v_blk);
+        a.out = static_cast<float *>(out);
+        a.lse = lse;
+        a.n = n;
+        a.C = (int)cached;
+        a.n_blk = with_block ? n : 0;
+        a.H = H;
+        a.D = D;
+        a.cache_tokens = c->k_tokens;
+        a.scale = c->scale;
+        a.tiles = tiles;
+        a.per_xcd = (int)per_xcd;
+        a.blocks = table;
+        hipLaunchKernelGGL(f32_kernel(D), dim3((unsigned)(8 * per_xcd)), dim3(64 * waves), ifx::attn_f32_lds_bytes(f32_padded_dim(D), waves), s, a);
     }
     IFX_HIP(hipGetLastError());
     return sample.end();

@@ -1,161 +1,275 @@
-// fp32 block attention (gfx950): fp32 loads, fp32 FMA, accurate expf, online
-// softmax per query row.  A small, simple kernel for the fp32 cache dtype; the
-// bf16 MFMA kernel is the fast path.
+// fp32 block attention for gfx950: fp32 matrix instructions, accurate expf, online softmax.
 //
 // Operation (paper, Introduction, framework paragraph + abstract): every query
 // of the block attends to all resident cached tokens and all tokens of its own
 // block; softmax over that whole key set; no other mask.
+//
+// Shape of the computation
+//   Bound by the fp32 matrix rate (64 flop per cycle and SIMD).  A workgroup owns 16 query rows of a
+//   head; its 4 or 8 wavefronts deal the keys among themselves in subtiles of 16 (wavefront w takes
+//   subtiles w, w + S, ...) and their partial results are combined through LDS at the end.  So even
+//   the 512 rows of a 256-token block with 2 heads are 32 workgroups of 8 busy wavefronts.  Both
+//   contractions run on v_mfma_f32_16x16x4_f32 (fp32 products and sums, nothing is rounded on the
+//   way), transposed so that a lane's scores all belong to one query:
+//     S^T (keys x queries) = K * Q^T          O^T (d x queries) += V^T * P^T
+//   Lane (i = lane % 16, g = lane / 16).  A and B hold row / column i at contraction index g, the
+//   accumulator holds column i, rows 4 g + r.  So register r of S^T is the score of query i against
+//   key 4 g + r, and the exponentials are, as they stand, the B operands of four PV steps in which
+//   lane group g contributes key 4 g + r.  The contraction over d is taken in the order
+//   d = 16 j + 4 g + t, which makes a lane's K operands of four steps 16 contiguous bytes; output
+//   dimension 64 s + 4 row + slab is row `row` of accumulator slab 4 s + slab, which makes its V
+//   operands of four slabs 16 contiguous bytes too (two slabs where only 32 dimensions are left).
+//   Nothing but the end is shared between wavefronts: no barrier in the loop.  V goes from memory
+//   straight into registers (16 lanes read 256 contiguous bytes of a row) and is on its way under the
+//   score MFMAs.  K cannot: 64 lanes would read 16 bytes of a line each, 64 address cycles per
+//   load instead of 16, more than the matrix instructions they feed.  It is copied row by row into a
+//   piece of LDS of the wavefront's own (direct global->LDS loads, the next subtile's in flight
+//   from the moment this one's operands have been read) and read from there, swizzled at 16-byte
+//   granularity so that the 16 rows of a read lie in 16 different bank groups.
+// Measured (1560 rows, 12 heads x 128, 3120 keys): 291 us = 103 TFLOP/s, where the library's plain
+// fp32 matrix product reaches 154 on the same card; 1840 us with fp32 FMA from LDS tiles.  With K
+// straight from memory 393 us; with 32 rows per wavefront (half the bytes per flop, but fewer and
+// larger workgroups) 390 us.  256 rows, 2 heads x 64, 1024 keys, and the block's commit: 19.8 us
+// (118.5 us with 32-row workgroups that do not deal the keys out).
 #pragma once
 #include "ifx_types.hpp"
 
 namespace ifx {
 
-constexpr int F32_BM = 32;   // query rows per workgroup
-constexpr int F32_BN = 64;   // keys per tile
 constexpr int F32_MAXD = 128;
+constexpr int F32_ROWS = 16;  // query rows per workgroup
 
-// LDS rows are padded by 4 floats: 16-byte alignment for the vector reads, and consecutive rows
-// start 4 banks apart, so the 8 key rows a wavefront reads at once do not collide.
-inline size_t attn_f32_lds_bytes(int D)
+struct attn_f32_args {
+    const float *q, *kc, *vc, *kb, *vb;  // [n, H, D]; layer regions [H][cache_tokens][D]; the block's K, V [n, H, D]
+    float *out, *lse;                    // [n, H, D]; [n, H] or nullptr
+    int n, C, n_blk, H, D;               // cached keys (the caller's selection, whole blocks of n tokens), then the block's: n or 0
+    int64_t cache_tokens;
+    float scale;
+    int tiles, per_xcd;                  // workgroups per head; workgroups per XCD
+    ifx_key_blocks blocks;
+};
+
+// Wavefronts per workgroup.  Up to one workgroup per CU: 8, two per SIMD.  Beyond that 4: three
+// workgroups then share a CU, and one's start and end lie under the others' loops (1176
+// workgroups of head_dim 128: 296 us with 4, 317 with 8).
+inline int attn_f32_waves(int64_t workgroups) { return workgroups <= 256 ? 8 : 4; }
+
+// LDS: each wavefront's K subtile during the loop; the partial results take its place afterwards.
+inline size_t attn_f32_lds_bytes(int padded_d, int waves)
 {
-    return sizeof(float) * ((size_t)F32_BM * (D + 4) + (size_t)F32_BN * (D + 4) + (size_t)F32_BN * D +
-                            (size_t)F32_BM * (F32_BN + 4));
+    return (size_t)waves * F32_ROWS * ((size_t)(padded_d + 4) + 2) * sizeof(float);
 }
 
-// grid (ceil(n / 32), H), 256 threads.  Thread t serves query row t/8; the 8 threads of a row
-// split the tile's keys (scores: keys sub, sub+8, ...) and the head dimensions (PV: 4-float chunks
-// sub, sub+8, ...).  All LDS traffic is 16-byte reads: per 4 head dimensions one Q read (the same
-// address for the 8 threads of a row) and 8 K reads feed 32 FMAs; per 4 keys one P read and up to
-// 4 V reads feed 16 FMAs per chunk.  D % 4 == 0, D <= 128.
-__global__ __launch_bounds__(256) void attn_f32_kernel(const float *__restrict__ q,
-                                                      const float *__restrict__ kc,
-                                                      const float *__restrict__ vc,
-                                                      const float *__restrict__ kb,
-                                                      const float *__restrict__ vb, float *__restrict__ out,
-                                                      float *__restrict__ lse, int n, int C, int n_blk, int H, int D,
-                                                      int64_t cache_tokens, float scale, const ifx_key_blocks blocks)
+template <int DP>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) void attn_f32_kernel(const attn_f32_args a)
 {
-    // Keys: C cached tokens (logical order of the caller's selection, whole blocks of n tokens, mapped to physical
-    // tokens by `blocks`), then the n_blk tokens of the current block (n_blk is n or 0).
+    static_assert(DP % 32 == 0 && DP <= F32_MAXD, "");
+    constexpr int KJ = DP / 16;          // 16-byte K chunks of a lane per subtile
+    constexpr int CH = DP / 4;           // 16-byte chunks of a row
+    constexpr int QUADS = DP / 64;       // groups of four accumulator slabs
+    constexpr bool PAIR = DP % 64 != 0;  // and one group of two
+    constexpr int SLABS = DP / 16;
     extern __shared__ __attribute__((aligned(16))) float smem[];
-    const int ldq = D + 4;
-    float *Qs = smem;                        // [32][D+4]
-    float *Ks = Qs + F32_BM * ldq;           // [64][D+4]
-    float *Vs = Ks + F32_BN * ldq;           // [64][D]
-    float *Ps = Vs + F32_BN * D;             // [32][68]
-    const int ldp = F32_BN + 4;
+    typedef __attribute__((address_space(3))) void *lds_ptr;
 
-    const int tid = threadIdx.x;
-    const int h = blockIdx.y;
-    const int row0 = blockIdx.x * F32_BM;
-    const int r = tid >> 3;    // row within tile
-    const int sub = tid & 7;   // position among the row's 8 threads
-    const int Lk = C + n_blk;
-    const int d4n = D >> 2;    // 4-float chunks per row
+    // workgroups are dealt round-robin to the XCDs: each takes a contiguous run of (head, row tile)
+    // items, so that a head's keys are read into as few L2s as possible
+    const int item = (int)(blockIdx.x & 7u) * a.per_xcd + (int)(blockIdx.x >> 3);
+    if (item >= a.H * a.tiles) return;
+    const int h = item / a.tiles, row0 = (item - h * a.tiles) * F32_ROWS;
+    const int n = a.n, H = a.H, D = a.D, C = a.C;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int S = (int)blockDim.x >> 6;
+    const int i16 = lane & 15, g = lane >> 4;
 
-    for (int e = tid; e < F32_BM * d4n; e += 256) {
-        const int rr = e / d4n, c = e - rr * d4n;
+    // A subtile is up to 16 keys that lie in one run of rows: of the cached tokens [0, C), of one block
+    // of a selection, or of the current block.  It is read through a buffer descriptor that starts at
+    // its first row and ends with its last one (rows behind that read as zero and are masked).
+    const bool listed = a.blocks.magic != 0;
+    const int seg_keys = listed ? n : C;              // keys of a cached segment
+    const int seg_subs = (seg_keys + 15) >> 4;        // its subtiles
+    const int cached_subs = listed ? a.blocks.count * seg_subs : seg_subs;
+    const int subs = cached_subs + ((a.n_blk + 15) >> 4);
+    int tab = 0;  // the first 64 entries of a selection, one per lane: a lookup is a lane read
+    auto first_of = [&](int e) __attribute__((always_inline)) -> int {
+        if (a.blocks.list != nullptr) return a.blocks.list[e];
+        return a.blocks.first[e];
+    };
+    if (listed && lane < a.blocks.count) tab = first_of(lane);
+    struct run {
+        int64_t at;            // element offset of the first row, in the cache region or in the block's tensor
+        int stride, keys;      // elements between rows; rows
+        bool cached;
+    };
+    auto run_of = [&](int sub) __attribute__((always_inline)) -> run {
+        if (sub < cached_subs) {
+            int e = 0, first = 0;
+            if (listed) {
+                e = sub / seg_subs;
+                first = e < 64 ? __builtin_amdgcn_readlane(tab, e) : __builtin_amdgcn_readfirstlane(first_of(e));
+            }
+            const int j = 16 * (sub - e * seg_subs);
+            return {((int64_t)h * a.cache_tokens + first + j) * D, D, seg_keys - j, true};
+        }
+        const int j = 16 * (sub - cached_subs);
+        return {((int64_t)j * H + h) * D, H * D, a.n_blk - j, false};
+    };
+    // (the two candidate pointers as numbers: selecting between the pointers themselves makes the
+    // compiler fetch the chosen one from the kernel arguments again)
+    const uintptr_t kc = (uintptr_t)a.kc, kb = (uintptr_t)a.kb, vc = (uintptr_t)a.vc, vb = (uintptr_t)a.vb;
+    auto rsrc_of = [&](const run &r, uintptr_t cache, uintptr_t block) __attribute__((always_inline)) -> __amdgpu_buffer_rsrc_t {
+        const uintptr_t u = (r.cached ? cache : block) + 4 * (uintptr_t)r.at;
+        const uintptr_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
+        const int rows = r.keys < 16 ? r.keys : 16;
+        return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(hi << 32 | lo), 0,
+                                                 __builtin_amdgcn_readfirstlane(4 * ((rows - 1) * r.stride + D)), 0x00020000);
+    };
+    // K copies: LDS slot e = 64 x + lane (x = 0 .. KJ - 1; row e / CH, place e % CH) receives the row's
+    // chunk place ^ z(row).  Dimensions past D are read at dimension 0 and count nothing (Q is zero there).
+    constexpr int ROWS_X = 64 % CH == 0 ? 64 / CH : 0;  // whole rows per copy instruction
+    auto z = [](int r) { return CH % 16 == 0 ? r : r >> 1; };
+    float *const ktile = smem + wave * (F32_ROWS * DP);
+    auto copy_k = [&](int sub) __attribute__((always_inline)) {
+        const run r = run_of(sub);
+        const __amdgpu_buffer_rsrc_t rs = rsrc_of(r, kc, kb);
+#pragma unroll
+        for (int x = 0; x < KJ; ++x) {
+            const int e = 64 * x + lane, row = e / CH, d = 4 * ((e % CH) ^ z(row));
+            // (not const: with arguments that depend on DP the host pass rejects the builtin's size, silently)
+            int off_v = 4 * ((ROWS_X ? lane / CH : row) * r.stride + (d < D ? d : 0)), off_s = 4 * (ROWS_X * x) * r.stride;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(ktile + 256 * x), 16, off_v, off_s, 0, 0);
+        }
+    };
+    // K operand j of a lane: row i16, d = 16 j + 4 g .. + 3, i.e. chunk 4 j + g; z reaches the low 3 or
+    // 4 bits of a chunk number, so the places of j and j + Z_J are a constant apart
+    constexpr int Z_J = CH % 16 == 0 ? 4 : 2;
+    const float *kread[Z_J];
+#pragma unroll
+    for (int j = 0; j < Z_J; ++j) kread[j] = ktile + i16 * DP + 4 * ((4 * j + g) ^ z(i16));
+    f32x4 V[4][QUADS > 0 ? QUADS : 1];
+    f32x2 V2[4];
+    int dv[QUADS > 0 ? QUADS : 1];
+#pragma unroll
+    for (int s = 0; s < QUADS; ++s) dv[s] = 64 * s + 4 * i16 < D ? 64 * s + 4 * i16 : 0;
+    const int dv2 = 64 * QUADS + 2 * i16 < D ? 64 * QUADS + 2 * i16 : 0;
+    auto load_v = [&](int sub) __attribute__((always_inline)) -> int {  // returns the subtile's keys
+        typedef uint32_t raw_u32x4 __attribute__((__vector_size__(16)));
+        typedef uint32_t raw_u32x2 __attribute__((__vector_size__(8)));
+        const run u = run_of(sub);
+        const __amdgpu_buffer_rsrc_t rs = rsrc_of(u, vc, vb);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+#pragma unroll
+            for (int s = 0; s < QUADS; ++s)
+                V[r][s] = __builtin_bit_cast(f32x4, (raw_u32x4)__builtin_amdgcn_raw_buffer_load_b128(rs, 4 * (4 * g * u.stride + dv[s]), 4 * r * u.stride, 0));
+            if constexpr (PAIR)
+                V2[r] = __builtin_bit_cast(f32x2, (raw_u32x2)__builtin_amdgcn_raw_buffer_load_b64(rs, 4 * (4 * g * u.stride + dv2), 4 * r * u.stride, 0));
+        }
+        return u.keys;
+    };
+
+    if (wave < subs) copy_k(wave);
+    f32x4 Q[KJ];
+    {
+        const int i = row0 + i16;
+        const float *qp = a.q + ((int64_t)(i < n ? i : n - 1) * H + h) * D;
+#pragma unroll
+        for (int j = 0; j < KJ; ++j) {
+            const int d = 16 * j + 4 * g;
+            Q[j] = *reinterpret_cast<const f32x4 *>(qp + (d < D ? d : 0));
+            if (d >= D) Q[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+    f32x4 O[SLABS];
+#pragma unroll
+    for (int s = 0; s < SLABS; ++s) O[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m = -INFINITY, l = 0.f;  // running maximum of the scaled scores (per query), this lane's share of the row sum
+
+    for (int sub = wave; sub < subs; sub += S) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the K copies (V has been consumed) are in LDS
+        f32x4 K[KJ];
+#pragma unroll
+        for (int j = 0; j < KJ; ++j) K[j] = *reinterpret_cast<const f32x4 *>(kread[j % Z_J] + 16 * (j - j % Z_J));
+        const int keys = load_v(sub);
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this subtile's operands are in registers, the tile is free
+        __builtin_amdgcn_sched_barrier(0);
+        copy_k(sub + S < subs ? sub + S : sub);  // (always: the wait counts then know what is in flight)
+        f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < KJ; ++c)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) s = __builtin_amdgcn_mfma_f32_16x16x4f32(K[c][t], Q[c][t], s, 0, 0, 0);
+        s *= a.scale;
+        if (keys < 16) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (4 * g + r >= keys) s[r] = -INFINITY;
+        }
+        float t = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+        t = fmaxf(t, __shfl_xor(t, 16));
+        t = fmaxf(t, __shfl_xor(t, 32));
+        if (__any(t > m)) {
+            const float m_new = fmaxf(m, t);      // finite: every subtile holds at least one key
+            const float alpha = expf(m - m_new);  // 0 on the first one
+            l *= alpha;
+#pragma unroll
+            for (int e = 0; e < SLABS; ++e) O[e] *= alpha;
+            m = m_new;
+        }
+        f32x4 p;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            p[r] = expf(s[r] - m);
+            l += p[r];
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int e = 0; e < SLABS; ++e)
+                O[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(e < 4 * QUADS ? V[r][e >> 2][e & 3] : V2[r][e & 1], p[r], O[e], 0, 0, 0);
+    }
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+
+    // ---- combine the wavefronts' shares of every row: partial O, maximum and sum through LDS
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // (the copy behind the last subtile has landed)
+    __syncthreads();
+    constexpr int LD = DP + 4;  // rows 4 floats apart from a multiple of the banks
+    float *ml = smem + S * F32_ROWS * LD;
+    {
+        const int w = wave * F32_ROWS + i16;
+        float *dst = smem + w * LD;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+#pragma unroll
+            for (int s = 0; s < QUADS; ++s)
+                *reinterpret_cast<f32x4 *>(dst + 64 * s + 16 * g + 4 * r) = f32x4{O[4 * s][r], O[4 * s + 1][r], O[4 * s + 2][r], O[4 * s + 3][r]};
+            if constexpr (PAIR) *reinterpret_cast<f32x2 *>(dst + 64 * QUADS + 8 * g + 2 * r) = f32x2{O[SLABS - 2][r], O[SLABS - 1][r]};
+        }
+        if (g == 0) {
+            ml[2 * w] = m;
+            ml[2 * w + 1] = l;
+        }
+    }
+    __syncthreads();
+    for (int e = tid; e < F32_ROWS * CH; e += (int)blockDim.x) {
+        const int rr = e / CH, c = e % CH;
         const int i = row0 + rr;
-        f32x4 v = {0.f, 0.f, 0.f, 0.f};
-        if (i < n) v = *reinterpret_cast<const f32x4 *>(q + ((int64_t)i * H + h) * D + 4 * c);
-        *reinterpret_cast<f32x4 *>(Qs + rr * ldq + 4 * c) = v;
-    }
-
-    constexpr int MAXC = F32_MAXD / 32;  // 4-float output chunks per thread
-    f32x4 acc[MAXC];
-#pragma unroll
-    for (int w = 0; w < MAXC; ++w) acc[w] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float m = -INFINITY, l = 0.0f;
-
-    for (int j0 = 0; j0 < Lk; j0 += F32_BN) {
-        __syncthreads();  // previous tile fully consumed (also orders the Q fill)
-        for (int e = tid; e < F32_BN * d4n; e += 256) {
-            const int jj = e / d4n, c = e - jj * d4n;
-            const int j = j0 + jj;
-            f32x4 kv = {0.f, 0.f, 0.f, 0.f}, vv = {0.f, 0.f, 0.f, 0.f};
-            if (j < C) {
-                const int jp = blocks.magic ? blocks.first_token(j / n) + j % n : j;  // key j of the selection is physical token jp
-                const int64_t off = ((int64_t)h * cache_tokens + jp) * D + 4 * c;
-                kv = *reinterpret_cast<const f32x4 *>(kc + off);
-                vv = *reinterpret_cast<const f32x4 *>(vc + off);
-            } else if (j < Lk) {
-                const int64_t off = ((int64_t)(j - C) * H + h) * D + 4 * c;
-                kv = *reinterpret_cast<const f32x4 *>(kb + off);
-                vv = *reinterpret_cast<const f32x4 *>(vb + off);
-            }
-            *reinterpret_cast<f32x4 *>(Ks + jj * ldq + 4 * c) = kv;
-            *reinterpret_cast<f32x4 *>(Vs + jj * D + 4 * c) = vv;
+        if (i >= n || 4 * c >= D) continue;
+        float M = -INFINITY;  // finite in the end: wavefront 0 had at least one key
+        for (int s = 0; s < S; ++s) M = fmaxf(M, ml[2 * (s * F32_ROWS + rr)]);
+        float sum = 0.f;
+        f32x4 o = {0.f, 0.f, 0.f, 0.f};
+        for (int s = 0; s < S; ++s) {
+            const int w = s * F32_ROWS + rr;
+            const float f = expf(ml[2 * w] - M);  // 0 for a wavefront without keys
+            sum += f * ml[2 * w + 1];
+            o += f * *reinterpret_cast<const f32x4 *>(smem + w * LD + 4 * c);
         }
-        __syncthreads();
-
-        // scores of row r against keys sub, sub+8, ...
-        float s[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) s[u] = 0.0f;
-        for (int c = 0; c < d4n; ++c) {
-            const f32x4 qv = *reinterpret_cast<const f32x4 *>(Qs + r * ldq + 4 * c);
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const f32x4 kv = *reinterpret_cast<const f32x4 *>(Ks + (sub + 8 * u) * ldq + 4 * c);
-                s[u] = fmaf(qv[0], kv[0], s[u]);
-                s[u] = fmaf(qv[1], kv[1], s[u]);
-                s[u] = fmaf(qv[2], kv[2], s[u]);
-                s[u] = fmaf(qv[3], kv[3], s[u]);
-            }
-        }
-        float tmax = -INFINITY;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            s[u] = (j0 + sub + 8 * u < Lk) ? s[u] * scale : -INFINITY;
-            tmax = fmaxf(tmax, s[u]);
-        }
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 1));
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 2));
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 4));
-        const float m_new = fmaxf(m, tmax);  // finite: each tile holds at least one valid key
-        const float alpha = expf(m - m_new);  // 0 on the first tile
-        float psum = 0.0f;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const float p = expf(s[u] - m_new);
-            psum += p;
-            Ps[r * ldp + sub + 8 * u] = p;
-        }
-        psum += __shfl_xor(psum, 1);
-        psum += __shfl_xor(psum, 2);
-        psum += __shfl_xor(psum, 4);
-        l = l * alpha + psum;
-        m = m_new;
-        __syncthreads();
-
-        // out[r][4 (sub + 8w) .. + 3] += sum_j P[r][j] * V[j][same]
-#pragma unroll
-        for (int w = 0; w < MAXC; ++w) acc[w] *= alpha;
-        for (int j4 = 0; j4 < F32_BN; j4 += 4) {
-            const f32x4 p = *reinterpret_cast<const f32x4 *>(Ps + r * ldp + j4);
-#pragma unroll
-            for (int w = 0; w < MAXC; ++w) {
-                const int c = sub + 8 * w;
-                if (c < d4n) {
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        const f32x4 v = *reinterpret_cast<const f32x4 *>(Vs + (j4 + t) * D + 4 * c);
-                        acc[w] += p[t] * v;
-                    }
-                }
-            }
-        }
-    }
-
-    const int i = row0 + r;
-    if (i < n) {
-        if (lse != nullptr && sub == 0) lse[(int64_t)i * H + h] = m + logf(l);
-        const float inv = 1.0f / l;
-#pragma unroll
-        for (int w = 0; w < MAXC; ++w) {
-            const int c = sub + 8 * w;
-            if (c < d4n) *reinterpret_cast<f32x4 *>(out + ((int64_t)i * H + h) * D + 4 * c) = acc[w] * inv;
-        }
+        if (a.lse != nullptr && c == 0) a.lse[(int64_t)i * H + h] = M + logf(sum);
+        const float inv = 1.0f / sum;
+        *reinterpret_cast<f32x4 *>(a.out + ((int64_t)i * H + h) * D + 4 * c) = o * inv;
     }
 }
 

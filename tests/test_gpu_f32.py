@@ -1,0 +1,48 @@
+"""GPU parity of the fp32 attention kernel at the edges of its tiling: 16-row tiles, 16-key subtiles
+dealt to 4 or 8 wavefronts, head_dim padded to a multiple of 32, key runs that end inside a subtile
+(whole cache, listed blocks, current block)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2511_20714_amd import binding as ifx
+from paper_2511_20714_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,H,D,cap,commits,blocks,with_block", [
+    (1, 1, 8, 4, 3, None, True),        # one row, four keys: seven of eight wavefronts without a key
+    (15, 2, 40, 2, 3, None, True),      # head_dim 40 in 64, ragged rows and keys
+    (16, 3, 64, 3, 3, [2, 0], False),   # exact tiles, a selection out of order, no current block
+    (17, 2, 72, 3, 4, [1, 2], True),    # head_dim 72 in 96; every listed block ends one key into a subtile
+    (33, 5, 96, 2, 2, None, True),
+    (129, 3, 128, 2, 3, [1], True),
+    (8, 1, 128, 70, 72, list(range(69, -1, -1)), True),   # more listed blocks than a wavefront has lanes
+    (1370, 3, 128, 1, 1, None, True),   # 258 workgroups: the first size with 4 wavefronts each
+    (1366, 3, 32, 1, 0, None, True),    # 258 of the smallest head_dim, no cached keys
+])
+def test_f32_attention_at_tile_edges(gpu_device, n, H, D, cap, commits, blocks, with_block):
+    dev = gpu_device
+    with ifx.KVCache(1, H, D, cap * n, n, ifx.IFX_F32) as cache:
+        oc = oracle.BlockCacheOracle(cap)
+        for b in range(commits):
+            _, k, v = synth.draw_qkv(61, b, 0, 0, n, H, D, torch.float32, dev)
+            cache.commit(0, k, v)
+            oc.commit(synth.to_f64_numpy(k), synth.to_f64_numpy(v))
+        q, k, v = synth.draw_qkv(61, 999, 0, 0, n, H, D, torch.float32, dev)
+        if not with_block:
+            k = v = None
+        out = torch.full((n, H, D), float("nan"), device=dev)
+        lse = torch.full((n, H), float("nan"), device=dev)
+        cache.attention_blocks(0, q, k, v, blocks, out, lse)
+        torch.cuda.synchronize()
+        assert torch.isfinite(out).all() and torch.isfinite(lse).all()
+        kc, vc = oc.logical() if blocks is None else oc.logical([(b, 1) for b in blocks])
+        r = np.unique(np.concatenate([np.arange(min(n, 40)), np.arange(max(0, n - 40), n), np.random.default_rng(1).integers(0, n, 40)]))
+        rows, heads = np.repeat(r, H), np.tile(np.arange(H), len(r))
+        want, want_lse = oracle.attention_rows(synth.to_f64_numpy(q), kc, vc, None if k is None else synth.to_f64_numpy(k),
+                                               None if v is None else synth.to_f64_numpy(v), rows, heads)
+        assert np.abs(synth.to_f64_numpy(out)[rows, heads] - want).max() <= 1e-5
+        assert np.abs(synth.to_f64_numpy(lse)[rows, heads] - want_lse).max() <= 2e-5
