@@ -777,6 +777,9 @@ __global__ __launch_bounds__(BF_THREADS, 1) void attn_bf16_kernel(const attn_bf1
                 }
             }
         }
+        // Nothing left: the steady tiles' last copies (of tiles past the end, zeros) may still be on their
+        // way into slots that the next phase fills, from other wavefronts' copies where the layouts differ.
+        if (i * BF_BN == Lp) wait_loads_and_sync<0>();
         // The last tile, one 32-key subtile at a time without software pipelining: key mask and
         // (running maximum) reference check, exponentials and PV of the current subtile, then the
         // scores of the next.  Sa holds the scores of subtile (i, 0), not yet masked or checked
