@@ -345,6 +345,8 @@ int ifx_ring_grow(ifx_ring *ring, int64_t new_capacity_blocks, int in_place);
 /* ---- launch shape of the bf16 attention kernel, for CPU tests -------------------------------
  * No passage of the paper: which workgroup takes which head and which query rows is this
  * library's own arithmetic (host integers that the kernel decodes with the same function).
+ * They describe the launch with up to 256 query rows per workgroup; a call with too few rows to
+ * occupy the chip that way runs with smaller workgroups among which the keys are dealt.
  * Pure host code, no device call.
  *
  * ifx_attention_launch_grid: workgroups of one attention launch over blocks of `block_tokens`

@@ -132,6 +132,16 @@ void (*f32_kernel(int D))(const ifx::attn_f32_args)
     }
 }
 
+// bf16 attention: the instance for a block table or none, an fp8 or a bf16 cache, one or two key groups.
+void (*bf16_kernel(bool table, bool fp8, int groups))(const ifx::attn_bf16_args)
+{
+    if (groups == 2)
+        return table ? fp8 ? ifx::attn_bf16_kernel<true, true, 2> : ifx::attn_bf16_kernel<true, false, 2>
+                     : fp8 ? ifx::attn_bf16_kernel<false, true, 2> : ifx::attn_bf16_kernel<false, false, 2>;
+    return table ? fp8 ? ifx::attn_bf16_kernel<true, true> : ifx::attn_bf16_kernel<true, false>
+                 : fp8 ? ifx::attn_bf16_kernel<false, true> : ifx::attn_bf16_kernel<false, false>;
+}
+
 // One timing sample (a pair of HIP events around what a call enqueues), taken only while
 // profiling is on and the stream is not being captured (an event recorded into a graph has no
 // time of its own to read back).  A sample that is not closed by end() - the call failed in
@@ -476,18 +486,11 @@ int ifx_kv_cache_configure(ifx_kv_cache *c, int64_t block_tokens, int dtype, flo
     if (e == hipSuccess && dtype == IFX_F32)
         e = hipFuncSetAttribute(reinterpret_cast<const void *>(f32_kernel(D)), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)ifx::attn_f32_lds_bytes(f32_padded_dim(D), 8));
-    if (e == hipSuccess && dtype == IFX_BF16)
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(ifx::attn_bf16_kernel<false, false>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, ifx::BF_LDS_BYTES);
-    if (e == hipSuccess && dtype == IFX_BF16)
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(ifx::attn_bf16_kernel<true, false>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, ifx::BF_LDS_BYTES);
-    if (e == hipSuccess && dtype == IFX_FP8_E4M3)
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(ifx::attn_bf16_kernel<false, true>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, ifx::BF_LDS_BYTES);
-    if (e == hipSuccess && dtype == IFX_FP8_E4M3)
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(ifx::attn_bf16_kernel<true, true>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, ifx::BF_LDS_BYTES);
+    for (const bool table : {false, true})
+        for (const int groups : {1, 2})
+            if (e == hipSuccess && dtype != IFX_F32)
+                e = hipFuncSetAttribute(reinterpret_cast<const void *>(bf16_kernel(table, dtype == IFX_FP8_E4M3, groups)),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, ifx::BF_LDS_BYTES);
     bool host_ok = e == hipSuccess;
     if (host_ok) {
         try {
@@ -774,6 +777,7 @@ static int attention_impl(ifx_kv_cache *c, int layer, const void *q, const void 
     timing_sample sample(c, c->attn_events, s);  // the whole call: everything it enqueues lies between the two events
     int rc = sample.begin();
     if (rc) return rc;
+    const int groups = c->mfma() ? ifx::attn_groups_for(n, H) : 0;
     if (c->mfma()) {
         ifx::attn_bf16_args a;
         a.q = static_cast<const __bf16 *>(q);
@@ -794,18 +798,10 @@ static int attention_impl(ifx_kv_cache *c, int layer, const void *q, const void 
         a.cap_blocks = (int)c->stride_blocks;
         a.parts = c->parts;
         a.resident_blocks = (int)ring.resident();
-        a.shape = ifx::attn_shape_for(n, H);
-        const unsigned grid = a.shape.grid;
+        a.shape = ifx::attn_shape_for(n, H, ifx::BF_WAVES / groups);
         a.blocks = table;
-        const bool fp8 = c->dtype == IFX_FP8_E4M3;
-        if (!use_table && !fp8)
-            hipLaunchKernelGGL((ifx::attn_bf16_kernel<false, false>), dim3(grid), dim3(ifx::BF_THREADS), ifx::BF_LDS_BYTES, s, a);
-        else if (!fp8)
-            hipLaunchKernelGGL((ifx::attn_bf16_kernel<true, false>), dim3(grid), dim3(ifx::BF_THREADS), ifx::BF_LDS_BYTES, s, a);
-        else if (!use_table)
-            hipLaunchKernelGGL((ifx::attn_bf16_kernel<false, true>), dim3(grid), dim3(ifx::BF_THREADS), ifx::BF_LDS_BYTES, s, a);
-        else
-            hipLaunchKernelGGL((ifx::attn_bf16_kernel<true, true>), dim3(grid), dim3(ifx::BF_THREADS), ifx::BF_LDS_BYTES, s, a);
+        hipLaunchKernelGGL(bf16_kernel(use_table, c->dtype == IFX_FP8_E4M3, groups), dim3(a.shape.grid), dim3(ifx::BF_THREADS),
+                           ifx::BF_LDS_BYTES, s, a);
     } else {
         const int tiles = (n + ifx::F32_ROWS - 1) / ifx::F32_ROWS;
         const int64_t groups = (int64_t)tiles * H, per_xcd = (groups + 7) / 8;

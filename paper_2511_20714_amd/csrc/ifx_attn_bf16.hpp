@@ -125,12 +125,13 @@ struct tile_offs {
 
 // Wait until at most `keep` of this wave's global->LDS loads are still in flight (they complete in
 // issue order), then meet the other waves.  No fence: LDS data of completed loads is visible.
-template <int keep>
+// `reads_too`: wait for this wave's LDS reads as well (a slot they read is refilled right behind the barrier).
+template <int keep, bool reads_too = false>
 __device__ __forceinline__ void wait_loads_and_sync()
 {
-    // s_waitcnt vmcnt(keep) only: expcnt and lgkmcnt fields at their no-wait maxima.  A builtin
-    // rather than inline asm, so the compiler keeps exact track of its own LDS read counters.
-    __builtin_amdgcn_s_waitcnt((keep & 0xF) | (7 << 4) | (15 << 8) | ((keep >> 4) << 14));
+    // s_waitcnt vmcnt(keep) only: expcnt and (unless asked for) lgkmcnt fields at their no-wait maxima.
+    // A builtin rather than inline asm, so the compiler keeps exact track of its own LDS read counters.
+    __builtin_amdgcn_s_waitcnt((keep & 0xF) | (7 << 4) | ((reads_too ? 0 : 15) << 8) | ((keep >> 4) << 14));
     __builtin_amdgcn_s_barrier();
 }
 
@@ -183,7 +184,18 @@ struct src_block {
 // are loaded into registers a tile ahead, widened (exactly) to bf16 and written into the same LDS
 // tile rings the bf16 cache's tiles are copied into; everything downstream is the same code and
 // the same arithmetic.  The current block is bf16 either way.
-template <bool SEG, bool FP8 = false>
+// GROUPS == 2: for calls whose rows are too few to occupy the chip (attn_groups_for).  A workgroup
+// holds up to 4 row wavefronts, each of them twice: wavefront w owns the rows of row wavefront
+// w / 2 and takes subtile w % 2 of every 64-key tile; the two shares of a row are put together
+// through LDS at the end.  1560 rows of 12 heads are 84 workgroups of 256 rows, and 156 of 128:
+// 176 -> 111 us against 10920 keys (0.60 us per tile, half of a whole tile's 0.97 at best; the
+// rest is the second barrier and the doubled copies).  The tiles, their copies and the ring are
+// those of GROUPS == 1; a tile is one step per wavefront instead of two, so K is copied five tiles
+// ahead and V three (K operands are in registers two tiles before their V is needed).  The two
+// wavefronts of a SIMD (w, w + 4) are kept half a step apart by a barrier in the middle of the
+// step, one in its score part while the other is in its PV part (4 % faster than side by side; over
+// an fp8 cache's keys, whose tiles are widened in the PV part, 8 % slower: not there).
+template <bool SEG, bool FP8 = false, int GROUPS = 1>
 __global__ __launch_bounds__(BF_THREADS, 1) void attn_bf16_kernel(const attn_bf16_args a)
 {
     constexpr int KEYB = FP8 ? BF_D : BF_D * 2;  // bytes of a cached key row, and of a key's share of its V granule
@@ -201,8 +213,10 @@ __global__ __launch_bounds__(BF_THREADS, 1) void attn_bf16_kernel(const attn_bf1
     const float c2 = a.scale_log2;
 
     // ---- Q: B operand of S^T = K Q^T; lane = query lq, d = 16 s + 8 lh + [0,8)
-    const int waves_here = item.waves;  // wavefronts of this workgroup that hold rows
-    const int qi = item.row0 + wave * 32 + lq;
+    const int waves_here = item.waves * GROUPS;  // wavefronts of this workgroup that hold rows
+    const int group = GROUPS == 2 ? wave & 1 : 0;   // which half of every tile's keys this wavefront takes
+    const int group_at = group * (32 * 256);        // byte offset of that half in a tile, K and V alike
+    const int qi = item.row0 + (wave / GROUPS) * 32 + lq;
     const int qi_c = qi < n ? qi : n - 1;
     bf16x8 Q[8];
     {
@@ -243,8 +257,8 @@ __global__ __launch_bounds__(BF_THREADS, 1) void attn_bf16_kernel(const attn_bf1
     const int kz = lh ^ (pkey & 15);
     int koff[8];
 #pragma unroll
-    for (int s = 0; s < 8; ++s) koff[s] = BF_LDS_K0 + pkey * 256 + (((2 * s) ^ kz) << 4);
-    const int voff = BF_LDS_V0 + lh * 2048 + lq * 16;
+    for (int s = 0; s < 8; ++s) koff[s] = BF_LDS_K0 + group_at + pkey * 256 + (((2 * s) ^ kz) << 4);
+    const int voff = BF_LDS_V0 + group_at + lh * 2048 + lq * 16;
     // Row-major V tile of the current block ([64 keys][128 d], 16-byte chunk c of key row r stored
     // at chunk c ^ 4 (r & 3)): lane l of a transposing read supplies the address of 8 bytes of row
     // (l & 15) / 4 of a group of 4 key rows, d columns 16 (l / 16 & 1) + 4 (l & 3) .. + 3 of a
@@ -253,7 +267,7 @@ __global__ __launch_bounds__(BF_THREADS, 1) void attn_bf16_kernel(const attn_bf1
     int vtoff[4];
     {
         const int l16 = lane & 15, g = lane >> 4;
-        const int base = BF_LDS_V0 + (8 * (g >> 1) + (l16 >> 2)) * 256 + (2 * (g & 1) + ((l16 & 3) >> 1)) * 16 + 8 * (l16 & 1);
+        const int base = BF_LDS_V0 + group_at + (8 * (g >> 1) + (l16 >> 2)) * 256 + (2 * (g & 1) + ((l16 & 3) >> 1)) * 16 + 8 * (l16 & 1);
 #pragma unroll
         for (int sl = 0; sl < 4; ++sl) vtoff[sl] = base + ((sl ^ (l16 >> 2)) << 6);
     }
@@ -585,31 +599,14 @@ __global__ __launch_bounds__(BF_THREADS, 1) void attn_bf16_kernel(const attn_bf1
     //   subtile's V data.  Only for subtiles that lie wholly inside the phase (no key masking).
     //   load_tag: which half of the tile three ahead this step brings in (0: K, 1: V), two
     //   global->LDS loads placed between the PV MFMAs; j_load / buf_load: its first key and ring slot.
-    auto halfstep = [&](auto src, auto bounded_tag, auto load_tag, auto idle_tag, f32x16 &Scur, f32x16 &Snext,
-                        int koffs_after, int voffs_cur, int j_load, int buf_load) IFX_INLINE {
+    //   2 (two key groups, one step per tile): K of that tile and V of the tile at j_v / buf_v
+    //   (codes: the tile at j_v is widened, the one at j_load, two further, starts on its way).
+    // first part: scores of the next subtile, V operands and exponentials (E, and P in bf16) of the current one
+    auto score_part = [&](auto src, auto bounded_tag, f32x16 &Scur, f32x16 &Snext, int voffs_cur, f32x16 &E, bf16x8 (&P)[2]) IFX_INLINE {
         constexpr bool BOUNDED = decltype(bounded_tag)::value;
         constexpr bool EXACT = decltype(bounded_tag)::exact;
         constexpr float HEADROOM = EXACT ? BF_HEADROOM_EXACT : BF_HEADROOM;
         constexpr int V_READS = decltype(src)::blk ? 2 : 1;  // LDS reads per V operand
-        bf16x8 P[2];
-        f32x16 E;
-        constexpr bool CODES = FP8 && !decltype(src)::blk;  // this phase's tiles come as E4M3 codes through registers
-        tile_offs offs;
-        if constexpr (!CODES) offs = decltype(load_tag)::value == 0 ? k_offs(src, j_load) : v_offs(src, j_load);  // for the copies of the PV phase
-        if constexpr (decltype(idle_tag)::value) {
-            // a wavefront without a query row: its share of the tile copies and nothing else
-            if constexpr (CODES) {
-                if constexpr (decltype(load_tag)::value == 0)
-                    fp8_load(j_load, buf_load & 1);
-                else
-                    fp8_store((buf_load + 1) & 1, (buf_load + 3) & 3);
-            } else if constexpr (decltype(load_tag)::value == 0) {
-                issue_k_at(src, offs, buf_load);
-            } else {
-                issue_v_at(src, offs, buf_load);
-            }
-            return;
-        }
         qk(Kop, Snext);
         v_fetch(src, voffs_cur, Vop);
         exps(Scur, E, P);
@@ -643,36 +640,72 @@ __global__ __launch_bounds__(BF_THREADS, 1) void attn_bf16_kernel(const attn_bf1
         // never held up, the other one's MFMAs fill the gaps.  (The instruction ends a scheduling
         // region, so each phase's instructions and its group sequence sit on their own side of it.)
         __builtin_amdgcn_s_setprio(0);
-        if constexpr (CODES) {
-            // first half of tile i: the codes of tile i + 3 start on their way into register set
-            // (i + 3) % 2; second half: those of tile i + 2 (set i % 2, asked for a tile ago) are
-            // widened into ring slot (i + 2) % 4, which tile i - 2 left free
-            if constexpr (decltype(load_tag)::value == 0)
-                fp8_load(j_load, buf_load & 1);
-            else
-                fp8_store((buf_load + 1) & 1, (buf_load + 3) & 3);
-        } else if constexpr (decltype(load_tag)::value == 0) {
-            issue_k_at(src, offs, buf_load);
-        } else {
-            issue_v_at(src, offs, buf_load);
+    };
+    // What a step brings into the ring: the scalar offsets of its copies ...
+    struct copy_offs {
+        tile_offs first, second;
+    };
+    auto copies_of = [&](auto src, auto load_tag, int j_load, int j_v) IFX_INLINE -> copy_offs {
+        constexpr int LOADS = decltype(load_tag)::value;
+        copy_offs c = {};
+        if constexpr (!(FP8 && !decltype(src)::blk)) {
+            c.first = LOADS == 1 ? v_offs(src, j_load) : k_offs(src, j_load);
+            if constexpr (LOADS == 2) c.second = v_offs(src, j_v);
         }
+        return c;
+    };
+    // ... and the copies.  Codes (fp8 cache): first half of tile i: the codes of tile i + 3 start on
+    // their way into register set (i + 3) % 2; second half: those of tile i + 2 (set i % 2, asked for
+    // a tile ago) are widened into ring slot (i + 2) % 4, which tile i - 2 left free.  Two key groups:
+    // tile i + 3 is widened, then the codes of tile i + 5 start on their way into the same set.
+    auto bring_in = [&](auto src, auto load_tag, const copy_offs &offs, int j_load, int buf_load, int buf_v) IFX_INLINE {
+        constexpr int LOADS = decltype(load_tag)::value;
+        if constexpr (FP8 && !decltype(src)::blk) {
+            if constexpr (LOADS == 0) {
+                fp8_load(j_load, buf_load & 1);
+            } else if constexpr (LOADS == 1) {
+                fp8_store((buf_load + 1) & 1, (buf_load + 3) & 3);
+            } else {
+                fp8_store(buf_v & 1, buf_v);
+                fp8_load(j_load, buf_load & 1);
+            }
+        } else if constexpr (LOADS == 1) {
+            issue_v_at(src, offs.first, buf_load);
+        } else {
+            if constexpr (LOADS == 2) issue_v_at(src, offs.second, buf_v);
+            issue_k_at(src, offs.first, buf_load);
+        }
+    };
+    // second part: the PV product and row sum of the current subtile, K operands of the one after the next
+    auto pv_part = [&](auto src, auto bounded_tag, auto load_tag, f32x16 &E, const bf16x8 (&P)[2], int koffs_after, const copy_offs &offs,
+                       int j_load, int buf_load, int buf_v) IFX_INLINE {
+        constexpr int LOADS = decltype(load_tag)::value;
+        constexpr bool BOUNDED = decltype(bounded_tag)::value;
+        constexpr bool EXACT = decltype(bounded_tag)::exact;
+        constexpr bool CODES = FP8 && !decltype(src)::blk;  // this phase's tiles come as E4M3 codes through registers
+        bring_in(src, load_tag, offs, j_load, buf_load, buf_v);
         pv(Vop, P);
         k_fetch(koffs_after, Kop);
         if constexpr (EXACT) as_rounded(E, P);  // (here, under the PV MFMAs: the score phase has no VALU slots to spare)
         row_sum(E);
         // (a step that widens a tile of codes: its 16 conversions and 4 LDS stores go under the first
         // PV MFMAs, so that the stores have landed when the tile's barrier asks for them)
-        constexpr bool WIDENS = CODES && decltype(load_tag)::value == 1;
+        constexpr bool WIDENS = CODES && LOADS != 0;
 #pragma unroll
         for (int g = 0; g < 8; ++g) {  // PV MFMAs: K operand reads, row sum, the two loads
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            // (two key groups: the K operands' slot is refilled right behind the step's barrier, which
+            // therefore waits for these reads: under the first four MFMAs, so that they are back by then)
+            if (LOADS != 2)
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            else if (g < 4)
+                __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
             if (WIDENS && g < 4)
                 __builtin_amdgcn_sched_group_barrier(0x002, EXACT ? 8 : 6, 0);
             else
                 __builtin_amdgcn_sched_group_barrier(0x002, EXACT ? 4 : 2, 0);
             if (WIDENS && (g == 1 || g == 3)) __builtin_amdgcn_sched_group_barrier(0x200, 2, 0);
-            if (g == 1 || g == 5) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+            if (g == 1 || g == 5 || (LOADS == 2 && !CODES && (g == 3 || g == 6))) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
         }
         if constexpr (BOUNDED) {
             // Never taken (n > 0).  Without a use of the row sum at the end of every step the
@@ -685,6 +718,23 @@ __global__ __launch_bounds__(BF_THREADS, 1) void attn_bf16_kernel(const attn_bf1
             }
         }
         __builtin_amdgcn_s_setprio(1);
+    };
+    // Two key groups, tiles copied into LDS: a barrier between the parts (see phase_pair).
+    auto staggered = [](auto src, auto load_tag) constexpr { return decltype(load_tag)::value == 2 && !(FP8 && !decltype(src)::blk); };
+    auto halfstep = [&](auto src, auto bounded_tag, auto load_tag, auto idle_tag, f32x16 &Scur, f32x16 &Snext,
+                        int koffs_after, int voffs_cur, int j_load, int buf_load, int j_v = 0, int buf_v = 0) IFX_INLINE {
+        const copy_offs offs = copies_of(src, load_tag, j_load, j_v);  // for the copies of the PV phase
+        if constexpr (decltype(idle_tag)::value) {
+            // a wavefront without a query row: its share of the tile copies and nothing else
+            if constexpr (staggered(src, load_tag)) __builtin_amdgcn_s_barrier();
+            bring_in(src, load_tag, offs, j_load, buf_load, buf_v);
+        } else {
+            bf16x8 P[2];
+            f32x16 E;
+            score_part(src, bounded_tag, Scur, Snext, voffs_cur, E, P);
+            if constexpr (staggered(src, load_tag)) __builtin_amdgcn_s_barrier();
+            pv_part(src, bounded_tag, load_tag, E, P, koffs_after, offs, j_load, buf_load, buf_v);
+        }
     };
 
     // One phase: the Lp > 0 keys of one source, tiles of 64, through the accumulators O, l_acc and
@@ -822,6 +872,113 @@ __global__ __launch_bounds__(BF_THREADS, 1) void attn_bf16_kernel(const attn_bf1
         }
     };
 
+    // The same with two key groups: this wavefront's subtile `group` of every tile.  Entered and left
+    // like `phase`.  During tile i: K(i + 2) and V(i) are read, K(i + 5) and V(i + 3) are issued into the
+    // slots that K(i + 1) and V(i - 1) left free at the barrier before.  Wavefronts 4 .. 7 run half a
+    // step (one barrier) behind: what the others read in step i + 1 must have landed by the end of
+    // their step i - 1 + 1/2, so at the end of step i only K(i + 4), V(i + 3) and K(i + 5) may still be
+    // in flight, and its K reads must be back, as their slot is refilled one barrier later.
+    auto phase_pair = [&](auto src, auto bounded_tag, auto idle_tag, const int Lp) IFX_INLINE {
+        constexpr bool BOUNDED = decltype(bounded_tag)::value;
+        constexpr bool EXACT = decltype(bounded_tag)::exact;
+        constexpr float HEADROOM = EXACT ? BF_HEADROOM_EXACT : BF_HEADROOM;
+        constexpr bool IDLE = decltype(idle_tag)::value;
+        constexpr bool CODES = FP8 && !decltype(src)::blk;
+        const int j_own = 32 * group;  // first key of this wavefront's subtile in a tile
+        if constexpr (CODES) {
+            // tiles 0, 1 and 2 widened into their ring slots, the codes of tiles 3 and 4 on their way
+            fp8_load(0, 0);
+            fp8_load(BF_BN, 1);
+            fp8_store(0, 0);
+            fp8_load(2 * BF_BN, 0);
+            fp8_store(1, 1);
+            fp8_load(3 * BF_BN, 1);
+            fp8_store(0, 2);
+            fp8_load(4 * BF_BN, 0);
+            wait_lds_and_sync();
+        } else {
+#pragma unroll
+            for (int t = 0; t < 3; ++t) {
+                issue_k(src, t * BF_BN, t);
+                issue_v(src, t * BF_BN, t);
+            }
+            issue_k(src, 3 * BF_BN, 3);
+            wait_loads_and_sync<0>();
+        }
+        f32x16 Sa, Sb;
+        if constexpr (!IDLE) {
+            k_fetch(0, Kop);
+            qk(Kop, Sa);
+            if constexpr (!BOUNDED) {
+                // (a phase of 32 keys or fewer leaves the second group without a key, and its reference at -inf)
+                if (j_own < Lp) {
+                    mask_keys(Sa, j_own, Lp);
+                    raise_for(Sa, HEADROOM);
+                }
+            }
+            k_fetch(BF_TILE_BYTES, Kop);
+        }
+        if constexpr (!CODES) {
+            wait_lds_and_sync();  // K(0) is in registers everywhere: its slot is free
+            issue_k(src, 4 * BF_BN, 0);
+        }
+        auto tile_steady = [&](int i, int b, f32x16 &Scur, f32x16 &Snext) IFX_INLINE {
+            halfstep(src, bounded_tag, std::integral_constant<int, 2>{}, idle_tag, Scur, Snext, ((b + 2) % 4) * BF_TILE_BYTES,
+                     b * BF_TILE_BYTES, (i + 5) * BF_BN, (b + 1) % 4, (i + 3) * BF_BN, (b + 3) % 4);
+            if constexpr (CODES)
+                wait_lds_and_sync();
+            else
+                wait_loads_and_sync<3 * BF_NX, true>();
+        };
+        const int n_steady = Lp / BF_BN;
+        if (!CODES && wave >= BF_WAVES / 2) __builtin_amdgcn_s_barrier();  // half a step behind
+        int i = 0;
+        for (; i + 4 <= n_steady; i += 4) {
+            tile_steady(i, 0, Sa, Sb);
+            tile_steady(i + 1, 1, Sb, Sa);
+            tile_steady(i + 2, 2, Sa, Sb);
+            tile_steady(i + 3, 3, Sb, Sa);
+        }
+        if (i < n_steady) {
+            tile_steady(i, 0, Sa, Sb);
+            ++i;
+            if (i < n_steady) {
+                tile_steady(i, 1, Sb, Sa);
+                ++i;
+                if (i < n_steady) {
+                    tile_steady(i, 2, Sa, Sb);
+                    ++i;
+                    if constexpr (!IDLE) Sa = Sb;
+                }
+            } else {
+                if constexpr (!IDLE) Sa = Sb;
+            }
+        }
+        if (!CODES && wave < BF_WAVES / 2) __builtin_amdgcn_s_barrier();
+        // the partial last tile: this wavefront's subtile of it, if that holds a key
+        if constexpr (!IDLE) {
+            const int j_sub = i * BF_BN + j_own;
+            if (j_sub < Lp) {
+                bf16x8 P[2];
+                f32x16 E;
+                mask_keys(Sa, j_sub, Lp);
+                if constexpr (!BOUNDED) raise_for(Sa, HEADROOM);
+                v_fetch(src, (i & 3) * BF_TILE_BYTES, Vop);
+                exps(Sa, E, P);
+                if constexpr (EXACT) as_rounded(E, P);
+                row_sum(E);
+                pv(Vop, P);
+            }
+        }
+        wait_loads_and_sync<0>();  // nothing is on its way into the ring any more, and nobody reads it
+    };
+    auto keys_of = [&](auto src, auto bounded_tag, auto idle_tag, const int Lp) IFX_INLINE {
+        if constexpr (GROUPS == 2)
+            phase_pair(src, bounded_tag, idle_tag, Lp);
+        else
+            phase(src, bounded_tag, idle_tag, Lp);
+    };
+
     // ---- phase 1: the cached keys (a selection: one pass per segment of the list)
     auto cached_keys = [&](auto bounded_tag, auto idle_tag) IFX_INLINE {
         if constexpr (SEG) {
@@ -830,16 +987,17 @@ __global__ __launch_bounds__(BF_THREADS, 1) void attn_bf16_kernel(const attn_bf1
             for (int base = 0; base < total; base += IFX_MAX_KEY_BLOCKS) {
                 const int cnt = total - base < IFX_MAX_KEY_BLOCKS ? total - base : IFX_MAX_KEY_BLOCKS;
                 load_segment(base, cnt);
-                phase(src_cache{}, bounded_tag, idle_tag, cnt * n);
+                keys_of(src_cache{}, bounded_tag, idle_tag, cnt * n);
             }
         } else {
-            phase(src_cache{}, bounded_tag, idle_tag, a.C);
+            keys_of(src_cache{}, bounded_tag, idle_tag, a.C);
         }
     };
     // A wavefront that holds no query row only helps with the copies.
     if (wave >= waves_here) {
         if (a.C > 0) cached_keys(softmax_running{}, std::true_type{});
-        if (a.nb > 0) phase(src_block{}, softmax_running{}, std::true_type{}, a.nb);
+        if (a.nb > 0) keys_of(src_block{}, softmax_running{}, std::true_type{}, a.nb);
+        if constexpr (GROUPS == 2) __builtin_amdgcn_s_barrier();  // the exchange below
         return;
     }
     // A wavefront whose scores the norm bound covers: fixed maximum over the cached keys, then the
@@ -851,33 +1009,74 @@ __global__ __launch_bounds__(BF_THREADS, 1) void attn_bf16_kernel(const attn_bf1
             m_used = m_bound;
             cached_keys(softmax_fixed{}, std::false_type{});
         }
-        if (a.nb > 0) phase(src_block{}, softmax_running{}, std::false_type{}, a.nb);
+        if (a.nb > 0) keys_of(src_block{}, softmax_running{}, std::false_type{}, a.nb);
     } else {
         if (a.C > 0) cached_keys(softmax_running_exact{}, std::false_type{});
-        if (a.nb > 0) phase(src_block{}, softmax_running_exact{}, std::false_type{}, a.nb);
+        if (a.nb > 0) keys_of(src_block{}, softmax_running_exact{}, std::false_type{}, a.nb);
     }
 
     // ---- epilogue: out[q, d] = O^T[d, q] / l;  register r of O[sl] is d = 32 sl + 8 (r/4) + 4 lh + r%4
     const float l_part = (l_acc[0] + l_acc[1]) + (l_acc[2] + l_acc[3]);
-    const float l_tot = l_part + __shfl_xor(l_part, 32);
+    float l_tot = l_part + __shfl_xor(l_part, 32);
+    constexpr int SLABS = GROUPS == 2 ? 2 : 4;  // slabs of 32 output dimensions this wavefront finishes
+    f32x16 R[SLABS];
+    if constexpr (GROUPS == 2) {
+        // The two key groups of a row: each gives the other two of its four slabs, its reference and
+        // its sum through LDS, and finishes the two it keeps.  A group without keys has reference
+        // -inf and weight 0; the other one then has keys.
+        float *const give = reinterpret_cast<float *>(lds + wave * 8192) + lane * 4;
+        const float *const take = reinterpret_cast<const float *>(lds + (wave ^ 1) * 8192) + lane * 4;
+        f32x2 *const stats = reinterpret_cast<f32x2 *>(lds + BF_WAVES * 8192) + lane;
+#pragma unroll
+        for (int sl = 0; sl < 2; ++sl)
+#pragma unroll
+            for (int r = 0; r < 16; r += 4) {
+                f32x4 w;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    w[e] = group ? O[sl][r + e] : O[2 + sl][r + e];
+                    R[sl][r + e] = group ? O[2 + sl][r + e] : O[sl][r + e];
+                }
+                *reinterpret_cast<f32x4 *>(give + (sl * 4 + r / 4) * 256) = w;
+            }
+        stats[wave * 64] = f32x2{m_used, l_tot};
+        wait_lds_and_sync();
+        const f32x2 first = stats[(wave & ~1) * 64], second = stats[(wave | 1) * 64];
+        const float m_all = fmaxf(first[0], second[0]);
+        const float w0 = __builtin_amdgcn_exp2f(first[0] - m_all), w1 = __builtin_amdgcn_exp2f(second[0] - m_all);
+        m_used = m_all;
+        l_tot = w0 * first[1] + w1 * second[1];
+        const float w_own = group ? w1 : w0, w_other = group ? w0 : w1;
+#pragma unroll
+        for (int sl = 0; sl < 2; ++sl)
+#pragma unroll
+            for (int r = 0; r < 16; r += 4) {
+                const f32x4 o = *reinterpret_cast<const f32x4 *>(take + (sl * 4 + r / 4) * 256);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) R[sl][r + e] = w_own * R[sl][r + e] + w_other * o[e];
+            }
+    } else {
+#pragma unroll
+        for (int sl = 0; sl < SLABS; ++sl) R[sl] = O[sl];
+    }
     const float inv = 1.0f / l_tot;
-    if (a.lse != nullptr && lh == 0 && qi < n)  // ln sum_j exp(scale s_ij) = ln 2 * (m + log2 l)
+    if (a.lse != nullptr && lh == 0 && group == 0 && qi < n)  // ln sum_j exp(scale s_ij) = ln 2 * (m + log2 l)
         a.lse[(int64_t)qi * H + head] = (m_used + __builtin_amdgcn_logf(l_tot)) * 0.6931471805599453f;
     // A lane holds 4 consecutive d per (sl, g), its partner lane ^ 32 the 4 that follow.  The two
     // trade halves (the lower lane gives its g-odd group for the partner's g-even one), so that
     // each stores 8 consecutive d, 16 bytes: v_permlane32_swap puts lanes 0..31 of its second
     // operand into lanes 32..63 of the first and the other way round.  (Partners share the query
     // row, so both or neither are past the end; the exchange itself runs in all lanes.)
-    __bf16 *op = a.out + ((int64_t)qi_c * H + head) * BF_D;
+    __bf16 *op = a.out + ((int64_t)qi_c * H + head) * BF_D + 32 * SLABS * group;
 #pragma unroll
-    for (int sl = 0; sl < 4; ++sl)
+    for (int sl = 0; sl < SLABS; ++sl)
 #pragma unroll
         for (int gp = 0; gp < 2; ++gp) {
             f32x4 e4, o4;
 #pragma unroll
             for (int b = 0; b < 4; ++b) {
-                e4[b] = O[sl][8 * gp + b] * inv;
-                o4[b] = O[sl][8 * gp + 4 + b] * inv;
+                e4[b] = R[sl][8 * gp + b] * inv;
+                o4[b] = R[sl][8 * gp + 4 + b] * inv;
             }
             typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
             const u32x2 even = __builtin_bit_cast(u32x2, __builtin_convertvector(e4, bf16x4));

@@ -33,11 +33,12 @@ struct attn_item {
     int head, q_tile, row0, waves;
 };
 
-inline attn_shape attn_shape_for(int n, int heads)
+// row_waves: the most wavefronts' worth of rows a workgroup takes (8, or 4 with two key groups)
+inline attn_shape attn_shape_for(int n, int heads, int row_waves = 8)
 {
     attn_shape s;
-    s.q_tiles = (n + 255) / 256;
-    const int q_wavefronts = (n + 31) / 32;  // q_tiles = ceil(q_wavefronts / 8), so 1 <= q_waves <= 8
+    const int q_wavefronts = (n + 31) / 32;
+    s.q_tiles = (q_wavefronts + row_waves - 1) / row_waves;  // so 1 <= q_waves <= row_waves
     s.q_waves = q_wavefronts / s.q_tiles;
     s.q_more = q_wavefronts % s.q_tiles;
     s.whole_heads = heads / 8;
@@ -48,6 +49,22 @@ inline attn_shape attn_shape_for(int n, int heads)
                                      : (s.left_heads * s.q_tiles + 7) / 8;
     s.grid = 8u * (unsigned)(s.whole_heads * s.q_tiles + s.left_chunk);
     return s;
+}
+
+// Into how many groups of wavefronts a call's keys are dealt.  One (a wavefront takes every key) is
+// the least copying per flop and the choice wherever 256-row workgroups fill the chip.  Two (128
+// rows per workgroup, half the keys per wavefront: half the serial chain at 1.15 times the work)
+//  - when its workgroups still run in one round on 256 CUs: 1.2 .. 1.8 times as fast (1560 rows x 12
+//    heads x 10920 keys 176 -> 111 us; 4680 x 6 x 14040 226 -> 178); one more workgroup is a second
+//    round (4680 x 7: 231 -> 316);
+//  - when 256-row workgroups need a short second round, which costs as long as a full one: up to about
+//    700 (4680 x 14 x 14040: 571 -> 508 us, 10800 x 6 x 32400: 1300 -> 862; level at 740, and at
+//    888 0.92 times as fast).
+// The rule looks at the rows only, never at the keys: a block's calls all take the same path.
+inline int attn_groups_for(int n, int heads)
+{
+    const unsigned whole = attn_shape_for(n, heads).grid, halved = attn_shape_for(n, heads, 4).grid;
+    return halved <= 256 || (whole > 256 && halved <= 680) ? 2 : 1;
 }
 
 __host__ __device__ inline attn_item attn_item_of(const attn_shape &s, unsigned workgroup)
