@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "ifx_attn_bf16.hpp"
+#include "ifx_attn_few.hpp"
 #include "ifx_merge.hpp"
 #include "ifx_attn_f32.hpp"
 #include "ifx_commit.hpp"
@@ -141,6 +142,8 @@ void (*bf16_kernel(bool table, bool fp8, int groups))(const ifx::attn_bf16_args)
     return table ? fp8 ? ifx::attn_bf16_kernel<true, true> : ifx::attn_bf16_kernel<true, false>
                  : fp8 ? ifx::attn_bf16_kernel<false, true> : ifx::attn_bf16_kernel<false, false>;
 }
+
+void (*few_kernel(bool fp8))(const ifx::attn_few_args) { return fp8 ? ifx::attn_few_kernel<true> : ifx::attn_few_kernel<false>; }
 
 // One timing sample (a pair of HIP events around what a call enqueues), taken only while
 // profiling is on and the stream is not being captured (an event recorded into a graph has no
@@ -486,11 +489,18 @@ int ifx_kv_cache_configure(ifx_kv_cache *c, int64_t block_tokens, int dtype, flo
     if (e == hipSuccess && dtype == IFX_F32)
         e = hipFuncSetAttribute(reinterpret_cast<const void *>(f32_kernel(D)), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)ifx::attn_f32_lds_bytes(f32_padded_dim(D), 8));
-    for (const bool table : {false, true})
-        for (const int groups : {1, 2})
-            if (e == hipSuccess && dtype != IFX_F32)
-                e = hipFuncSetAttribute(reinterpret_cast<const void *>(bf16_kernel(table, dtype == IFX_FP8_E4M3, groups)),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, ifx::BF_LDS_BYTES);
+    if (e == hipSuccess && dtype != IFX_F32) {  // the instances this cache's calls will run
+        const int groups = ifx::attn_groups_for((int)block_tokens, c->heads);
+        const bool fp8 = dtype == IFX_FP8_E4M3;
+        if (groups == 8) {
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(few_kernel(fp8)), hipFuncAttributeMaxDynamicSharedMemorySize, ifx::FEW_LDS_BYTES);
+        } else {
+            for (const bool table : {false, true})
+                if (e == hipSuccess)
+                    e = hipFuncSetAttribute(reinterpret_cast<const void *>(bf16_kernel(table, fp8, groups)),
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, ifx::BF_LDS_BYTES);
+        }
+    }
     bool host_ok = e == hipSuccess;
     if (host_ok) {
         try {
@@ -778,7 +788,27 @@ static int attention_impl(ifx_kv_cache *c, int layer, const void *q, const void 
     int rc = sample.begin();
     if (rc) return rc;
     const int groups = c->mfma() ? ifx::attn_groups_for(n, H) : 0;
-    if (c->mfma()) {
+    if (groups == 8) {
+        ifx::attn_few_args a;
+        a.q = static_cast<const __bf16 *>(q);
+        a.kc = c->k_of(layer);
+        a.vt = c->v_of(layer);
+        a.kb = static_cast<const __bf16 *>(k_blk);
+        a.vb = static_cast<const __bf16 *>(v_blk);
+        a.out = static_cast<__bf16 *>(out);
+        a.lse = lse;
+        a.n = n;
+        a.H = H;
+        a.C = (int)cached;
+        a.nb = with_block ? n : 0;
+        a.k_tokens = c->k_tokens;
+        a.v_tokens = c->v_tokens;
+        a.scale_log2 = c->scale * 1.4426950408889634f;
+        a.tiles = (n + ifx::FEW_ROWS - 1) / ifx::FEW_ROWS;
+        a.per_xcd = (a.tiles * H + 7) / 8;
+        a.blocks = table;
+        hipLaunchKernelGGL(few_kernel(c->dtype == IFX_FP8_E4M3), dim3((unsigned)(8 * a.per_xcd)), dim3(64 * ifx::FEW_WAVES), ifx::FEW_LDS_BYTES, s, a);
+    } else if (c->mfma()) {
         ifx::attn_bf16_args a;
         a.q = static_cast<const __bf16 *>(q);
         a.kc = c->k_of(layer);

@@ -1,0 +1,339 @@
+// bf16 block attention for gfx950 where the query rows are too few to occupy the chip: 32 rows per
+// workgroup, the keys dealt to its 8 wavefronts.
+//
+// The same operation and arithmetic as the unbounded path of ifx_attn_bf16.hpp (running reference,
+// output divided by the sum of the weights as rounded to bf16; the log-sum-exp from a second sum, of
+// the fp32 exponentials); operand layouts as described there.
+//
+// Shape of the computation
+//   A call of H heads x ceil(n / 32) row tiles that do not fill 256 CUs with 256-row workgroups is
+//   bound by the serial chain over its keys.  Here every row tile is a workgroup of its own and
+//   wavefront w takes the 32-key subtiles w, w + 8, ... of the key set (cached keys, then the current
+//   block): the chain is an eighth as long.  The partial results (output, reference, sum) are put
+//   together through LDS at the end, in a fixed order.  The price is that a subtile's keys are
+//   read into LDS once per 32 rows instead of once per 256: 64 bytes per cycle and CU, twice
+//   the time of the MFMAs it feeds, so larger calls keep the other kernel (attn_groups_for).
+//   Nothing but the end is shared between wavefronts, so the loop has no barrier.  Each has its own
+//   16 KiB of LDS, 8 for K and 8 for V: a subtile is copied in by direct global->LDS loads, its
+//   operands are read into registers, and the copy of the wavefront's next subtile starts at
+//   once into the same place, under the whole of the current step.
+//   fp8 cache: the codes are copied as they are and widened (exactly) as they are read.
+#pragma once
+#include "ifx_attn_bf16.hpp"
+
+namespace ifx {
+
+constexpr int FEW_WAVES = 8;
+constexpr int FEW_ROWS = 32;
+constexpr int FEW_WAVE_LDS = 16384;       // K subtile, V subtile
+constexpr int FEW_LD = BF_D + 4;          // floats between the rows of a partial result: 16-byte accesses of 16 rows hit 16 bank groups
+constexpr int FEW_PARTIAL_LDS = FEW_WAVES * FEW_ROWS * FEW_LD * 4;
+constexpr int FEW_LDS_BYTES = FEW_PARTIAL_LDS + FEW_WAVES * FEW_ROWS * 16;  // partial results take the tiles' place, then references and sums
+static_assert(FEW_LDS_BYTES >= FEW_WAVES * FEW_WAVE_LDS && FEW_LDS_BYTES <= 160 * 1024, "");
+
+struct attn_few_args {
+    const __bf16 *q;                  // [n, H, 128]
+    const unsigned char *kc, *vt;     // the layer's K region and V region (see attn_bf16_args)
+    const __bf16 *kb, *vb;            // the current block [n, H, 128], or nullptr when nb == 0
+    __bf16 *out;                      // [n, H, 128]
+    float *lse;                       // [n, H] or nullptr
+    int n, H;
+    int C, nb;                        // cached keys (whole blocks of n), keys of the current block (n or 0); C + nb > 0
+    int64_t k_tokens, v_tokens;
+    float scale_log2;
+    int tiles, per_xcd;               // row tiles per head; workgroups per XCD
+    ifx_key_blocks blocks;
+};
+
+template <bool FP8>
+__global__ __launch_bounds__(64 * FEW_WAVES, 1) void attn_few_kernel(const attn_few_args a)
+{
+    constexpr int KEYB = FP8 ? BF_D : BF_D * 2;  // bytes of a cached key row, and of a key's share of its V granule
+    constexpr int COPIES = FP8 ? 4 : 8;          // copy instructions of a cached K or V subtile (a subtile of the block: always 8)
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+
+    // workgroups are dealt round-robin to the XCDs: each takes a contiguous run of (head, row tile)
+    const int item = (int)(blockIdx.x & 7u) * a.per_xcd + (int)(blockIdx.x >> 3);
+    if (item >= a.H * a.tiles) return;
+    const int head = item / a.tiles, row0 = (item - head * a.tiles) * FEW_ROWS;
+    const int n = a.n, H = a.H;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lq = lane & 31, lh = lane >> 5;
+    const float c2 = a.scale_log2;
+    unsigned char *const ktile = lds + wave * FEW_WAVE_LDS, *const vtile = ktile + FEW_WAVE_LDS / 2;
+
+    // A subtile is up to 32 keys of one run of rows: of the cached tokens [0, C), of one block of a
+    // selection, or of the current block.  Blocks are multiples of 8 tokens, so a run starts and ends
+    // on a V granule.  It is read through a buffer descriptor that ends with its last row: rows behind
+    // that read as zero, touch no memory and are masked.
+    const bool listed = a.blocks.magic != 0;
+    const int seg_keys = listed ? n : a.C;
+    const int seg_subs = (seg_keys + 31) >> 5;
+    const int cached_subs = listed ? a.blocks.count * seg_subs : seg_subs;
+    const int subs = cached_subs + ((a.nb + 31) >> 5);
+    int tab = 0;  // the first 64 entries of a selection, one per lane: a lookup is a lane read
+    auto first_of = [&](int e) IFX_INLINE -> int {
+        if (a.blocks.list != nullptr) return a.blocks.list[e];
+        return a.blocks.first[e];
+    };
+    if (listed && lane < a.blocks.count) tab = first_of(lane);
+    struct run {
+        int first, keys;  // first token (of the head's region, or of the block), keys from there to the run's end
+        bool cached;
+    };
+    auto run_of = [&](int sub) IFX_INLINE -> run {
+        if (sub < cached_subs) {
+            int e = 0, first = 0;
+            if (listed) {
+                e = sub / seg_subs;
+                first = e < 64 ? __builtin_amdgcn_readlane(tab, e) : __builtin_amdgcn_readfirstlane(first_of(e));
+            }
+            const int j = 32 * (sub - e * seg_subs);
+            return {first + j, seg_keys - j, true};
+        }
+        const int j = 32 * (sub - cached_subs);
+        return {j, a.nb - j, false};
+    };
+    auto rsrc_at = [&](uintptr_t u, int bytes) IFX_INLINE -> __amdgpu_buffer_rsrc_t {
+        const uintptr_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
+        return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(hi << 32 | lo), 0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+    };
+    const uintptr_t kc = (uintptr_t)a.kc + (uintptr_t)head * (uintptr_t)a.k_tokens * KEYB;
+    const uintptr_t vc = (uintptr_t)a.vt + (uintptr_t)head * (uintptr_t)a.v_tokens * KEYB;
+    const uintptr_t kb = (uintptr_t)a.kb + (uintptr_t)head * (BF_D * 2), vb = (uintptr_t)a.vb + (uintptr_t)head * (BF_D * 2);
+    const int pitch = H * (BF_D * 2);
+    const int l16 = lane & 15, g = lane >> 4;
+    // K: row r (256 bytes), 16-byte chunk c at place c ^ (r % 16); codes: 128-byte rows, place c ^ (r % 8)
+    auto copy_k = [&](int sub) IFX_INLINE {
+        const run r = run_of(sub);
+        const int rows = r.keys < 32 ? r.keys : 32;
+        if (FP8 && r.cached) {
+            const __amdgpu_buffer_rsrc_t rs = rsrc_at(kc + (uintptr_t)r.first * KEYB, rows * KEYB);
+            const int at = (lane >> 3) * KEYB + (((lane & 7) ^ (lane >> 3)) << 4);
+#pragma unroll
+            for (int x = 0; x < COPIES; ++x) __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lptr_t)(ktile + 1024 * x), 16, at, 1024 * x, 0, 0);
+            return;
+        }
+        const int stride = r.cached ? BF_D * 2 : pitch;
+        const __amdgpu_buffer_rsrc_t rs = rsrc_at((r.cached ? kc : kb) + (uintptr_t)r.first * (uintptr_t)stride, (rows - 1) * stride + BF_D * 2);
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+            const int at = g * stride + ((l16 ^ (4 * (x & 3) + g)) << 4);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lptr_t)(ktile + 1024 * x), 16, at, 4 * x * stride, 0, 0);
+        }
+    };
+    // V: cached granules as they lie; rows of the current block with chunk c of row r at place c ^ 4 (r % 4)
+    auto copy_v = [&](int sub) IFX_INLINE {
+        const run r = run_of(sub);
+        const int rows = r.keys < 32 ? r.keys : 32;
+        if (r.cached) {
+            const __amdgpu_buffer_rsrc_t rs = rsrc_at(vc + (uintptr_t)r.first * KEYB, rows * KEYB);
+#pragma unroll
+            for (int x = 0; x < COPIES; ++x) __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lptr_t)(vtile + 1024 * x), 16, lane * 16, 1024 * x, 0, 0);
+            return;
+        }
+        const __amdgpu_buffer_rsrc_t rs = rsrc_at(vb + (uintptr_t)r.first * (uintptr_t)pitch, (rows - 1) * pitch + BF_D * 2);
+        const int at = g * pitch + ((l16 ^ (g << 2)) << 4);
+#pragma unroll
+        for (int x = 0; x < 8; ++x) __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lptr_t)(vtile + 1024 * x), 16, at, 4 * x * pitch, 0, 0);
+    };
+
+    if (wave < subs) {
+        copy_k(wave);
+        copy_v(wave);
+    }
+    bf16x8 Q[8];
+    {
+        const int qi = row0 + lq;
+        const bf16x8 *qp = reinterpret_cast<const bf16x8 *>(a.q + ((int64_t)(qi < n ? qi : n - 1) * H + head) * BF_D);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) Q[s] = qp[2 * s + lh];
+    }
+
+    // operand addresses (see ifx_attn_bf16.hpp)
+    const int pkey = (lq & 16) | ((lq & 4) << 1) | ((lq & 8) >> 1) | (lq & 3);
+    const int kz = lh ^ (pkey & 15);
+    int vtoff[4];
+    {
+        const int base = (8 * (g >> 1) + (l16 >> 2)) * 256 + (2 * (g & 1) + ((l16 & 3) >> 1)) * 16 + 8 * (l16 & 1);
+#pragma unroll
+        for (int sl = 0; sl < 4; ++sl) vtoff[sl] = base + ((sl ^ (l16 >> 2)) << 6);
+    }
+    typedef uint32_t raw_u32x2 __attribute__((ext_vector_type(2)));
+    auto widen8 = [&](const raw_u32x2 &c) IFX_INLINE -> bf16x8 {
+        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+        u32x4 r;
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+            r[2 * w] = __builtin_bit_cast(uint32_t, (bf16x2)__builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)c[w], 1.0f, false));
+            r[2 * w + 1] = __builtin_bit_cast(uint32_t, (bf16x2)__builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)c[w], 1.0f, true));
+        }
+        return __builtin_bit_cast(bf16x8, r);
+    };
+
+    f32x16 O[4];
+#pragma unroll
+    for (int sl = 0; sl < 4; ++sl)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) O[sl][r] = 0.0f;
+    float m_used = -INFINITY;  // reference of the exponentials (scaled log2 units); -inf: no key yet
+    // this lane's share of the row sum: of the weights as rounded to bf16, which is what the PV product
+    // uses (the output's denominator), and, where the log-sum-exp is asked for, of the fp32 exponentials
+    float l_acc[4] = {0.f, 0.f, 0.f, 0.f}, e_acc[4] = {0.f, 0.f, 0.f, 0.f};
+    const bool with_lse = a.lse != nullptr;
+
+    for (int sub = wave; sub < subs; sub += FEW_WAVES) {
+        const int next = sub + FEW_WAVES < subs ? sub + FEW_WAVES : sub;  // (always copied: the wait counts then know what is in flight)
+        const bool cached = sub < cached_subs;
+        const int keys = run_of(sub).keys;
+        bf16x8 A[8];
+        // K: only V's copies, issued behind it, may still be on their way
+        __builtin_amdgcn_s_waitcnt(0x0F70 | COPIES);
+        if (FP8 && cached) {
+            raw_u32x2 c[8];
+#pragma unroll
+            for (int s = 0; s < 8; ++s) c[s] = *reinterpret_cast<const raw_u32x2 *>(ktile + pkey * 128 + ((s ^ (pkey & 7)) << 4) + lh * 8);
+#pragma unroll
+            for (int s = 0; s < 8; ++s) A[s] = widen8(c[s]);
+        } else {
+#pragma unroll
+            for (int s = 0; s < 8; ++s) A[s] = *reinterpret_cast<const bf16x8 *>(ktile + pkey * 256 + (((2 * s) ^ kz) << 4));
+        }
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the operands are in registers, the tile is free
+        __builtin_amdgcn_sched_barrier(0);
+        copy_k(next);
+        __builtin_amdgcn_s_setprio(1);  // (the MFMAs, and the operand reads that free V's tile, first: 5 % faster)
+        f32x16 S = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < 8; ++s) S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[s], Q[s], S, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        // V, under the score MFMAs: only the K copies just issued may still be on their way
+        __builtin_amdgcn_s_waitcnt(0x0F70 | COPIES);
+        bf16x8 V[8];
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int sl = 0; sl < 4; ++sl) {
+                if (cached) {
+                    if constexpr (FP8)
+                        V[t * 4 + sl] = widen8(*reinterpret_cast<const raw_u32x2 *>(vtile + lh * 1024 + lq * 8 + t * 2048 + sl * 256));
+                    else
+                        V[t * 4 + sl] = *reinterpret_cast<const bf16x8 *>(vtile + lh * 2048 + lq * 16 + t * 4096 + sl * 512);
+                } else {
+                    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lptr_t)(vtile + vtoff[sl] + (16 * t) * 256));
+                    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lptr_t)(vtile + vtoff[sl] + (16 * t + 4) * 256));
+                    typedef short s16x8 __attribute__((ext_vector_type(8)));
+                    V[t * 4 + sl] = __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                }
+            }
+        __builtin_amdgcn_s_waitcnt(0xC07F);
+        __builtin_amdgcn_sched_barrier(0);
+        copy_v(next);
+        __builtin_amdgcn_s_setprio(0);
+
+        // register r of S is key 16 (r / 8) + 8 lh + r % 8 of the subtile
+        if (keys < 32) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (16 * (r >> 3) + 8 * lh + (r & 7) >= keys) S[r] = -INFINITY;
+        }
+        auto raise = [&]() IFX_INLINE {
+            float t = S[0];
+#pragma unroll
+            for (int r = 1; r < 16; ++r) t = fmaxf(t, S[r]);
+            t = max_across_halves(t) * c2;
+            const float m_next = t > m_used ? t + BF_HEADROOM : m_used;  // (a large reference would cost the log-sum-exp bits)
+            const float alpha = __builtin_amdgcn_exp2f(m_used - m_next);  // 1 where unchanged, 0 at the start
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                l_acc[e] *= alpha;
+                e_acc[e] *= alpha;
+            }
+#pragma unroll
+            for (int sl = 0; sl < 4; ++sl)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) O[sl][r] *= alpha;
+            m_used = m_next;
+        };
+        if (sub == wave) raise();  // the first subtile (every subtile holds a key, so its largest score is one)
+        bf16x8 P[2];
+        f32x8 E[2];
+        auto exps = [&]() IFX_INLINE {
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) E[t][e] = __builtin_amdgcn_exp2f(fmaf(S[8 * t + e], c2, -m_used));
+                P[t] = __builtin_convertvector(E[t], bf16x8);
+            }
+        };
+        exps();
+        {
+            // a score a whole unit above the reference: an exponential of 2 or more, i.e. a top exponent bit
+            const u32x4 x = __builtin_bit_cast(u32x4, P[0]), y = __builtin_bit_cast(u32x4, P[1]);
+            const uint32_t o = (x[0] | x[1] | x[2]) | (x[3] | y[0] | y[1]) | (y[2] | y[3]);
+            if (__builtin_expect(__any((o & 0x40004000u) != 0u), 0)) {
+                raise();
+                exps();
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int sl = 0; sl < 4; ++sl) O[sl] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(V[t * 4 + sl], P[t], O[sl], 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) l_acc[r & 3] += (float)P[r >> 3][r & 7];
+        if (with_lse) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) e_acc[r & 3] += E[r >> 3][r & 7];
+        }
+    }
+
+    // ---- put the wavefronts' shares together: partial outputs, references and sums through LDS
+    const float l_half = (l_acc[0] + l_acc[1]) + (l_acc[2] + l_acc[3]);
+    const float l_own = l_half + __shfl_xor(l_half, 32);
+    const float e_half = (e_acc[0] + e_acc[1]) + (e_acc[2] + e_acc[3]);
+    const float e_own = e_half + __shfl_xor(e_half, 32);
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the copies behind the last subtile have landed
+    __syncthreads();
+    float *const partial = reinterpret_cast<float *>(lds);
+    f32x4 *const stats = reinterpret_cast<f32x4 *>(lds + FEW_PARTIAL_LDS);
+    {
+        // register r of O[sl] is d = 32 sl + 8 (r / 4) + 4 lh + r % 4 of query lq
+        float *dst = partial + (wave * FEW_ROWS + lq) * FEW_LD + 4 * lh;
+#pragma unroll
+        for (int sl = 0; sl < 4; ++sl)
+#pragma unroll
+            for (int r = 0; r < 16; r += 4)
+                *reinterpret_cast<f32x4 *>(dst + 32 * sl + 2 * r) = f32x4{O[sl][r], O[sl][r + 1], O[sl][r + 2], O[sl][r + 3]};
+        if (lh == 0) stats[wave * FEW_ROWS + lq] = f32x4{m_used, l_own, e_own, 0.f};
+    }
+    __syncthreads();
+    const int rr = tid >> 4, c = tid & 15;  // row of the tile, 8 output dimensions
+    const int i = row0 + rr;
+    if (i >= n) return;
+    float M = -INFINITY;  // finite in the end: wavefront 0 had a key
+#pragma unroll
+    for (int s = 0; s < FEW_WAVES; ++s) M = fmaxf(M, stats[s * FEW_ROWS + rr][0]);
+    float sum = 0.f, sum_e = 0.f;
+    f32x8 o = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < FEW_WAVES; ++s) {
+        const f32x4 ml = stats[s * FEW_ROWS + rr];
+        const float w = __builtin_amdgcn_exp2f(ml[0] - M);  // 0 for a wavefront without keys
+        sum += w * ml[1];
+        sum_e += w * ml[2];
+        const f32x4 *src = reinterpret_cast<const f32x4 *>(partial + (s * FEW_ROWS + rr) * FEW_LD + 8 * c);
+        const f32x4 lo = src[0], hi = src[1];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            o[e] += w * lo[e];
+            o[4 + e] += w * hi[e];
+        }
+    }
+    if (with_lse && c == 0) a.lse[(int64_t)i * H + head] = (M + __builtin_amdgcn_logf(sum_e)) * 0.6931471805599453f;
+    o *= 1.0f / sum;
+    *reinterpret_cast<bf16x8 *>(a.out + ((int64_t)i * H + head) * BF_D + 8 * c) = __builtin_convertvector(o, bf16x8);
+}
+
+}  // namespace ifx

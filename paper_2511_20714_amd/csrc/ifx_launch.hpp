@@ -60,9 +60,13 @@ inline attn_shape attn_shape_for(int n, int heads, int row_waves = 8)
 //  - when 256-row workgroups need a short second round, which costs as long as a full one: up to about
 //    700 (4680 x 14 x 14040: 571 -> 508 us, 10800 x 6 x 32400: 1300 -> 862; level at 740, and at
 //    888 0.92 times as fast).
+// Eight (ifx_attn_few.hpp: 32 rows per workgroup) when even that is one round: 2 .. 3 times as fast
+// as one group, 1.5 as two (1560 x 5 x 10920: 176, 102, 65 us; 264 x 2 x 792: 21.2, 16.5, 10.3); at two
+// rounds (1560 x 6) it falls behind two groups.
 // The rule looks at the rows only, never at the keys: a block's calls all take the same path.
 inline int attn_groups_for(int n, int heads)
 {
+    if ((int64_t)((n + 31) / 32) * heads <= 256) return 8;
     const unsigned whole = attn_shape_for(n, heads).grid, halved = attn_shape_for(n, heads, 4).grid;
     return halved <= 256 || (whole > 256 && halved <= 680) ? 2 : 1;
 }
