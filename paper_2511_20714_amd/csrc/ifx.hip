@@ -216,14 +216,27 @@ int timing_sample::begin()
     return IFX_OK;
 }
 
-// fp32: enqueue the copy of one block's V into the layer's private layout at token offset tok0.
-int launch_store_v(const ifx_kv_cache *c, int layer, const void *v_blk, int64_t tok0, hipStream_t s)
+// fp32 caches: workgroups per head of a copy launch: enough to fill the chip (several layers' worth
+// help), each with a few rounds of 256 / cpr rows.
+int f32_copy_parts(const ifx_kv_cache *c, int64_t rows_of_launch)
 {
-    const int64_t n = c->n;
-    const int H = c->heads;
-    const int cpr = (int)(c->head_dim * c->elem / 16);
-    hipLaunchKernelGGL(ifx::rows_to_heads_kernel, dim3(grid_for(n * H * cpr)), dim3(256), 0, s, (const u32x4 *)v_blk,
-                       (u32x4 *)c->v_of(layer), n, H, cpr, c->v_tokens, tok0);
+    const int64_t round = 4 * (256 / (c->head_dim / 4));
+    const int64_t most = (c->n + round - 1) / round, enough = (4096 + rows_of_launch - 1) / rows_of_launch;
+    return (int)(most < enough ? most : enough);
+}
+
+// fp32, one launch for the blocks of layers [first_layer, first_layer + n_layers), n_layers <= COMMIT_MAX_LAYERS.
+int launch_store_blocks_f32(ifx_kv_cache *c, int first_layer, int n_layers, const void *const *k_blks, const void *const *v_blks, hipStream_t s)
+{
+    ifx::commit_layers args = {};
+    for (int i = 0; i < n_layers; ++i) {
+        const int layer = first_layer + i;
+        const int64_t slot = c->rings[(size_t)layer].next_slot();
+        args.l[i] = ifx::commit_layer{k_blks[i], v_blks[i], c->k_of(layer), c->v_of(layer), nullptr, slot * c->n, (int)slot};
+    }
+    const int parts = f32_copy_parts(c, (int64_t)c->heads * 2 * n_layers);
+    hipLaunchKernelGGL(ifx::store_block_f32_kernel, dim3((unsigned)(c->heads * parts), (unsigned)(2 * n_layers)), dim3(256), 0, s, args, (int)c->n,
+                       c->heads, c->head_dim / 4, c->k_tokens, parts);
     IFX_HIP(hipGetLastError());
     return IFX_OK;
 }
@@ -256,15 +269,10 @@ int launch_store_blocks_bf16(ifx_kv_cache *c, int first_layer, int n_layers, con
     return IFX_OK;
 }
 
-int launch_store_k(const ifx_kv_cache *c, int layer, const void *k_blk, int64_t tok0, hipStream_t s)
+int launch_store_blocks(ifx_kv_cache *c, int first_layer, int n_layers, const void *const *k_blks, const void *const *v_blks, hipStream_t s)
 {
-    const int64_t n = c->n;
-    const int H = c->heads;
-    const int cpr = (int)(c->head_dim * c->elem / 16);
-    hipLaunchKernelGGL(ifx::rows_to_heads_kernel, dim3(grid_for(n * H * cpr)), dim3(256), 0, s,
-                       (const u32x4 *)k_blk, (u32x4 *)c->k_of(layer), n, H, cpr, c->k_tokens, tok0);
-    IFX_HIP(hipGetLastError());
-    return IFX_OK;
+    return c->mfma() ? launch_store_blocks_bf16(c, first_layer, n_layers, k_blks, v_blks, s)
+                     : launch_store_blocks_f32(c, first_layer, n_layers, k_blks, v_blks, s);
 }
 
 }  // namespace
@@ -990,15 +998,9 @@ int ifx_kv_cache_commit(ifx_kv_cache *c, int layer, const void *k_blk, const voi
     if ((rc = check_ptr(k_blk, "k_blk")) || (rc = check_ptr(v_blk, "v_blk"))) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
     ifx_ring &ring = c->rings[(size_t)layer];
-    const int64_t tok0 = ring.next_slot() * c->n;
     timing_sample sample(c, c->commit_events, s);
     if ((rc = sample.begin())) return rc;
-    if (c->mfma()) {
-        if ((rc = launch_store_blocks_bf16(c, layer, 1, &k_blk, &v_blk, s))) return rc;
-    } else {
-        if ((rc = launch_store_k(c, layer, k_blk, tok0, s))) return rc;
-        if ((rc = launch_store_v(c, layer, v_blk, tok0, s))) return rc;
-    }
+    if ((rc = launch_store_blocks(c, layer, 1, &k_blk, &v_blk, s))) return rc;
     ring.commit();  // the copy is enqueued: the slot now holds this block
     return sample.end();
 }
@@ -1021,18 +1023,8 @@ int ifx_kv_cache_commit_layers(ifx_kv_cache *c, int first_layer, int n_layers, c
     // committed (the call reports the error; ifx_kv_cache_committed tells how far it got).
     for (int done = 0; done < n_layers;) {
         const int chunk = n_layers - done < ifx::COMMIT_MAX_LAYERS ? n_layers - done : ifx::COMMIT_MAX_LAYERS;
-        if (c->mfma()) {
-            if ((rc = launch_store_blocks_bf16(c, first_layer + done, chunk, k_blks + done, v_blks + done, s))) return rc;
-            for (int i = 0; i < chunk; ++i) c->rings[(size_t)(first_layer + done + i)].commit();
-        } else {
-            for (int i = 0; i < chunk; ++i) {
-                const int layer = first_layer + done + i;
-                const int64_t tok0 = c->rings[(size_t)layer].next_slot() * c->n;
-                if ((rc = launch_store_k(c, layer, k_blks[done + i], tok0, s))) return rc;
-                if ((rc = launch_store_v(c, layer, v_blks[done + i], tok0, s))) return rc;
-                c->rings[(size_t)layer].commit();
-            }
-        }
+        if ((rc = launch_store_blocks(c, first_layer + done, chunk, k_blks + done, v_blks + done, s))) return rc;
+        for (int i = 0; i < chunk; ++i) c->rings[(size_t)(first_layer + done + i)].commit();
         done += chunk;
     }
     return sample.end();
@@ -1046,28 +1038,32 @@ int ifx_kv_cache_read(const ifx_kv_cache *c, int layer, void *k_out, void *v_out
     if (ring.resident() == 0) return IFX_OK;
     if ((rc = check_ptr(k_out, "k_out")) || (rc = check_ptr(v_out, "v_out"))) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int H = c->heads, D = c->head_dim;
-    const int cpr = (int)(D * c->elem / 16);
-    const size_t blk_bytes = (size_t)c->n * H * D * c->io_elem();
-    // one block per launch: block b of the order asked for comes from slot slot_of_logical(b) or b
-    for (int64_t b = 0; b < ring.resident(); ++b) {
-        const int64_t slot = logical_order ? ring.slot_of_logical(b) : b;
-        unsigned char *kd = static_cast<unsigned char *>(k_out) + (size_t)b * blk_bytes, *vd = static_cast<unsigned char *>(v_out) + (size_t)b * blk_bytes;
-        if (c->dtype == IFX_FP8_E4M3) {  // the codes widened to bf16
-            hipLaunchKernelGGL(ifx::e4m3_block_to_rows_kernel, dim3(grid_for(c->n * H * 16)), dim3(256), 0, s, c->k_of(layer), c->v_of(layer),
-                               (u32x4 *)kd, (u32x4 *)vd, c->n, H, c->k_tokens, c->v_tokens, slot);
-            IFX_HIP(hipGetLastError());
-            continue;
+    const int n = (int)c->n, H = c->heads;
+    const size_t blk_bytes = (size_t)c->n * H * c->head_dim * c->io_elem();
+    // block b of the order asked for comes from slot slot_of_logical(b) or b
+    for (int64_t done = 0; done < ring.resident();) {
+        const int count = (int)(ring.resident() - done < ifx::READ_MAX_BLOCKS ? ring.resident() - done : ifx::READ_MAX_BLOCKS);
+        ifx::read_slots slots = {};
+        for (int b = 0; b < count; ++b) slots.slot[b] = (int)(logical_order ? ring.slot_of_logical(done + b) : done + b);
+        u32x4 *kd = reinterpret_cast<u32x4 *>(static_cast<unsigned char *>(k_out) + (size_t)done * blk_bytes);
+        u32x4 *vd = reinterpret_cast<u32x4 *>(static_cast<unsigned char *>(v_out) + (size_t)done * blk_bytes);
+        if (c->mfma()) {
+            const int v_blocks = grid_for((c->n / 8) * H * 2, 16, 2048);  // as in the commit
+            const dim3 grid((unsigned)(H * c->parts + v_blocks), (unsigned)count);
+            if (c->dtype == IFX_FP8_E4M3)
+                hipLaunchKernelGGL((ifx::read_blocks_bf16_kernel<4, true>), grid, dim3(256), 0, s, c->k_of(layer), c->v_of(layer), kd, vd, slots, n,
+                                   H, c->k_tokens, c->v_tokens, c->parts);
+            else
+                hipLaunchKernelGGL((ifx::read_blocks_bf16_kernel<4, false>), grid, dim3(256), 0, s, c->k_of(layer), c->v_of(layer), kd, vd, slots,
+                                   n, H, c->k_tokens, c->v_tokens, c->parts);
+        } else {
+            const int parts = f32_copy_parts(c, (int64_t)H * 2 * count);
+            hipLaunchKernelGGL(ifx::read_blocks_f32_kernel, dim3((unsigned)(H * parts), (unsigned)(2 * count)), dim3(256), 0, s,
+                               reinterpret_cast<const u32x4 *>(c->k_of(layer)), reinterpret_cast<const u32x4 *>(c->v_of(layer)), kd, vd, slots, n, H,
+                               c->head_dim / 4, c->k_tokens, parts);
         }
-        hipLaunchKernelGGL(ifx::heads_to_rows_kernel, dim3(grid_for(c->n * H * cpr)), dim3(256), 0, s, (const u32x4 *)c->k_of(layer),
-                           (u32x4 *)kd, c->n, H, cpr, c->k_tokens, slot);
-        if (c->dtype == IFX_BF16)
-            hipLaunchKernelGGL(ifx::granules_to_rows_kernel, dim3(grid_for(c->n * H * (D / 8))), dim3(256), 0, s,
-                               (const uint16_t *)c->v_of(layer), (u16x8 *)vd, c->n, H, D, c->v_tokens, slot);
-        else
-            hipLaunchKernelGGL(ifx::heads_to_rows_kernel, dim3(grid_for(c->n * H * cpr)), dim3(256), 0, s, (const u32x4 *)c->v_of(layer),
-                               (u32x4 *)vd, c->n, H, cpr, c->v_tokens, slot);
         IFX_HIP(hipGetLastError());
+        done += count;
     }
     return IFX_OK;
 }
