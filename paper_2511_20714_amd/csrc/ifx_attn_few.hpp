@@ -13,11 +13,15 @@
 //   together through LDS at the end, in a fixed order.  The price is that a subtile's keys are
 //   read into LDS once per 32 rows instead of once per 256: 64 bytes per cycle and CU, twice
 //   the time of the MFMAs it feeds, so larger calls keep the other kernel (attn_groups_for).
-//   Nothing but the end is shared between wavefronts, so the loop has no barrier.  Each has its own
-//   16 KiB of LDS, 8 for K and 8 for V: a subtile is copied in by direct global->LDS loads, its
-//   operands are read into registers, and the copy of the wavefront's next subtile starts at
-//   once into the same place, under the whole of the current step.
-//   fp8 cache: the codes are copied as they are and widened (exactly) as they are read.
+//   Nothing but the end is shared between wavefronts, so the loop has no barrier.  K goes through 8 KiB
+//   of LDS of the wavefront's own: a subtile is copied in by direct global->LDS loads, its operands
+//   are read into registers, and the copy of the wavefront's next subtile starts at once into the same
+//   place, under the whole of the current step.  Cached V lies as the PV product needs it and goes
+//   straight into registers, asked for as soon as the registers' last product has been issued (through
+//   LDS like K: 2 % slower, 18 % with an fp8 cache); only the current block's V needs LDS, for the
+//   transposing reads.  fp8 codes are widened (exactly) as they are read.
+//   Measured (5 heads x 1560 rows, 10920 keys): 64 us, 1.1 us per step and wavefront, where the loads
+//   alone would take 0.85; fp8 cache 61 us.  264 rows, 2 heads, 792 keys: 10.1 us.
 #pragma once
 #include "ifx_attn_bf16.hpp"
 
@@ -25,7 +29,7 @@ namespace ifx {
 
 constexpr int FEW_WAVES = 8;
 constexpr int FEW_ROWS = 32;
-constexpr int FEW_WAVE_LDS = 16384;       // K subtile, V subtile
+constexpr int FEW_WAVE_LDS = 16384;       // K subtile, V subtile of the current block
 constexpr int FEW_LD = BF_D + 4;          // floats between the rows of a partial result: 16-byte accesses of 16 rows hit 16 bank groups
 constexpr int FEW_PARTIAL_LDS = FEW_WAVES * FEW_ROWS * FEW_LD * 4;
 constexpr int FEW_LDS_BYTES = FEW_PARTIAL_LDS + FEW_WAVES * FEW_ROWS * 16;  // partial results take the tiles' place, then references and sums
@@ -49,7 +53,7 @@ template <bool FP8>
 __global__ __launch_bounds__(64 * FEW_WAVES, 1) void attn_few_kernel(const attn_few_args a)
 {
     constexpr int KEYB = FP8 ? BF_D : BF_D * 2;  // bytes of a cached key row, and of a key's share of its V granule
-    constexpr int COPIES = FP8 ? 4 : 8;          // copy instructions of a cached K or V subtile (a subtile of the block: always 8)
+    constexpr int COPIES = FP8 ? 4 : 8;          // copy instructions of a cached K subtile (V, and subtiles of the block: always 8)
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
 
     // workgroups are dealt round-robin to the XCDs: each takes a contiguous run of (head, row tile)
@@ -123,14 +127,28 @@ __global__ __launch_bounds__(64 * FEW_WAVES, 1) void attn_few_kernel(const attn_
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lptr_t)(ktile + 1024 * x), 16, at, 4 * x * stride, 0, 0);
         }
     };
-    // V: cached granules as they lie; rows of the current block with chunk c of row r at place c ^ 4 (r % 4)
-    auto copy_v = [&](int sub) IFX_INLINE {
+    // V: cached granules straight into registers (a lane's 8 keys of a dimension are 16 contiguous bytes,
+    // 8 as codes); rows of the current block into LDS, chunk c of row r at place c ^ 4 (r % 4).  Eight
+    // instructions either way.
+    typedef uint32_t raw_u32x4 __attribute__((__vector_size__(16)));
+    typedef uint32_t raw_u32x2 __attribute__((__vector_size__(8)));
+    typedef typename std::conditional<FP8, raw_u32x2, raw_u32x4>::type stored_v;
+    stored_v Vc[8];
+    auto load_v = [&](int sub) IFX_INLINE {
         const run r = run_of(sub);
         const int rows = r.keys < 32 ? r.keys : 32;
         if (r.cached) {
             const __amdgpu_buffer_rsrc_t rs = rsrc_at(vc + (uintptr_t)r.first * KEYB, rows * KEYB);
+            const int at = lh * (8 * KEYB) + lq * (KEYB / 16);
 #pragma unroll
-            for (int x = 0; x < COPIES; ++x) __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lptr_t)(vtile + 1024 * x), 16, lane * 16, 1024 * x, 0, 0);
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int sl = 0; sl < 4; ++sl) {
+                    if constexpr (FP8)
+                        Vc[t * 4 + sl] = __builtin_amdgcn_raw_buffer_load_b64(rs, at, t * (16 * KEYB) + sl * (2 * KEYB), 0);
+                    else
+                        Vc[t * 4 + sl] = __builtin_amdgcn_raw_buffer_load_b128(rs, at, t * (16 * KEYB) + sl * (2 * KEYB), 0);
+                }
             return;
         }
         const __amdgpu_buffer_rsrc_t rs = rsrc_at(vb + (uintptr_t)r.first * (uintptr_t)pitch, (rows - 1) * pitch + BF_D * 2);
@@ -141,7 +159,7 @@ __global__ __launch_bounds__(64 * FEW_WAVES, 1) void attn_few_kernel(const attn_
 
     if (wave < subs) {
         copy_k(wave);
-        copy_v(wave);
+        load_v(wave);
     }
     bf16x8 Q[8];
     {
@@ -160,7 +178,6 @@ __global__ __launch_bounds__(64 * FEW_WAVES, 1) void attn_few_kernel(const attn_
 #pragma unroll
         for (int sl = 0; sl < 4; ++sl) vtoff[sl] = base + ((sl ^ (l16 >> 2)) << 6);
     }
-    typedef uint32_t raw_u32x2 __attribute__((ext_vector_type(2)));
     auto widen8 = [&](const raw_u32x2 &c) IFX_INLINE -> bf16x8 {
         typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
         u32x4 r;
@@ -188,8 +205,8 @@ __global__ __launch_bounds__(64 * FEW_WAVES, 1) void attn_few_kernel(const attn_
         const bool cached = sub < cached_subs;
         const int keys = run_of(sub).keys;
         bf16x8 A[8];
-        // K: only V's copies, issued behind it, may still be on their way
-        __builtin_amdgcn_s_waitcnt(0x0F70 | COPIES);
+        // K: only V's eight loads, issued behind it, may still be on their way
+        __builtin_amdgcn_s_waitcnt(0x0F70 | 8);
         if (FP8 && cached) {
             raw_u32x2 c[8];
 #pragma unroll
@@ -203,33 +220,10 @@ __global__ __launch_bounds__(64 * FEW_WAVES, 1) void attn_few_kernel(const attn_
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the operands are in registers, the tile is free
         __builtin_amdgcn_sched_barrier(0);
         copy_k(next);
-        __builtin_amdgcn_s_setprio(1);  // (the MFMAs, and the operand reads that free V's tile, first: 5 % faster)
+        __builtin_amdgcn_s_setprio(1);  // (MFMAs first: 5 % faster)
         f32x16 S = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int s = 0; s < 8; ++s) S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[s], Q[s], S, 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        // V, under the score MFMAs: only the K copies just issued may still be on their way
-        __builtin_amdgcn_s_waitcnt(0x0F70 | COPIES);
-        bf16x8 V[8];
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int sl = 0; sl < 4; ++sl) {
-                if (cached) {
-                    if constexpr (FP8)
-                        V[t * 4 + sl] = widen8(*reinterpret_cast<const raw_u32x2 *>(vtile + lh * 1024 + lq * 8 + t * 2048 + sl * 256));
-                    else
-                        V[t * 4 + sl] = *reinterpret_cast<const bf16x8 *>(vtile + lh * 2048 + lq * 16 + t * 4096 + sl * 512);
-                } else {
-                    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lptr_t)(vtile + vtoff[sl] + (16 * t) * 256));
-                    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lptr_t)(vtile + vtoff[sl] + (16 * t + 4) * 256));
-                    typedef short s16x8 __attribute__((ext_vector_type(8)));
-                    V[t * 4 + sl] = __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-                }
-            }
-        __builtin_amdgcn_s_waitcnt(0xC07F);
-        __builtin_amdgcn_sched_barrier(0);
-        copy_v(next);
         __builtin_amdgcn_s_setprio(0);
 
         // register r of S is key 16 (r / 8) + 8 lh + r % 8 of the subtile
@@ -277,10 +271,34 @@ __global__ __launch_bounds__(64 * FEW_WAVES, 1) void attn_few_kernel(const attn_
                 exps();
             }
         }
+        bf16x8 V[8];
+        if (cached) {
+#pragma unroll
+            for (int o = 0; o < 8; ++o) {
+                if constexpr (FP8)
+                    V[o] = widen8(Vc[o]);
+                else
+                    V[o] = __builtin_bit_cast(bf16x8, Vc[o]);
+            }
+        } else {
+            __builtin_amdgcn_s_waitcnt(0x0F70 | COPIES);  // only the K copies issued in this step may still be on their way
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int sl = 0; sl < 4; ++sl) {
+                    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lptr_t)(vtile + vtoff[sl] + (16 * t) * 256));
+                    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lptr_t)(vtile + vtoff[sl] + (16 * t + 4) * 256));
+                    typedef short s16x8 __attribute__((ext_vector_type(8)));
+                    V[t * 4 + sl] = __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                }
+            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the tile is free
+        }
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
             for (int sl = 0; sl < 4; ++sl) O[sl] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(V[t * 4 + sl], P[t], O[sl], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        load_v(next);
 #pragma unroll
         for (int r = 0; r < 16; ++r) l_acc[r & 3] += (float)P[r >> 3][r & 7];
         if (with_lse) {
