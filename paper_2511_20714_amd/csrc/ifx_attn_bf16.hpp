@@ -590,57 +590,6 @@ __global__ __launch_bounds__(BF_THREADS, 1) void attn_bf16_kernel(const attn_bf1
     bf16x8 Kop[8];  // K operands of the subtile whose scores are computed next
     bf16x8 Vop[8];  // V operands of the current subtile
 
-    // One pipelined step of 16 MFMAs, one LDS operand per MFMA, each read about eight MFMAs
-    // ahead of its use.  Scores of the NEXT subtile (operands already in Kop) with the V operands of
-    // the CURRENT subtile fetched meanwhile and its exponentials spread under them; then the PV
-    // product of the current subtile with the K operands of the subtile AFTER the next fetched
-    // meanwhile and the current subtile's row-sum adds.
-    //   koffs_after: LDS offset of the subtile after the next; voffs_cur: offset of the current
-    //   subtile's V data.  Only for subtiles that lie wholly inside the phase (no key masking).
-    //   load_tag: which half of the tile three ahead this step brings in (0: K, 1: V), two
-    //   global->LDS loads placed between the PV MFMAs; j_load / buf_load: its first key and ring slot.
-    //   2 (two key groups, one step per tile): K of that tile and V of the tile at j_v / buf_v
-    //   (codes: the tile at j_v is widened, the one at j_load, two further, starts on its way).
-    // first part: scores of the next subtile, V operands and exponentials (E, and P in bf16) of the current one
-    auto score_part = [&](auto src, auto bounded_tag, f32x16 &Scur, f32x16 &Snext, int voffs_cur, f32x16 &E, bf16x8 (&P)[2]) IFX_INLINE {
-        constexpr bool BOUNDED = decltype(bounded_tag)::value;
-        constexpr bool EXACT = decltype(bounded_tag)::exact;
-        constexpr float HEADROOM = EXACT ? BF_HEADROOM_EXACT : BF_HEADROOM;
-        constexpr int V_READS = decltype(src)::blk ? 2 : 1;  // LDS reads per V operand
-        qk(Kop, Snext);
-        v_fetch(src, voffs_cur, Vop);
-        exps(Scur, E, P);
-#pragma unroll
-        for (int g = 0; g < 8; ++g) {  // score MFMAs: V operand reads, exponentials
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            // The V operands are first used eight MFMAs on.  Cached keys: one operand read per MFMA
-            // from the first on.  Current block (two transposing reads per operand): under the last
-            // four score MFMAs only, four reads apiece; measured 3 % faster on that phase.
-            if constexpr (decltype(src)::blk) {
-                if (g >= 4) __builtin_amdgcn_sched_group_barrier(0x100, 2 * V_READS, 0);
-            } else {
-                __builtin_amdgcn_sched_group_barrier(0x100, V_READS, 0);
-            }
-            __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
-            __builtin_amdgcn_sched_group_barrier(0x400, 2, 0);
-        }
-        if constexpr (!BOUNDED) {
-            // Running maximum, checked after the fact: the exponentials were taken against the
-            // reference as it stood; only if one of them shows that a score lies above it, the
-            // reference is raised from the scores (still in Scur) and the exponentials are redone.
-            // Nothing of this subtile has reached the accumulators yet.
-            if (__builtin_expect(__any(p_reaches_two(P)), 0)) {
-                raise_for(Scur, HEADROOM);
-                exps(Scur, E, P);
-            }
-        }
-        // Wave priority: high while a wavefront is in its score phase (per MFMA 3 VALU and 2
-        // transcendental instructions), low in its PV phase (per MFMA 2 VALU).  The two wavefronts
-        // of a SIMD then settle into opposite phases: the one with the long instruction stream is
-        // never held up, the other one's MFMAs fill the gaps.  (The instruction ends a scheduling
-        // region, so each phase's instructions and its group sequence sit on their own side of it.)
-        __builtin_amdgcn_s_setprio(0);
-    };
     // What a step brings into the ring: the scalar offsets of its copies ...
     struct copy_offs {
         tile_offs first, second;
@@ -676,13 +625,69 @@ __global__ __launch_bounds__(BF_THREADS, 1) void attn_bf16_kernel(const attn_bf1
             issue_k_at(src, offs.first, buf_load);
         }
     };
-    // second part: the PV product and row sum of the current subtile, K operands of the one after the next
-    auto pv_part = [&](auto src, auto bounded_tag, auto load_tag, f32x16 &E, const bf16x8 (&P)[2], int koffs_after, const copy_offs &offs,
-                       int j_load, int buf_load, int buf_v) IFX_INLINE {
+    // One pipelined step of 16 MFMAs, one LDS operand per MFMA, each read about eight MFMAs
+    // ahead of its use.  Scores of the NEXT subtile (operands already in Kop) with the V operands of
+    // the CURRENT subtile fetched meanwhile and its exponentials spread under them; then the PV
+    // product of the current subtile with the K operands of the subtile AFTER the next fetched
+    // meanwhile and the current subtile's row-sum adds.
+    //   koffs_after: LDS offset of the subtile after the next; voffs_cur: offset of the current
+    //   subtile's V data.  Only for subtiles that lie wholly inside the phase (no key masking).
+    //   load_tag: which half of the tile three ahead this step brings in (0: K, 1: V), two
+    //   global->LDS loads placed between the PV MFMAs; j_load / buf_load: its first key and ring slot.
+    //   2 (two key groups, one step per tile): K of that tile and V of the tile at j_v / buf_v
+    //   (codes: the tile at j_v is widened, the one at j_load, two further, starts on its way).
+    auto halfstep = [&](auto src, auto bounded_tag, auto load_tag, auto idle_tag, f32x16 &Scur, f32x16 &Snext,
+                        int koffs_after, int voffs_cur, int j_load, int buf_load, int j_v = 0, int buf_v = 0) IFX_INLINE {
         constexpr int LOADS = decltype(load_tag)::value;
         constexpr bool BOUNDED = decltype(bounded_tag)::value;
         constexpr bool EXACT = decltype(bounded_tag)::exact;
+        constexpr float HEADROOM = EXACT ? BF_HEADROOM_EXACT : BF_HEADROOM;
+        constexpr int V_READS = decltype(src)::blk ? 2 : 1;  // LDS reads per V operand
         constexpr bool CODES = FP8 && !decltype(src)::blk;  // this phase's tiles come as E4M3 codes through registers
+        constexpr bool STAGGERED = LOADS == 2 && !CODES;    // a barrier between the two parts (see phase_pair)
+        bf16x8 P[2];
+        f32x16 E;
+        const copy_offs offs = copies_of(src, load_tag, j_load, j_v);  // for the copies of the PV phase
+        if constexpr (decltype(idle_tag)::value) {
+            // a wavefront without a query row: its share of the tile copies and nothing else
+            if constexpr (STAGGERED) __builtin_amdgcn_s_barrier();
+            bring_in(src, load_tag, offs, j_load, buf_load, buf_v);
+            return;
+        }
+        qk(Kop, Snext);
+        v_fetch(src, voffs_cur, Vop);
+        exps(Scur, E, P);
+#pragma unroll
+        for (int g = 0; g < 8; ++g) {  // score MFMAs: V operand reads, exponentials
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            // The V operands are first used eight MFMAs on.  Cached keys: one operand read per MFMA
+            // from the first on.  Current block (two transposing reads per operand): under the last
+            // four score MFMAs only, four reads apiece; measured 3 % faster on that phase.
+            if constexpr (decltype(src)::blk) {
+                if (g >= 4) __builtin_amdgcn_sched_group_barrier(0x100, 2 * V_READS, 0);
+            } else {
+                __builtin_amdgcn_sched_group_barrier(0x100, V_READS, 0);
+            }
+            __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
+            __builtin_amdgcn_sched_group_barrier(0x400, 2, 0);
+        }
+        if constexpr (!BOUNDED) {
+            // Running maximum, checked after the fact: the exponentials were taken against the
+            // reference as it stood; only if one of them shows that a score lies above it, the
+            // reference is raised from the scores (still in Scur) and the exponentials are redone.
+            // Nothing of this subtile has reached the accumulators yet.
+            if (__builtin_expect(__any(p_reaches_two(P)), 0)) {
+                raise_for(Scur, HEADROOM);
+                exps(Scur, E, P);
+            }
+        }
+        // Wave priority: high while a wavefront is in its score phase (per MFMA 3 VALU and 2
+        // transcendental instructions), low in its PV phase (per MFMA 2 VALU).  The two wavefronts
+        // of a SIMD then settle into opposite phases: the one with the long instruction stream is
+        // never held up, the other one's MFMAs fill the gaps.  (The instruction ends a scheduling
+        // region, so each phase's instructions and its group sequence sit on their own side of it.)
+        __builtin_amdgcn_s_setprio(0);
+        if constexpr (STAGGERED) __builtin_amdgcn_s_barrier();
         bring_in(src, load_tag, offs, j_load, buf_load, buf_v);
         pv(Vop, P);
         k_fetch(koffs_after, Kop);
@@ -718,23 +723,6 @@ __global__ __launch_bounds__(BF_THREADS, 1) void attn_bf16_kernel(const attn_bf1
             }
         }
         __builtin_amdgcn_s_setprio(1);
-    };
-    // Two key groups, tiles copied into LDS: a barrier between the parts (see phase_pair).
-    auto staggered = [](auto src, auto load_tag) constexpr { return decltype(load_tag)::value == 2 && !(FP8 && !decltype(src)::blk); };
-    auto halfstep = [&](auto src, auto bounded_tag, auto load_tag, auto idle_tag, f32x16 &Scur, f32x16 &Snext,
-                        int koffs_after, int voffs_cur, int j_load, int buf_load, int j_v = 0, int buf_v = 0) IFX_INLINE {
-        const copy_offs offs = copies_of(src, load_tag, j_load, j_v);  // for the copies of the PV phase
-        if constexpr (decltype(idle_tag)::value) {
-            // a wavefront without a query row: its share of the tile copies and nothing else
-            if constexpr (staggered(src, load_tag)) __builtin_amdgcn_s_barrier();
-            bring_in(src, load_tag, offs, j_load, buf_load, buf_v);
-        } else {
-            bf16x8 P[2];
-            f32x16 E;
-            score_part(src, bounded_tag, Scur, Snext, voffs_cur, E, P);
-            if constexpr (staggered(src, load_tag)) __builtin_amdgcn_s_barrier();
-            pv_part(src, bounded_tag, load_tag, E, P, koffs_after, offs, j_load, buf_load, buf_v);
-        }
     };
 
     // One phase: the Lp > 0 keys of one source, tiles of 64, through the accumulators O, l_acc and
