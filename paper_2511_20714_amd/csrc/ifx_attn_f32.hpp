@@ -29,8 +29,8 @@
 // Measured (1560 rows, 12 heads x 128, 3120 keys): 291 us = 103 TFLOP/s, where the library's plain
 // fp32 matrix product reaches 154 on the same card; 1840 us with fp32 FMA from LDS tiles.  With K
 // straight from memory 393 us; with 32 rows per wavefront (half the bytes per flop, but fewer and
-// larger workgroups) 390 us.  256 rows, 2 heads x 64, 1024 keys, and the block's commit: 19.8 us
-// (118.5 us with 32-row workgroups that do not deal the keys out).
+// larger workgroups) 390 us.  256 rows, 2 heads x 64, 1024 keys, and the block's commit: 18.4 us, of
+// which 14 are attention (118.6 us with 32-row workgroups that do not deal the keys out).
 #pragma once
 #include "ifx_types.hpp"
 
