@@ -32,6 +32,8 @@
 // larger workgroups) 390 us.  256 rows, 2 heads x 64, 1024 keys, and the block's commit: 18.4 us, of
 // which 14 are attention (118.6 us with 32-row workgroups that do not deal the keys out).
 #pragma once
+#include <cfloat>
+
 #include "ifx_types.hpp"
 
 namespace ifx {
@@ -184,7 +186,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) void a
     f32x4 O[SLABS];
 #pragma unroll
     for (int s = 0; s < SLABS; ++s) O[s] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float m = -INFINITY, l = 0.f;  // running maximum of the scaled scores (per query), this lane's share of the row sum
+    // running maximum of the scaled scores (per query), this lane's share of the row sum.  The maximum starts
+    // at the lowest finite value, not at -inf: a subtile whose scores are all -inf then has weight 0 (-inf
+    // less -inf is NaN), and so has a wavefront without keys
+    float m = -FLT_MAX, l = 0.f;
 
     for (int sub = wave; sub < subs; sub += S) {
         __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the K copies (V has been consumed) are in LDS
@@ -210,7 +215,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) void a
         t = fmaxf(t, __shfl_xor(t, 16));
         t = fmaxf(t, __shfl_xor(t, 32));
         if (__any(t > m)) {
-            const float m_new = fmaxf(m, t);      // finite: every subtile holds at least one key
+            const float m_new = fmaxf(m, t);
             const float alpha = expf(m - m_new);  // 0 on the first one
             l *= alpha;
 #pragma unroll
@@ -257,7 +262,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) void a
         const int rr = e / CH, c = e % CH;
         const int i = row0 + rr;
         if (i >= n || 4 * c >= D) continue;
-        float M = -INFINITY;  // finite in the end: wavefront 0 had at least one key
+        float M = -FLT_MAX;
         for (int s = 0; s < S; ++s) M = fmaxf(M, ml[2 * (s * F32_ROWS + rr)]);
         float sum = 0.f;
         f32x4 o = {0.f, 0.f, 0.f, 0.f};

@@ -46,3 +46,36 @@ def test_f32_attention_at_tile_edges(gpu_device, n, H, D, cap, commits, blocks, 
                                                None if v is None else synth.to_f64_numpy(v), rows, heads)
         assert np.abs(synth.to_f64_numpy(out)[rows, heads] - want).max() <= 1e-5
         assert np.abs(synth.to_f64_numpy(lse)[rows, heads] - want_lse).max() <= 2e-5
+
+
+@pytest.mark.parametrize("n,H,D,commits", [
+    (256, 2, 64, 3),    # 8 wavefronts: some of them first see keys that count nothing
+    (48, 3, 128, 1),
+    (1370, 3, 64, 1),   # 4 wavefronts
+])
+def test_f32_keys_with_scores_of_minus_infinity(gpu_device, n, H, D, commits):
+    """A key whose score is -inf for every query (an element of -inf against positive query elements)
+    has weight 0, whatever share of a wavefront's keys it makes up: the result is that of the other
+    keys.  Runs of such keys that fill subtiles, a wavefront's first subtile, a whole block."""
+    dev = gpu_device
+    blocks = [synth.draw_qkv(67, b, 0, 0, n, H, D, torch.float32, dev) for b in range(commits)] + [synth.draw_qkv(67, 999, 0, 0, n, H, D, torch.float32, dev)]
+    q = blocks[-1][0].clone()
+    q[..., 0] = q[..., 0].abs() + 0.5
+    keys, values = (np.concatenate([synth.to_f64_numpy(b[i]) for b in blocks]) for i in (1, 2))
+    r = np.unique(np.concatenate([np.arange(min(n, 20)), np.arange(n - 20, n)]))
+    rows, heads = np.repeat(r, H), np.tile(np.arange(H), len(r))
+    for lo, hi in ((5, 6), (16, 32), (32, 64), (16, n), (n, 2 * n), (2 * n - 20, 2 * n)):
+        with ifx.KVCache(1, H, D, commits * n, n, ifx.IFX_F32) as cache:
+            for b in range(commits + 1):
+                k = blocks[b][1].clone()
+                k[max(0, lo - b * n):max(0, hi - b * n), :, 0] = -float("inf")
+                if b < commits:
+                    cache.commit(0, k, blocks[b][2])
+            out = torch.full((n, H, D), float("nan"), device=dev)
+            lse = torch.full((n, H), float("nan"), device=dev)
+            cache.attention_blocks(0, q, k, blocks[-1][2], None, out, lse)
+            torch.cuda.synchronize()
+        count = np.r_[0:lo, hi:len(keys)]
+        want, want_lse = oracle.attention_rows(synth.to_f64_numpy(q), keys[count], values[count], None, None, rows, heads)
+        assert np.abs(synth.to_f64_numpy(out)[rows, heads] - want).max() <= 1e-5, (lo, hi)
+        assert np.abs(synth.to_f64_numpy(lse)[rows, heads] - want_lse).max() <= 2e-5, (lo, hi)
