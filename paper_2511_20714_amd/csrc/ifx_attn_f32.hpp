@@ -128,8 +128,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) void a
                                                  __builtin_amdgcn_readfirstlane(4 * ((rows - 1) * r.stride + D)), 0x00020000);
     };
     // K copies: LDS slot e = 64 x + lane (x = 0 .. KJ - 1; row e / CH, place e % CH) receives the row's
-    // chunk place ^ z(row).  Dimensions past D are read at dimension 0 and count nothing (Q is zero there).
+    // chunk place ^ z(row).  Dimensions past D are asked for behind the run's end and read as zero, like Q's
+    // there (at a dimension of the row an infinite element would meet Q's zero and make the score NaN).
     constexpr int ROWS_X = 64 % CH == 0 ? 64 / CH : 0;  // whole rows per copy instruction
+    // an offset behind any run: a run is at most 16 rows of 65535 heads of 128 floats, 2^29 bytes, and this and a
+    // row's offset added stay below 2^32
+    constexpr int PAST_RUN = 0x7f000000;
     auto z = [](int r) { return CH % 16 == 0 ? r : r >> 1; };
     float *const ktile = smem + wave * (F32_ROWS * DP);
     auto copy_k = [&](int sub) __attribute__((always_inline)) {
@@ -139,7 +143,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) void a
         for (int x = 0; x < KJ; ++x) {
             const int e = 64 * x + lane, row = e / CH, d = 4 * ((e % CH) ^ z(row));
             // (not const: with arguments that depend on DP the host pass rejects the builtin's size, silently)
-            int off_v = 4 * ((ROWS_X ? lane / CH : row) * r.stride + (d < D ? d : 0)), off_s = 4 * (ROWS_X * x) * r.stride;
+            int off_v = d < D ? 4 * ((ROWS_X ? lane / CH : row) * r.stride + d) : PAST_RUN, off_s = 4 * (ROWS_X * x) * r.stride;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(ktile + 256 * x), 16, off_v, off_s, 0, 0);
         }
     };

@@ -52,6 +52,9 @@ def test_f32_attention_at_tile_edges(gpu_device, n, H, D, cap, commits, blocks, 
     (256, 2, 64, 3),    # 8 wavefronts: some of them first see keys that count nothing
     (48, 3, 128, 1),
     (1370, 3, 64, 1),   # 4 wavefronts
+    (256, 2, 40, 3),    # head_dim padded to 64: the padding must not meet the infinite element
+    (100, 3, 72, 2),    # to 96
+    (33, 1, 8, 1),      # to 32
 ])
 def test_f32_keys_with_scores_of_minus_infinity(gpu_device, n, H, D, commits):
     """A key whose score is -inf for every query (an element of -inf against positive query elements)
@@ -64,7 +67,7 @@ def test_f32_keys_with_scores_of_minus_infinity(gpu_device, n, H, D, commits):
     keys, values = (np.concatenate([synth.to_f64_numpy(b[i]) for b in blocks]) for i in (1, 2))
     r = np.unique(np.concatenate([np.arange(min(n, 20)), np.arange(n - 20, n)]))
     rows, heads = np.repeat(r, H), np.tile(np.arange(H), len(r))
-    for lo, hi in ((5, 6), (16, 32), (32, 64), (16, n), (n, 2 * n), (2 * n - 20, 2 * n)):
+    for lo, hi in ((5, 6), (16, 32), (32, min(64, 2 * n)), (16, n), (n, 2 * n), (2 * n - 20, 2 * n)):
         with ifx.KVCache(1, H, D, commits * n, n, ifx.IFX_F32) as cache:
             for b in range(commits + 1):
                 k = blocks[b][1].clone()
