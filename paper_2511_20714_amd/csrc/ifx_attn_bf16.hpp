@@ -95,6 +95,9 @@ constexpr float BF_HEADROOM = 7.0f;
 // weight need not be a power of two to cancel, and raises can be made rare
 constexpr float BF_HEADROOM_EXACT = 31.0f;
 constexpr float BF_BOUND_LIMIT = 50.0f;                    // log2 units; 2^-100 is still a normal bf16 / fp32
+// The reference before a key has counted: the lowest finite value.  With -inf a first subtile whose
+// scores are all -inf would make the row NaN (-inf less -inf); every finite score lies above this.
+constexpr float BF_NO_REFERENCE = -3.402823466e+38f;
 
 struct attn_bf16_args {
     const __bf16 *q;    // [n, H, 128]
@@ -460,7 +463,7 @@ __global__ __launch_bounds__(BF_THREADS, 1) void attn_bf16_kernel(const attn_bf1
     for (int sl = 0; sl < 4; ++sl)
 #pragma unroll
         for (int r = 0; r < 16; ++r) O[sl][r] = 0.0f;
-    float m_used = -INFINITY;     // maximum the exponentials are taken against (scaled log2 units)
+    float m_used = BF_NO_REFERENCE;  // maximum the exponentials are taken against (scaled log2 units)
     float l_acc[4] = {0.f, 0.f, 0.f, 0.f};  // this lane's share of the row sum, in partial sums
 
     // The eight K operands (one per 16-wide d step) of the 32-key subtile at LDS byte offset koffs.
@@ -898,7 +901,7 @@ __global__ __launch_bounds__(BF_THREADS, 1) void attn_bf16_kernel(const attn_bf1
             k_fetch(0, Kop);
             qk(Kop, Sa);
             if constexpr (!BOUNDED) {
-                // (a phase of 32 keys or fewer leaves the second group without a key, and its reference at -inf)
+                // (a phase of 32 keys or fewer leaves the second group without a key, and its reference where it was)
                 if (j_own < Lp) {
                     mask_keys(Sa, j_own, Lp);
                     raise_for(Sa, HEADROOM);
@@ -1010,8 +1013,8 @@ __global__ __launch_bounds__(BF_THREADS, 1) void attn_bf16_kernel(const attn_bf1
     f32x16 R[SLABS];
     if constexpr (GROUPS == 2) {
         // The two key groups of a row: each gives the other two of its four slabs, its reference and
-        // its sum through LDS, and finishes the two it keeps.  A group without keys has reference
-        // -inf and weight 0; the other one then has keys.
+        // its sum through LDS, and finishes the two it keeps.  A group without keys has the lowest
+        // reference and weight 0; the other one then has keys.
         float *const give = reinterpret_cast<float *>(lds + wave * 8192) + lane * 4;
         const float *const take = reinterpret_cast<const float *>(lds + (wave ^ 1) * 8192) + lane * 4;
         f32x2 *const stats = reinterpret_cast<f32x2 *>(lds + BF_WAVES * 8192) + lane;

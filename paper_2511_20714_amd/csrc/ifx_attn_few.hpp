@@ -194,7 +194,7 @@ __global__ __launch_bounds__(64 * FEW_WAVES, 1) void attn_few_kernel(const attn_
     for (int sl = 0; sl < 4; ++sl)
 #pragma unroll
         for (int r = 0; r < 16; ++r) O[sl][r] = 0.0f;
-    float m_used = -INFINITY;  // reference of the exponentials (scaled log2 units); -inf: no key yet
+    float m_used = BF_NO_REFERENCE;  // reference of the exponentials (scaled log2 units)
     // this lane's share of the row sum: of the weights as rounded to bf16, which is what the PV product
     // uses (the output's denominator), and, where the log-sum-exp is asked for, of the fp32 exponentials
     float l_acc[4] = {0.f, 0.f, 0.f, 0.f}, e_acc[4] = {0.f, 0.f, 0.f, 0.f};
@@ -250,7 +250,7 @@ __global__ __launch_bounds__(64 * FEW_WAVES, 1) void attn_few_kernel(const attn_
                 for (int r = 0; r < 16; ++r) O[sl][r] *= alpha;
             m_used = m_next;
         };
-        if (sub == wave) raise();  // the first subtile (every subtile holds a key, so its largest score is one)
+        if (sub == wave) raise();  // the first subtile
         bf16x8 P[2];
         f32x8 E[2];
         auto exps = [&]() IFX_INLINE {
@@ -330,7 +330,7 @@ __global__ __launch_bounds__(64 * FEW_WAVES, 1) void attn_few_kernel(const attn_
     const int rr = tid >> 4, c = tid & 15;  // row of the tile, 8 output dimensions
     const int i = row0 + rr;
     if (i >= n) return;
-    float M = -INFINITY;  // finite in the end: wavefront 0 had a key
+    float M = BF_NO_REFERENCE;
 #pragma unroll
     for (int s = 0; s < FEW_WAVES; ++s) M = fmaxf(M, stats[s * FEW_ROWS + rr][0]);
     float sum = 0.f, sum_e = 0.f;

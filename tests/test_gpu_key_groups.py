@@ -73,3 +73,51 @@ def test_key_groups_at_every_switch(gpu_device, n, H, cap, commits, blocks, with
             assert_attention_close(to_np_exact(out)[rows, heads].astype(np.float64), want, ifx.IFX_BF16, f"gain {gain}")
             # a sum of weights rounded to bf16 (past the norm bound) is off by 2^-9 at most, one taken in fp32 by rounding alone
             assert np.abs(f64(lse)[rows, heads] - want_lse).max() <= 4e-3
+
+
+@pytest.mark.parametrize("dtype", [ifx.IFX_BF16, ifx.IFX_FP8_E4M3])
+@pytest.mark.parametrize("n,H,cap", [
+    (264, 2, 2),     # eight groups
+    (8, 3, 9),       # whole blocks that count nothing
+    (1560, 12, 1),   # two groups
+    (264, 135, 1),   # two groups, two rounds of workgroups
+    (200, 150, 2),   # one group
+])
+def test_keys_with_scores_of_minus_infinity(gpu_device, n, H, cap, dtype):
+    """Keys whose score is -inf for every query (finite elements whose product overflows) have weight
+    0, whatever share of a group's keys they make up: the result is that of the other keys."""
+    dev, D = gpu_device, 128
+    rng = np.random.default_rng(5)
+    hs = np.unique(np.concatenate([[0, H - 1], rng.integers(0, H, 2)]))
+    r = np.unique(np.concatenate([np.arange(min(n, 10)), np.arange(n - 8, n), rng.integers(0, n, 10)]))
+    rows, heads = np.repeat(r, len(hs)), np.tile(np.arange(len(hs)), len(r))
+    blocks = [synth.draw_qkv(29, b, 0, 0, n, H, D, torch.bfloat16, dev, rms_norm=True) for b in range(cap + 1)]
+    big = 2.0 ** 8 if dtype == ifx.IFX_FP8_E4M3 else 2.0 ** 64  # the largest codes are 448
+    q = blocks[cap][0].clone()
+    q[..., 0] = 3.0e38 if dtype == ifx.IFX_FP8_E4M3 else 2.0 ** 70
+    Lk = (cap + 1) * n
+    for lo, hi in ((5, 6), (32, 64), (n, 2 * n), (32, Lk - n), (Lk - 40 if n > 40 else Lk - 5, Lk)):
+        if lo >= hi:
+            continue
+        oc = OracleCacheFP8(cap) if dtype == ifx.IFX_FP8_E4M3 else OracleCacheF(cap, torch.bfloat16)
+        with ifx.KVCache(1, H, D, cap * n, n, dtype) as cache:
+            for b in range(cap + 1):
+                k = blocks[b][1].clone()
+                k[..., 0] = 0.0  # the keys that count do not meet the huge query element
+                k[max(0, lo - b * n):max(0, hi - b * n), :, 0] = -big
+                if b < cap:
+                    cache.commit(0, k, blocks[b][2])
+                    oc.commit(k[:, hs], blocks[b][2][:, hs])
+            out = torch.full((n, H, D), float("nan"), dtype=torch.bfloat16, device=dev)
+            lse = torch.full((n, H), float("nan"), device=dev)
+            cache.attention_blocks(0, q, k, blocks[cap][2], None, out, lse)
+            torch.cuda.synchronize()
+        kc, vc = oc.logical()
+        count = np.r_[0:lo, hi:Lk]
+        q0 = f64(q)[:, hs]
+        q0[..., 0] = 0.0
+        want, want_lse = oracle.attention_rows(q0, np.concatenate([kc, f64(k)[:, hs]])[count], np.concatenate([vc, f64(blocks[cap][2])[:, hs]])[count],
+                                               None, None, rows, heads)
+        assert_attention_close(to_np_exact(out)[rows, hs[heads]].astype(np.float64), want, ifx.IFX_BF16, f"{lo}..{hi}")
+        # (sums of weights rounded to bf16 are off by 2^-9 at most)
+        assert np.abs(f64(lse)[rows, hs[heads]] - want_lse).max() <= 4e-3, (lo, hi)
