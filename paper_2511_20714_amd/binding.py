@@ -65,6 +65,7 @@ _SIGS = {
     "ifx_ring_block_ids": (_int, [_vp, ctypes.POINTER(_i64), _int]),
     "ifx_ring_reset": (None, [_vp]),
     "ifx_ring_grow": (_int, [_vp, _i64, _int]),
+    "ifx_attention_key_groups": (_int, [_int, _int]),
     "ifx_attention_launch_grid": (_int, [_int, _int]),
     "ifx_attention_launch_item": (_int, [_int, _int, _int, ctypes.POINTER(_int)]),
 }
@@ -279,6 +280,10 @@ def ifx_ring_reset(ring) -> None:
 
 def ifx_ring_grow(ring, new_capacity_blocks: int, in_place: bool = False) -> None:
     _check(lib().ifx_ring_grow(ring, new_capacity_blocks, int(bool(in_place))))
+
+
+def ifx_attention_key_groups(block_tokens: int, heads: int) -> int:
+    return _check(lib().ifx_attention_key_groups(block_tokens, heads))
 
 
 def ifx_attention_launch_grid(block_tokens: int, heads: int) -> int:

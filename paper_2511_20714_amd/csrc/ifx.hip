@@ -1152,6 +1152,12 @@ int ifx_ring_grow(ifx_ring *r, int64_t new_capacity_blocks, int in_place)
     return IFX_OK;
 }
 
+int ifx_attention_key_groups(int block_tokens, int heads)
+{
+    if (block_tokens < 1 || heads < 1) return fail(IFX_ERR_INVALID_ARG, "key_groups: block_tokens and heads must be positive");
+    return ifx::attn_groups_for(block_tokens, heads);
+}
+
 int ifx_attention_launch_grid(int block_tokens, int heads)
 {
     if (block_tokens < 1 || heads < 1) return fail(IFX_ERR_INVALID_ARG, "launch_grid: block_tokens and heads must be positive");

@@ -52,23 +52,36 @@ inline attn_shape attn_shape_for(int n, int heads, int row_waves = 8)
 }
 
 // Into how many groups of wavefronts a call's keys are dealt.  One (a wavefront takes every key) is
-// the least copying per flop and the choice wherever 256-row workgroups fill the chip.  Two (128
-// rows per workgroup, half the keys per wavefront: half the serial chain at 1.15 times the work)
-//  - when its workgroups still run in one round on 256 CUs: 1.2 .. 1.8 times as fast (1560 rows x 12
-//    heads x 10920 keys 176 -> 111 us; 4680 x 6 x 14040 226 -> 178); one more workgroup is a second
-//    round (4680 x 7: 231 -> 316);
-//  - when 256-row workgroups need a short second round, which costs as long as a full one: up to about
-//    700 (4680 x 14 x 14040: 571 -> 508 us, 10800 x 6 x 32400: 1300 -> 862; level at 740, and at
-//    888 0.92 times as fast).
+// the least copying per flop and the choice wherever 256-row workgroups fill the chip, and where a
+// head's rows are so few that its keys are read once either way: up to 5 wavefronts of rows per head
+// two groups have (almost) the same workgroups, twice the start and end, and nothing to gain at the
+// memory's rate (128 rows x 300 heads x 896 keys: 41 us, 46 with two; 32 x 257 x 256: 16.2, 17.6;
+// 136 x 100 x 136: 9.6, 9.7; 168 x 100 x 168: 10.8, 9.8).
+// Two (128 rows per workgroup, half the keys per wavefront: half the serial chain at 1.15 times the
+// work) is taken by its rounds of workgroups on 256 CUs:
+//  - one round: 1.04 .. 1.8 times as fast (1560 rows x 12 heads x 10920 keys 176 -> 106 us; 4680 x 6 x
+//    14040 228 -> 168); one more workgroup is a second round (4680 x 7: 231 -> 316);
+//  - two, where 256-row workgroups need a short second one, which costs as long as a full one: 1.1 ..
+//    1.5 (264 x 135 x 1056 50 -> 39 us; 10800 x 6 x 32400 1259 -> 820);
+//  - three short ones instead of two long ones: three of a two-group workgroup take 0.9 of two of the
+//    others, so it pays only where a workgroup's start and end are lost in its keys, from about 1150
+//    rows on (1160 x 52: 1.02 .. 1.1 times as fast, 4680 x 18 1.06 .. 1.1; 1032 x 57 .. 76 0.98 .. 1.09, 392 x 135
+//    0.87 .. 1.02), and only up to about 680 workgroups (level at 690 .. 760).
+// Measured on both caches, with and without a block table, under and past the norm bound: the lines lie
+// in the same places (an fp8 cache gains a little less throughout).
 // Eight (ifx_attn_few.hpp: 32 rows per workgroup) when even that is one round: 2 .. 3 times as fast
-// as one group, 1.5 as two (1560 x 5 x 10920: 176, 102, 65 us; 264 x 2 x 792: 21.2, 16.5, 10.3); at two
-// rounds (1560 x 6) it falls behind two groups.
+// as one group, 1.5 as two (1560 x 5 x 10920: 176, 102, 63 us; 264 x 2 x 792: 21.2, 16.5, 10.1); level
+// with one for a handful of keys (64 rows and less, no cached keys); at two rounds (1560 x 6) it falls
+// behind two groups.
 // The rule looks at the rows only, never at the keys: a block's calls all take the same path.
 inline int attn_groups_for(int n, int heads)
 {
-    if ((int64_t)((n + 31) / 32) * heads <= 256) return 8;
+    const int row_wavefronts = (n + 31) / 32;
+    if ((int64_t)row_wavefronts * heads <= 256) return 8;
+    if (row_wavefronts <= 5) return 1;
     const unsigned whole = attn_shape_for(n, heads).grid, halved = attn_shape_for(n, heads, 4).grid;
-    return halved <= 256 || (whole > 256 && halved <= 680) ? 2 : 1;
+    if (halved <= 256) return 2;
+    return whole > 256 && halved <= (row_wavefronts > 36 ? 680 : 512) ? 2 : 1;
 }
 
 __host__ __device__ inline attn_item attn_item_of(const attn_shape &s, unsigned workgroup)

@@ -249,3 +249,26 @@ def test_attention_launch_shape_rejects_bad_arguments():
     busy = [ifx.ifx_attention_launch_item(4680, 12, w) for w in range(grid)]
     assert sum(1 for it in busy if it[3] > 0) == 228
     assert sorted(it[3] for it in busy if it[0] == 0 and it[3] > 0) == [7] * 5 + [8] * 14
+
+
+@pytest.mark.parametrize("groups,shapes", [
+    # 32-row workgroups as long as they are one round on 256 CUs
+    (8, [(8, 1), (8, 256), (32, 256), (264, 28), (1560, 5), (8192, 1)]),
+    # up to 160 rows a head: a head's workgroups are the same, or read its keys once more, with two groups
+    (1, [(8, 257), (32, 257), (32, 600), (64, 131), (104, 250), (128, 65), (128, 300), (136, 64), (160, 300)]),
+    # 128-row workgroups in one round
+    (2, [(168, 43), (192, 128), (256, 128), (264, 85), (520, 16), (1560, 6), (1560, 12), (4680, 6)]),
+    (1, [(168, 130), (256, 200), (264, 86), (520, 64), (4680, 7), (4680, 12)]),
+    # in two rounds, where 256-row workgroups take two as well
+    (2, [(264, 135), (264, 170), (520, 100), (1560, 39), (10800, 6)]),
+    # in three: only from 37 wavefronts of rows on, and up to 680 workgroups
+    (2, [(1160, 52), (1160, 68), (1560, 40), (4680, 14), (4680, 18), (10800, 8)]),
+    (1, [(192, 300), (256, 300), (264, 200), (392, 135), (520, 130), (1032, 57), (1152, 58), (1560, 58), (4680, 20), (10800, 40)]),
+])
+def test_key_groups_where_they_pay(groups, shapes):
+    """Where a call's keys are dealt to groups: on either side of every line of the rule."""
+    for n, heads in shapes:
+        assert ifx.ifx_attention_key_groups(n, heads) == groups, (n, heads)
+    for bad in ((0, 12), (4680, 0), (-8, 3)):
+        with pytest.raises(ifx.IfxError):
+            ifx.ifx_attention_key_groups(*bad)
