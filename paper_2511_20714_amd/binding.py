@@ -119,8 +119,9 @@ def _stream(stream) -> int:
         import torch
 
         # the raw handle of torch.cuda.current_stream(), without building the stream object, which took
-        # 2.9 of a call's 6.9 us
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        # 2.9 of a call's 6.9 us (a private name of torch: where it is not there, the long way)
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        return torch.cuda.current_stream().cuda_stream if raw is None else raw(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream

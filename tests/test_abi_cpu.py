@@ -172,6 +172,21 @@ def test_no_cpu_fallback_without_a_device():
     assert e.value.code == ifx.IFX_ERR_HIP
 
 
+def test_current_stream_with_and_without_torchs_raw_handle(monkeypatch):
+    """stream=None is the current stream of the current device, whether or not this torch has the
+    private function that gives its handle directly."""
+    torch = pytest.importorskip("torch")
+    import types
+
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 100 + device, raising=False)
+    assert ifx._stream(None) == 103
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    assert ifx._stream(None) == 77
+    assert ifx._stream(5) == 5 and ifx._stream(types.SimpleNamespace(cuda_stream=9)) == 9
+
+
 def test_bench_refuses_more_than_one_gpu():
     """bench.py is a one-GPU benchmark: any other --gpus value ends with a message, before any GPU work."""
     import subprocess
