@@ -342,24 +342,24 @@ void ifx_ring_reset(ifx_ring *ring);
  * in_place != 0: they stay in their slots and the new slots are used next */
 int ifx_ring_grow(ifx_ring *ring, int64_t new_capacity_blocks, int in_place);
 
-/* ---- launch shape of the bf16 attention kernel, for CPU tests -------------------------------
+/* ---- launch shapes of the bf16 attention kernels, for CPU tests ------------------------------
  * No passage of the paper: which workgroup takes which head and which query rows is this
- * library's own arithmetic (host integers that the kernel decodes with the same function).
- * ifx_attention_launch_grid and _item describe the launch with up to 256 query rows per workgroup; a
- * call with too few rows to occupy the chip that way runs with smaller workgroups among whose
- * wavefronts the keys are dealt (ifx_attention_key_groups > 1).
+ * library's own arithmetic (host integers that the kernels decode with the same functions).
  * Pure host code, no device call.
  *
  * ifx_attention_key_groups: into how many groups of wavefronts the keys of a bf16 or fp8 cache's
- * calls are dealt, by the rows alone: 1 (256 query rows per workgroup), 2 (128) or 8 (32);
+ * calls are dealt, by the rows alone: 1 (up to 256 query rows per workgroup), 2 (up to 128) or 8 (32);
  * IFX_ERR_INVALID_ARG (< 0) if either argument is < 1.
- * ifx_attention_launch_grid: workgroups of one attention launch over blocks of `block_tokens`
- * tokens and `heads` heads; IFX_ERR_INVALID_ARG (< 0) if either is < 1.
- * ifx_attention_launch_item: what workgroup `workgroup` of that launch does, written to item[0..4]:
- * head, query tile of the head, first query row, wavefronts that hold rows (32 rows each, 1..8;
- * 0: the workgroup exits at once, the other entries are then meaningless), XCD it runs on
- * (workgroup % 8).  IFX_ERR_INVALID_ARG for a workgroup outside the grid or item == NULL. */
+ * ifx_attention_group_grid: workgroups of one attention launch over blocks of `block_tokens` tokens
+ * and `heads` heads with `groups` (1, 2, 8) key groups; IFX_ERR_INVALID_ARG (< 0) for anything else.
+ * ifx_attention_group_item: what workgroup `workgroup` of that launch does, written to item[0..4]:
+ * head, query tile of the head, first query row, wavefronts' worth of rows it holds (32 rows each, up
+ * to 8, 4 or 1; 0: the workgroup exits at once, the other entries are then meaningless), XCD it
+ * runs on (workgroup % 8).  IFX_ERR_INVALID_ARG for a workgroup outside the grid or item == NULL.
+ * ifx_attention_launch_grid, ifx_attention_launch_item: the same with one group. */
 int ifx_attention_key_groups(int block_tokens, int heads);
+int ifx_attention_group_grid(int block_tokens, int heads, int groups);
+int ifx_attention_group_item(int block_tokens, int heads, int groups, int workgroup, int *item);
 int ifx_attention_launch_grid(int block_tokens, int heads);
 int ifx_attention_launch_item(int block_tokens, int heads, int workgroup, int *item);
 

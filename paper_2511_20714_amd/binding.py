@@ -66,6 +66,8 @@ _SIGS = {
     "ifx_ring_reset": (None, [_vp]),
     "ifx_ring_grow": (_int, [_vp, _i64, _int]),
     "ifx_attention_key_groups": (_int, [_int, _int]),
+    "ifx_attention_group_grid": (_int, [_int, _int, _int]),
+    "ifx_attention_group_item": (_int, [_int, _int, _int, _int, ctypes.POINTER(_int)]),
     "ifx_attention_launch_grid": (_int, [_int, _int]),
     "ifx_attention_launch_item": (_int, [_int, _int, _int, ctypes.POINTER(_int)]),
 }
@@ -285,6 +287,17 @@ def ifx_ring_grow(ring, new_capacity_blocks: int, in_place: bool = False) -> Non
 
 def ifx_attention_key_groups(block_tokens: int, heads: int) -> int:
     return _check(lib().ifx_attention_key_groups(block_tokens, heads))
+
+
+def ifx_attention_group_grid(block_tokens: int, heads: int, groups: int) -> int:
+    return _check(lib().ifx_attention_group_grid(block_tokens, heads, groups))
+
+
+def ifx_attention_group_item(block_tokens: int, heads: int, groups: int, workgroup: int):
+    """(head, row tile, first row, wavefronts' worth of rows, xcd) of one workgroup of a launch with `groups` key groups."""
+    item = (_int * 5)()
+    _check(lib().ifx_attention_group_item(block_tokens, heads, groups, workgroup, item))
+    return tuple(item)
 
 
 def ifx_attention_launch_grid(block_tokens: int, heads: int) -> int:

@@ -812,10 +812,9 @@ static int attention_impl(ifx_kv_cache *c, int layer, const void *q, const void 
         a.k_tokens = c->k_tokens;
         a.v_tokens = c->v_tokens;
         a.scale_log2 = c->scale * 1.4426950408889634f;
-        a.tiles = (n + ifx::FEW_ROWS - 1) / ifx::FEW_ROWS;
-        a.per_xcd = (a.tiles * H + 7) / 8;
+        a.tiles = ifx::row_tiles_for(n, H, ifx::FEW_ROWS);
         a.blocks = table;
-        hipLaunchKernelGGL(few_kernel(c->dtype == IFX_FP8_E4M3), dim3((unsigned)(8 * a.per_xcd)), dim3(64 * ifx::FEW_WAVES), ifx::FEW_LDS_BYTES, s, a);
+        hipLaunchKernelGGL(few_kernel(c->dtype == IFX_FP8_E4M3), dim3((unsigned)(8 * a.tiles.per_xcd)), dim3(64 * ifx::FEW_WAVES), ifx::FEW_LDS_BYTES, s, a);
     } else if (c->mfma()) {
         ifx::attn_bf16_args a;
         a.q = static_cast<const __bf16 *>(q);
@@ -841,9 +840,8 @@ static int attention_impl(ifx_kv_cache *c, int layer, const void *q, const void 
         hipLaunchKernelGGL(bf16_kernel(use_table, c->dtype == IFX_FP8_E4M3, groups), dim3(a.shape.grid), dim3(ifx::BF_THREADS),
                            ifx::BF_LDS_BYTES, s, a);
     } else {
-        const int tiles = (n + ifx::F32_ROWS - 1) / ifx::F32_ROWS;
-        const int64_t groups = (int64_t)tiles * H, per_xcd = (groups + 7) / 8;
-        const int waves = ifx::attn_f32_waves(groups);
+        const ifx::row_tiles tiles = ifx::row_tiles_for(n, H, ifx::F32_ROWS);
+        const int waves = ifx::attn_f32_waves((int64_t)tiles.tiles * H);
         ifx::attn_f32_args a;
         a.q = static_cast<const float *>(q);
         a.kc = reinterpret_cast<const float *>(c->k_of(layer));
@@ -860,9 +858,8 @@ static int attention_impl(ifx_kv_cache *c, int layer, const void *q, const void 
         a.cache_tokens = c->k_tokens;
         a.scale = c->scale;
         a.tiles = tiles;
-        a.per_xcd = (int)per_xcd;
         a.blocks = table;
-        hipLaunchKernelGGL(f32_kernel(D), dim3((unsigned)(8 * per_xcd)), dim3(64 * waves), ifx::attn_f32_lds_bytes(f32_padded_dim(D), waves), s, a);
+        hipLaunchKernelGGL(f32_kernel(D), dim3((unsigned)(8 * tiles.per_xcd)), dim3(64 * waves), ifx::attn_f32_lds_bytes(f32_padded_dim(D), waves), s, a);
     }
     IFX_HIP(hipGetLastError());
     return sample.end();
@@ -1158,26 +1155,43 @@ int ifx_attention_key_groups(int block_tokens, int heads)
     return ifx::attn_groups_for(block_tokens, heads);
 }
 
-int ifx_attention_launch_grid(int block_tokens, int heads)
+int ifx_attention_group_grid(int block_tokens, int heads, int groups)
 {
     if (block_tokens < 1 || heads < 1) return fail(IFX_ERR_INVALID_ARG, "launch_grid: block_tokens and heads must be positive");
-    return (int)ifx::attn_shape_for(block_tokens, heads).grid;
+    if (groups == 8) return 8 * ifx::row_tiles_for(block_tokens, heads, ifx::FEW_ROWS).per_xcd;
+    if (groups != 1 && groups != 2) return fail(IFX_ERR_INVALID_ARG, "launch_grid: %d key groups (1, 2 or 8)", groups);
+    return (int)ifx::attn_shape_for(block_tokens, heads, ifx::BF_WAVES / groups).grid;
 }
 
-int ifx_attention_launch_item(int block_tokens, int heads, int workgroup, int *item)
+int ifx_attention_group_item(int block_tokens, int heads, int groups, int workgroup, int *item)
 {
     if (block_tokens < 1 || heads < 1) return fail(IFX_ERR_INVALID_ARG, "launch_item: block_tokens and heads must be positive");
     if (!item) return fail(IFX_ERR_INVALID_ARG, "launch_item: item is NULL");
-    const ifx::attn_shape shape = ifx::attn_shape_for(block_tokens, heads);
-    if (workgroup < 0 || (unsigned)workgroup >= shape.grid)
-        return fail(IFX_ERR_INVALID_ARG, "launch_item: workgroup %d outside the grid of %u", workgroup, shape.grid);
-    const ifx::attn_item it = ifx::attn_item_of(shape, (unsigned)workgroup);
+    const int grid = ifx_attention_group_grid(block_tokens, heads, groups);
+    if (grid < 0) return grid;
+    if (workgroup < 0 || workgroup >= grid) return fail(IFX_ERR_INVALID_ARG, "launch_item: workgroup %d outside the grid of %d", workgroup, grid);
+    item[4] = workgroup & 7;
+    if (groups == 8) {
+        const ifx::row_tile it = ifx::row_tile_of(ifx::row_tiles_for(block_tokens, heads, ifx::FEW_ROWS), heads, (unsigned)workgroup);
+        item[0] = it.head;
+        item[1] = it.tile;
+        item[2] = it.tile * ifx::FEW_ROWS;
+        item[3] = it.head < 0 ? 0 : 1;
+        return IFX_OK;
+    }
+    const ifx::attn_item it = ifx::attn_item_of(ifx::attn_shape_for(block_tokens, heads, ifx::BF_WAVES / groups), (unsigned)workgroup);
     item[0] = it.head;
     item[1] = it.q_tile;
     item[2] = it.row0;
     item[3] = it.waves;
-    item[4] = workgroup & 7;
     return IFX_OK;
+}
+
+int ifx_attention_launch_grid(int block_tokens, int heads) { return ifx_attention_group_grid(block_tokens, heads, 1); }
+
+int ifx_attention_launch_item(int block_tokens, int heads, int workgroup, int *item)
+{
+    return ifx_attention_group_item(block_tokens, heads, 1, workgroup, item);
 }
 
 }  // extern "C"

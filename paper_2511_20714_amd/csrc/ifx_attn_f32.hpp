@@ -34,6 +34,7 @@
 #pragma once
 #include <cfloat>
 
+#include "ifx_launch.hpp"
 #include "ifx_types.hpp"
 
 namespace ifx {
@@ -47,7 +48,7 @@ struct attn_f32_args {
     int n, C, n_blk, H, D;               // cached keys (the caller's selection, whole blocks of n tokens), then the block's: n or 0
     int64_t cache_tokens;
     float scale;
-    int tiles, per_xcd;                  // workgroups per head; workgroups per XCD
+    row_tiles tiles;                     // workgroup -> (head, row tile), see ifx_launch.hpp
     ifx_key_blocks blocks;
 };
 
@@ -74,12 +75,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) void a
     extern __shared__ __attribute__((aligned(16))) float smem[];
     typedef __attribute__((address_space(3))) void *lds_ptr;
 
-    // workgroups are dealt round-robin to the XCDs: each takes a contiguous run of (head, row tile)
-    // items, so that a head's keys are read into as few L2s as possible
-    const int item = (int)(blockIdx.x & 7u) * a.per_xcd + (int)(blockIdx.x >> 3);
-    if (item >= a.H * a.tiles) return;
-    const int h = item / a.tiles, row0 = (item - h * a.tiles) * F32_ROWS;
     const int n = a.n, H = a.H, D = a.D, C = a.C;
+    const row_tile item = row_tile_of(a.tiles, H, blockIdx.x);
+    if (item.head < 0) return;
+    const int h = item.head, row0 = item.tile * F32_ROWS;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int S = (int)blockDim.x >> 6;

@@ -45,7 +45,7 @@ struct attn_few_args {
     int C, nb;                        // cached keys (whole blocks of n), keys of the current block (n or 0); C + nb > 0
     int64_t k_tokens, v_tokens;
     float scale_log2;
-    int tiles, per_xcd;               // row tiles per head; workgroups per XCD
+    row_tiles tiles;                  // workgroup -> (head, row tile), see ifx_launch.hpp
     ifx_key_blocks blocks;
 };
 
@@ -56,11 +56,10 @@ __global__ __launch_bounds__(64 * FEW_WAVES, 1) void attn_few_kernel(const attn_
     constexpr int COPIES = FP8 ? 4 : 8;          // copy instructions of a cached K subtile (V, and subtiles of the block: always 8)
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
 
-    // workgroups are dealt round-robin to the XCDs: each takes a contiguous run of (head, row tile)
-    const int item = (int)(blockIdx.x & 7u) * a.per_xcd + (int)(blockIdx.x >> 3);
-    if (item >= a.H * a.tiles) return;
-    const int head = item / a.tiles, row0 = (item - head * a.tiles) * FEW_ROWS;
     const int n = a.n, H = a.H;
+    const row_tile item = row_tile_of(a.tiles, H, blockIdx.x);
+    if (item.head < 0) return;
+    const int head = item.head, row0 = item.tile * FEW_ROWS;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lq = lane & 31, lh = lane >> 5;

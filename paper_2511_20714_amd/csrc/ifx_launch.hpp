@@ -1,7 +1,7 @@
-// The launch shape of the bf16 attention kernel: how many workgroups, and which head and which
-// query rows each of them takes.  Plain integer code shared by the host (which fills the shape in),
-// the kernel (which decodes its workgroup number with it) and the CPU tests (which check, through
-// the library's diagnostic calls, that the decoded items tile every head's rows exactly once).
+// The launch shapes of the attention kernels: how many workgroups, and which head and which query
+// rows each of them takes.  Plain integer code shared by the host (which fills the shape in), the
+// kernels (which decode their workgroup number with it) and the CPU tests (which check, through the
+// library's diagnostic calls, that the decoded items tile every head's rows exactly once).
 //
 // Workgroups are dealt round-robin to the 8 XCDs (workgroup w runs on XCD w % 8), each with an L2
 // of its own.  A head's K/V stream is shared by all its workgroups, so a head is given to as few
@@ -108,6 +108,34 @@ __host__ __device__ inline attn_item attn_item_of(const attn_shape &s, unsigned 
     it.row0 = 32 * (it.q_tile * s.q_waves + (it.q_tile < s.q_more ? it.q_tile : s.q_more));
     it.waves = s.q_waves + (it.q_tile < s.q_more ? 1 : 0);
     return it;
+}
+
+// The kernels whose workgroups take one tile of rows each (bf16 with the keys dealt to eight groups, 32
+// rows; fp32, 16 rows): the (head, tile) items in order, every XCD a contiguous run of them, so that
+// a head's keys are read into as few L2s as possible.
+struct row_tiles {
+    int tiles;    // per head
+    int per_xcd;  // workgroups per XCD: 8 times as many are launched, the last few may exit at once
+};
+
+struct row_tile {
+    int head, tile;  // head < 0: nothing to do
+};
+
+inline row_tiles row_tiles_for(int n, int heads, int rows)
+{
+    row_tiles t;
+    t.tiles = (n + rows - 1) / rows;
+    t.per_xcd = (int)(((int64_t)t.tiles * heads + 7) / 8);
+    return t;
+}
+
+__host__ __device__ inline row_tile row_tile_of(const row_tiles &t, int heads, unsigned workgroup)
+{
+    const int item = (int)(workgroup & 7u) * t.per_xcd + (int)(workgroup >> 3);
+    if (item >= heads * t.tiles) return {-1, 0};
+    const int head = item / t.tiles;
+    return {head, item - head * t.tiles};
 }
 
 }  // namespace ifx

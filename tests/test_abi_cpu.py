@@ -287,3 +287,45 @@ def test_key_groups_where_they_pay(groups, shapes):
     for bad in ((0, 12), (4680, 0), (-8, 3)):
         with pytest.raises(ifx.IfxError):
             ifx.ifx_attention_key_groups(*bad)
+
+
+@pytest.mark.parametrize("heads", [1, 2, 3, 5, 7, 8, 9, 12, 13, 17, 40, 130, 257])
+@pytest.mark.parametrize("groups", [1, 2, 8])
+def test_attention_group_items_tile_every_head(heads, groups):
+    """The launches with one, two and eight key groups, decoded by the functions the kernels use: the
+    workgroups' items cover rows 0 .. n - 1 of every head exactly once, at most 8, 4 or 1 wavefronts'
+    worth of rows apiece; with eight groups a head's tiles sit on neighbouring XCDs."""
+    most = {1: 8, 2: 4, 8: 1}[groups]
+    for n in (8, 32, 40, 128, 136, 200, 264, 1032, 1560, 4680):
+        if heads > 40 and n > 264:
+            continue
+        grid = ifx.ifx_attention_group_grid(n, heads, groups)
+        assert grid % 8 == 0
+        covered = collections.defaultdict(list)
+        xcds = collections.defaultdict(set)
+        for w in range(grid):
+            head, tile, row0, waves, xcd = ifx.ifx_attention_group_item(n, heads, groups, w)
+            assert xcd == w % 8
+            if groups == 1:
+                assert ifx.ifx_attention_launch_item(n, heads, w) == (head, tile, row0, waves, xcd)
+            if waves == 0:
+                continue
+            assert 0 <= head < heads and 1 <= waves <= most and row0 % 32 == 0
+            covered[head].append((row0, waves, tile))
+            xcds[head].add(xcd)
+        assert sorted(covered) == list(range(heads)), n
+        for head, items in covered.items():
+            items.sort()
+            assert [tile for _, _, tile in items] == list(range(len(items)))
+            nxt = 0
+            for row0, waves, _ in items:
+                assert row0 == nxt, (n, head)
+                nxt = row0 + 32 * waves
+            assert n <= nxt < n + 32  # the last wavefront's worth holds the last row
+            if groups == 8:
+                assert max(xcds[head]) - min(xcds[head]) + 1 == len(xcds[head])
+    for bad in ((0, heads, groups), (8, 0, groups), (8, heads, 4)):
+        with pytest.raises(ifx.IfxError):
+            ifx.ifx_attention_group_grid(*bad)
+    with pytest.raises(ifx.IfxError):
+        ifx.ifx_attention_group_item(8, heads, groups, ifx.ifx_attention_group_grid(8, heads, groups))
