@@ -268,12 +268,16 @@ __global__ __launch_bounds__(BF_THREADS, 1) void attn_bf16_kernel(const attn_bf1
     // 32-wide d slab, and receives column l & 31 of those 4 rows.  The 4 rows of a group then lie
     // in 4 different quarters of the 64 banks.
     int vtoff[4];
-    {
+    auto transposing_reads = [&]() IFX_INLINE {
         const int l16 = lane & 15, g = lane >> 4;
         const int base = BF_LDS_V0 + group_at + (8 * (g >> 1) + (l16 >> 2)) * 256 + (2 * (g & 1) + ((l16 & 3) >> 1)) * 16 + 8 * (l16 & 1);
 #pragma unroll
         for (int sl = 0; sl < 4; ++sl) vtoff[sl] = base + ((sl ^ (l16 >> 2)) << 6);
-    }
+    };
+    // (two groups over codes: worked out where the current block begins.  Live through the cached keys
+    // they would be spilled, and a kernel with spills makes the runtime allocate scratch memory)
+    constexpr bool LATE = FP8 && GROUPS == 2;
+    if constexpr (!LATE) transposing_reads();
 
     // ---- global -> LDS copy roles: 2 K chunks and 2 V chunks of 16 bytes per lane per tile.
     // LDS slot c = tid + BF_THREADS x (16 bytes each).  K: slot (key = c >> 4, pos = c & 15) receives
@@ -964,6 +968,7 @@ __global__ __launch_bounds__(BF_THREADS, 1) void attn_bf16_kernel(const attn_bf1
         wait_loads_and_sync<0>();  // nothing is on its way into the ring any more, and nobody reads it
     };
     auto keys_of = [&](auto src, auto bounded_tag, auto idle_tag, const int Lp) IFX_INLINE {
+        if constexpr (LATE && decltype(src)::blk) transposing_reads();
         if constexpr (GROUPS == 2)
             phase_pair(src, bounded_tag, idle_tag, Lp);
         else

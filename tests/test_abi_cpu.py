@@ -329,3 +329,26 @@ def test_attention_group_items_tile_every_head(heads, groups):
             ifx.ifx_attention_group_grid(*bad)
     with pytest.raises(ifx.IfxError):
         ifx.ifx_attention_group_item(8, heads, groups, ifx.ifx_attention_group_grid(8, heads, groups))
+
+
+def test_kernels_need_no_scratch_memory(tmp_path):
+    """A kernel with spilled registers makes the runtime allocate scratch memory at its launch, behind
+    the back of callers that may not allocate.  Only the block-table instances over an fp8 cache
+    have any (a few registers, as the one-group instance always had)."""
+    import shutil
+    import subprocess
+
+    llvm = "/opt/rocm/llvm/bin"
+    tools = [os.path.join(llvm, t) for t in ("llvm-objcopy", "clang-offload-bundler", "llvm-readelf")]
+    if not all(shutil.which(t) for t in tools):
+        pytest.skip("no LLVM tools")
+    objcopy, bundler, readelf = tools
+    ifx.lib()
+    fat, code = str(tmp_path / "fat"), str(tmp_path / "code")
+    subprocess.check_call([objcopy, "--dump-section", ".hip_fatbin=" + fat, ifx.LIB_PATH, str(tmp_path / "copy")])
+    subprocess.check_call([bundler, "--unbundle", "--type=o", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", "--input=" + fat, "--output=" + code])
+    notes = subprocess.check_output([readelf, "--notes", code], text=True)
+    kernels = re.findall(r"\.name:\s+(\S*kernel\S*)\n\s+\.private_segment_fixed_size:\s+(\d+)", notes)
+    assert len(kernels) >= 20
+    with_scratch = {name: int(size) for name, size in kernels if int(size)}
+    assert all("attn_bf16_kernelILb1ELb1E" in name and size <= 40 for name, size in with_scratch.items()), with_scratch
