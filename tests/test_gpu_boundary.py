@@ -20,16 +20,21 @@ def all_pairs(n, H):
     return np.repeat(np.arange(n), H), np.tile(np.arange(H), n)
 
 
-@pytest.mark.parametrize("dtype,D", [(ifx.IFX_BF16, 128), (ifx.IFX_F32, 64)])
+@pytest.mark.parametrize("dtype,D,H", [
+    (ifx.IFX_BF16, 128, 3),    # eight key groups
+    (ifx.IFX_BF16, 128, 40),   # two
+    (ifx.IFX_BF16, 128, 130),  # one
+    (ifx.IFX_F32, 64, 3),
+])
 @pytest.mark.parametrize("scale", [0.05, 0.25])
-def test_softmax_scale_other_than_default(gpu_device, dtype, D, scale):
+def test_softmax_scale_other_than_default(gpu_device, dtype, D, H, scale):
     """ifx_kv_cache_configure's softmax_scale reaches the scores, the norm bound and the
     log-sum-exp.  0.05 is below 1/sqrt(D) (flatter rows); 0.25 is above it: with RMS-normed bf16
     rows the bound is 128 * 0.25 * log2(e) = 46 (still the fixed-maximum variant), and the
     rows with 1.5 x longer queries go over the limit and take the running maximum."""
     dev = gpu_device
     tdtype = TORCH_DTYPE[dtype]
-    n, H, cap = 200, 3, 3
+    n, cap = 200, 3
     with ifx.KVCache(1, H, D, cap * n, n, dtype, softmax_scale=scale) as cache:
         oc = OracleCacheF(cap, tdtype)
         for b in range(cap + 1):  # wraps once
@@ -58,7 +63,8 @@ def test_softmax_scale_other_than_default(gpu_device, dtype, D, scale):
         assert np.abs(lse.cpu().numpy().astype(np.float64)[rows, heads] - want_lse).max() <= LSE_TOL[dtype] * gain
 
 
-def test_bf16_key_norm_overflow_and_zero_query(gpu_device):
+@pytest.mark.parametrize("groups,n,H", [(8, 72, 2), (2, 200, 40), (1, 72, 90)])
+def test_bf16_key_norm_overflow_and_zero_query(gpu_device, groups, n, H):
     """Finite inputs that break the norm bound: a cached key whose squared norm overflows fp32
     (elements 2^66; head 0's queries are scaled by 2^-47 so that the scores themselves stay
     within fp32's accurate range) and a query row of zeros.  The bound is inf for ordinary rows
@@ -66,7 +72,8 @@ def test_bf16_key_norm_overflow_and_zero_query(gpu_device):
     zero row gives the mean of V and the other rows of that head are one-hot on the huge key or
     ignore it.  Head 1 has no such key and stays on the fixed maximum."""
     dev = gpu_device
-    n, H, D, cap = 72, 2, 128, 2
+    D, cap = 128, 2
+    assert ifx.ifx_attention_key_groups(n, H) == groups
     with ifx.KVCache(1, H, D, cap * n, n, ifx.IFX_BF16) as cache:
         oc = OracleCacheF(cap, torch.bfloat16)
         for b in range(cap):
@@ -96,12 +103,14 @@ def test_bf16_key_norm_overflow_and_zero_query(gpu_device):
         assert np.abs(to_np_exact(out)[40, 1] - vall[:, 1].mean(0)).max() <= 2e-3
 
 
-def test_bf16_non_finite_inputs_stay_in_their_head(gpu_device):
+@pytest.mark.parametrize("groups,n,H", [(8, 136, 2), (2, 200, 40), (1, 136, 60)])
+def test_bf16_non_finite_inputs_stay_in_their_head(gpu_device, groups, n, H):
     """Values that are not finite are not detected (include/ifx.h): the call succeeds, writes all
     of out, and the heads that hold none of them are as exact as ever.  An infinite cached key, a
     NaN in the current block's V and a NaN query, each in head 0; head 1 must match the oracle."""
     dev = gpu_device
-    n, H, D, cap = 136, 2, 128, 2
+    D, cap = 128, 2
+    assert ifx.ifx_attention_key_groups(n, H) == groups
     for case in ("inf cached key", "nan block v", "nan query"):
         with ifx.KVCache(1, H, D, cap * n, n, ifx.IFX_BF16) as cache:
             oc = OracleCacheF(cap, torch.bfloat16)

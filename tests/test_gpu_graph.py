@@ -14,9 +14,10 @@ from gpu_util import OracleCacheF, assert_attention_close, oracle_rows, to_np_ex
 pytestmark = pytest.mark.gpu
 
 
-def test_attention_calls_replay_from_a_graph(gpu_device):
+@pytest.mark.parametrize("H", [3, 40, 130])  # eight, two and one key groups
+def test_attention_calls_replay_from_a_graph(gpu_device, H):
     dev = gpu_device
-    L, H, D, n, cap = 2, 3, 128, 200, 3
+    L, D, n, cap = 2, 128, 200, 3
     with ifx.KVCache(L, H, D, cap * n, n, ifx.IFX_BF16) as cache:
         ocs = [OracleCacheF(cap, torch.bfloat16) for _ in range(L)]
         for b in range(cap + 1):  # the rings have wrapped

@@ -90,14 +90,21 @@ def test_bf16_peaked_logits(gpu_device):
              label="bf16 peaked")
 
 
-def test_bf16_mixed_softmax_paths_in_one_workgroup(gpu_device):
+@pytest.mark.parametrize("groups,shapes", [
+    (8, ((328, 2, 2), (200, 2, 1), (72, 2, 3), (104, 2, 4))),
+    (2, ((328, 40, 2), (200, 40, 1), (168, 43, 3), (192, 48, 1), (256, 40, 1))),
+    (1, ((328, 100, 2), (200, 150, 1), (72, 90, 3), (104, 70, 4))),
+])
+def test_bf16_mixed_softmax_paths_in_one_workgroup(gpu_device, groups, shapes):
     """Some 32-row groups of one 256-row tile get 8x larger queries: their wavefronts take the
     running-maximum path while their neighbours in the same workgroup take the bounded one; both
     share the K/V tiles and the barriers.  Key lengths with 1, 2, 3 and 0 tiles after the
-    unrolled part, with a partial last tile of one and of two 32-key halves."""
+    unrolled part, with a partial last tile of one and of two 32-key halves.  (Eight key groups have
+    one path only; the same inputs all the same.)"""
     dev = gpu_device
-    H, D = 2, 128
-    for n, resident in ((328, 2), (200, 1), (72, 3), (104, 4)):
+    D = 128
+    for n, H, resident in shapes:
+        assert ifx.ifx_attention_key_groups(n, H) == groups
         with ifx.KVCache(1, H, D, resident * n, n, ifx.IFX_BF16) as cache:
             oc = OracleCacheF(resident, torch.bfloat16)
             for b in range(resident):
@@ -123,15 +130,21 @@ def test_bf16_mixed_softmax_paths_in_one_workgroup(gpu_device):
             assert_attention_close(got, want, ifx.IFX_BF16, f"bf16 mixed paths n={n}", input_scale=8.0)
 
 
-def test_bf16_all_scores_far_below_the_norm_bound(gpu_device):
+@pytest.mark.parametrize("groups,shapes", [
+    (8, ((72, 2), (40, 2), (136, 2))),
+    (2, ((168, 43), (200, 40), (232, 40))),
+    (1, ((72, 90), (40, 130), (136, 60))),
+])
+def test_bf16_all_scores_far_below_the_norm_bound(gpu_device, groups, shapes):
     """Every key points away from every query: all scaled scores are about -30 in log2 units while
     the Cauchy-Schwarz bound the fast path uses as its fixed maximum is +30.  The zero-filled rows
     behind a partial last key tile would score 0, i.e. 2^30 times more than any real key, so they
     must be masked, not merely subtracted.  Keys are near-identical: the result is close to the
     mean of V, and the oracle says exactly what it is."""
     dev = gpu_device
-    H, D = 2, 128
-    for n in (72, 40, 136):  # partial last tile of one and of two 32-key halves
+    D = 128
+    for n, H in shapes:  # partial last tile of one and of two 32-key halves
+        assert ifx.ifx_attention_key_groups(n, H) == groups
         with ifx.KVCache(1, H, D, 2 * n, n, ifx.IFX_BF16) as cache:
             oc = OracleCacheF(2, torch.bfloat16)
             g = torch.Generator(device="cpu").manual_seed(n)
@@ -166,9 +179,10 @@ def test_bf16_unnormalised_inputs(gpu_device):
     run_loop(gpu_device, ifx.IFX_BF16, L=1, H=4, D=128, n=136, cap_blocks=4, blocks=5, steps=2, label="bf16 plain")
 
 
-def test_bf16_deterministic(gpu_device):
+@pytest.mark.parametrize("H", [3, 60, 100])  # eight, two and one key groups
+def test_bf16_deterministic(gpu_device, H):
     dev = gpu_device
-    n, H, D = 264, 3, 128
+    n, D = 264, 128
     with ifx.KVCache(1, H, D, 2 * n, n, ifx.IFX_BF16) as cache:
         for b in range(2):
             q, k, v = synth.draw_qkv(5, b, 0, 0, n, H, D, torch.bfloat16, dev, True)
