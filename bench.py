@@ -63,7 +63,7 @@ WORKLOADS["wan1.3b_layer_37k"] = (30, 12, 128, 4680, 7)  # steady state of the 7
 # the fp32 correctness configuration (2 heads x 64, blocks of 256, key length 1024): a latency figure, not a throughput one
 WORKLOADS["fp32_2x64_1k"] = (1, 2, 64, 256, 3)
 F32_WORKLOADS = {"fp32_2x64_1k"}
-PEAK_F32_VECTOR_TFLOPS = 157.3  # MI355X fp32 vector, published
+PEAK_F32_MATRIX_TFLOPS = 157.3  # MI355X fp32 matrix, published
 EXP2_PEAK_PER_S = 256 * 4 * 8 * 2.4e9  # transcendental issue: half the VALU rate (16 lanes per cycle and SIMD)
 LOOP_WORKLOADS = {"wan1.3b_generate_7x4x30": (30, 12, 128, 4680, 7, 7, 4)}
 
@@ -306,7 +306,7 @@ def main():
     fp8 = args.cache_dtype == "fp8" and not f32
     if fp8:
         idtype = ifx.IFX_FP8_E4M3
-    peak = PEAK_F32_VECTOR_TFLOPS if f32 else PEAK_BF16_TFLOPS
+    peak = PEAK_F32_MATRIX_TFLOPS if f32 else PEAK_BF16_TFLOPS
     C = (cap if ranges is None else sum(c for _, c in ranges)) * n
     Lk = C + n
     cache = ifx.KVCache(L, H, D, cap * n, n, idtype, reserve_tokens=2 * cap * n if args.reserve else None)
@@ -478,7 +478,7 @@ def main():
                         f"{'; cache kept as fp8 (E4M3) codes' if fp8 else ''}",
             "heads": H, "head_dim": D, "block_tokens": n, "cached_tokens": C, "key_len": Lk,
         },
-        ("pct_fp32_vector_peak" if f32 else "pct_bf16_mfma_peak"): 100.0 * tflops / peak,
+        ("pct_fp32_mfma_peak" if f32 else "pct_bf16_mfma_peak"): 100.0 * tflops / peak,
         "attention_call_ms": kern_ms,
         "ms_per_denoise_step_30_layers": denoise_step_ms,
         "ms_per_step_with_kernel_events": (t3 - t2) * 1e3 / args.steps,
@@ -487,7 +487,7 @@ def main():
                   "ifx_block_attention call (one kernel launch) and each commit enqueues; ms_per_denoise_step_30_layers: "
                   "30 attention calls in a row between two events, measured",
         "roofline": {
-            "bound": "alu" if f32 else "mfma",
+            "bound": "mfma",
             "kernel": "attn_f32_kernel" if f32 else "attn_bf16_kernel",
             "achieved": kern_tflops,
             "peak": peak,

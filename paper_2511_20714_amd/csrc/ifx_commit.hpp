@@ -215,9 +215,9 @@ __device__ __forceinline__ void v_to_granules_body(int bid, int nblocks, unsigne
 
 // What one layer's share of a commit launch needs: the caller's block and where it goes.
 struct commit_layer {
-    const void *k_src, *v_src;  // [n, H, 128] bf16
+    const void *k_src, *v_src;  // [n, H, 128] bf16, or [n, H, head_dim] fp32
     void *k_dst, *v_dst;        // the layer's K region and V region
-    uint32_t *knorm;            // the layer's key-norm table [H][cap_blocks][parts]
+    uint32_t *knorm;            // the layer's key-norm table [H][cap_blocks][parts]; nullptr for an fp32 cache
     int64_t tok0;               // first token of the slot
     int slot;
 };
