@@ -5,7 +5,8 @@
 // block; softmax over that whole key set; no other mask.
 //
 // Shape of the computation
-//   Bound by the fp32 matrix rate (64 flop per cycle and SIMD).  A workgroup owns 16 query rows of a
+//   Bound by the fp32 matrix rate (64 flop per cycle and SIMD; the pipes are 64 % busy on a large call),
+//   and by the chain inside a wavefront where rows are few.  A workgroup owns 16 query rows of a
 //   head; its 4 or 8 wavefronts deal the keys among themselves in subtiles of 16 (wavefront w takes
 //   subtiles w, w + S, ...) and their partial results are combined through LDS at the end.  So even
 //   the 512 rows of a 256-token block with 2 heads are 32 workgroups of 8 busy wavefronts.  Both
@@ -29,8 +30,10 @@
 // Measured (1560 rows, 12 heads x 128, 3120 keys): 291 us = 103 TFLOP/s, where the library's plain
 // fp32 matrix product reaches 154 on the same card; 1840 us with fp32 FMA from LDS tiles.  With K
 // straight from memory 393 us; with 32 rows per wavefront (half the bytes per flop, but fewer and
-// larger workgroups) 390 us.  256 rows, 2 heads x 64, 1024 keys, and the block's commit: 18.4 us, of
-// which 14 are attention (118.6 us with 32-row workgroups that do not deal the keys out).
+// larger workgroups) 390 us.  256 rows, 2 heads x 64, 1024 keys: 16.1 us, 18.5 with the block's commit
+// (118 with 32-row workgroups that do not deal the keys out).  Of the 16, the matrix pipes of the 32
+// CUs in use are busy for 8 (28 % of the launch as the counters see it); the rest is the launch and a
+// wavefront's serial chain of scores, maximum and exponentials, eight times.
 #pragma once
 #include <cfloat>
 
@@ -53,8 +56,10 @@ struct attn_f32_args {
 };
 
 // Wavefronts per workgroup.  Up to one workgroup per CU: 8, two per SIMD.  Beyond that 4: three
-// workgroups then share a CU, and one's start and end lie under the others' loops (1176
-// workgroups of head_dim 128: 296 us with 4, 317 with 8).
+// workgroups then share a CU, and one's start and end lie under the others' loops.  Measured with 4
+// and 8 (us), head_dim 128: 264 workgroups 47.0, 50.6; 520: 121, 132; 756: 119, 132; 900: 186, 202; 1176:
+// 290, 317; 1600: 407, 451.  head_dim 64: 264 workgroups 51.7, 48.9; 1008: 128.9, 128.2; head_dim 40: 300
+// workgroups 31.8, 30.4; 1600: 226, 229 (shorter rows leave more to hide; up to 6 % lost there just past 256).
 inline int attn_f32_waves(int64_t workgroups) { return workgroups <= 256 ? 8 : 4; }
 
 // LDS: each wavefront's K subtile during the loop; the partial results take its place afterwards.
