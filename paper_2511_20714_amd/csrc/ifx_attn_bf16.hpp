@@ -193,7 +193,7 @@ struct src_block {
 // through LDS at the end.  1560 rows of 12 heads are 84 workgroups of 256 rows, and 156 of 128:
 // 174 -> 107 us against 10920 keys of two layers in turn (0.62 us per tile, half of a whole tile's 0.97
 // at best; the rest is the second barrier and the doubled copies; matrix pipes 63 % busy on the 156
-// CUs in use, LDS 32 %), 115 with 30 layers in turn, whose keys come from memory.  fp8 cache 198 -> 127
+// CUs in use, LDS 32 %), 114 with 30 layers in turn, whose keys come from memory.  fp8 cache 198 -> 127
 // (matrix pipes 50 %, LDS 49 %, a quarter of it bank conflicts of the widened tiles' stores).  The tiles, their copies and the ring are
 // those of GROUPS == 1; a tile is one step per wavefront instead of two, so K is copied five tiles
 // ahead and V three (K operands are in registers two tiles before their V is needed).  The two

@@ -23,7 +23,7 @@
 //   Measured (5 heads x 1560 rows, 10920 keys): 64 us = 1.5 us per step of a wavefront's 43, against 176
 //   with one key group; fp8 cache 60 us.  Counters: matrix pipes 30 % busy, VALU 34 %, LDS 10 %, no bank
 //   conflicts, 1.40 GB read from the L2s (22 TB/s); wavefronts spend 24 % of their cycles at wait counts,
-//   32 % ready but not issued.  No unit is full: a wavefront has one subtile's loads in flight and
+//   32 % waiting to issue.  No unit is full: a wavefront has one subtile's loads in flight and
 //   its softmax between two products, and two wavefronts per SIMD do not cover that.
 //   264 rows, 2 heads, 792 keys: 10 us, four such steps and the launch (21 with one group).
 #pragma once
