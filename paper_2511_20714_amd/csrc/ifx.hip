@@ -143,7 +143,11 @@ void (*bf16_kernel(bool table, bool fp8, int groups))(const ifx::attn_bf16_args)
                  : fp8 ? ifx::attn_bf16_kernel<false, true> : ifx::attn_bf16_kernel<false, false>;
 }
 
-void (*few_kernel(bool fp8))(const ifx::attn_few_args) { return fp8 ? ifx::attn_few_kernel<true> : ifx::attn_few_kernel<false>; }
+void (*few_kernel(bool table, bool fp8))(const ifx::attn_few_args)
+{
+    return table ? fp8 ? ifx::attn_few_kernel<true, true> : ifx::attn_few_kernel<false, true>
+                 : fp8 ? ifx::attn_few_kernel<true, false> : ifx::attn_few_kernel<false, false>;
+}
 
 // One timing sample (a pair of HIP events around what a call enqueues), taken only while
 // profiling is on and the stream is not being captured (an event recorded into a graph has no
@@ -500,14 +504,12 @@ int ifx_kv_cache_configure(ifx_kv_cache *c, int64_t block_tokens, int dtype, flo
     if (e == hipSuccess && dtype != IFX_F32) {  // the instances this cache's calls will run
         const int groups = ifx::attn_groups_for((int)block_tokens, c->heads);
         const bool fp8 = dtype == IFX_FP8_E4M3;
-        if (groups == 8) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(few_kernel(fp8)), hipFuncAttributeMaxDynamicSharedMemorySize, ifx::FEW_LDS_BYTES);
-        } else {
-            for (const bool table : {false, true})
-                if (e == hipSuccess)
-                    e = hipFuncSetAttribute(reinterpret_cast<const void *>(bf16_kernel(table, fp8, groups)),
-                                            hipFuncAttributeMaxDynamicSharedMemorySize, ifx::BF_LDS_BYTES);
-        }
+        for (const bool table : {false, true})
+            if (e == hipSuccess)
+                e = groups == 8 ? hipFuncSetAttribute(reinterpret_cast<const void *>(few_kernel(table, fp8)),
+                                                      hipFuncAttributeMaxDynamicSharedMemorySize, ifx::FEW_LDS_BYTES)
+                                : hipFuncSetAttribute(reinterpret_cast<const void *>(bf16_kernel(table, fp8, groups)),
+                                                      hipFuncAttributeMaxDynamicSharedMemorySize, ifx::BF_LDS_BYTES);
     }
     bool host_ok = e == hipSuccess;
     if (host_ok) {
@@ -814,7 +816,7 @@ static int attention_impl(ifx_kv_cache *c, int layer, const void *q, const void 
         a.scale_log2 = c->scale * 1.4426950408889634f;
         a.tiles = ifx::row_tiles_for(n, H, ifx::FEW_ROWS);
         a.blocks = table;
-        hipLaunchKernelGGL(few_kernel(c->dtype == IFX_FP8_E4M3), dim3((unsigned)(8 * a.tiles.per_xcd)), dim3(64 * ifx::FEW_WAVES), ifx::FEW_LDS_BYTES, s, a);
+        hipLaunchKernelGGL(few_kernel(use_table, c->dtype == IFX_FP8_E4M3), dim3((unsigned)(8 * a.tiles.per_xcd)), dim3(64 * ifx::FEW_WAVES), ifx::FEW_LDS_BYTES, s, a);
     } else if (c->mfma()) {
         ifx::attn_bf16_args a;
         a.q = static_cast<const __bf16 *>(q);

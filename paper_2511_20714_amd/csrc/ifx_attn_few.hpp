@@ -53,7 +53,8 @@ struct attn_few_args {
     ifx_key_blocks blocks;
 };
 
-template <bool FP8>
+// TABLE: the cached keys are the blocks of a selection in a caller-given order.
+template <bool FP8, bool TABLE>
 __global__ __launch_bounds__(64 * FEW_WAVES, 1) void attn_few_kernel(const attn_few_args a)
 {
     constexpr int KEYB = FP8 ? BF_D : BF_D * 2;  // bytes of a cached key row, and of a key's share of its V granule
@@ -70,38 +71,14 @@ __global__ __launch_bounds__(64 * FEW_WAVES, 1) void attn_few_kernel(const attn_
     const float c2 = a.scale_log2;
     unsigned char *const ktile = lds + wave * FEW_WAVE_LDS, *const vtile = ktile + FEW_WAVE_LDS / 2;
 
-    // A subtile is up to 32 keys of one run of rows: of the cached tokens [0, C), of one block of a
-    // selection, or of the current block.  Blocks are multiples of 8 tokens, so a run starts and ends
-    // on a V granule.  It is read through a buffer descriptor that ends with its last row: rows behind
-    // that read as zero, touch no memory and are masked.
-    const bool listed = a.blocks.magic != 0;
-    const int seg_keys = listed ? n : a.C;
-    const int seg_subs = (seg_keys + 31) >> 5;
-    const int cached_subs = listed ? a.blocks.count * seg_subs : seg_subs;
+    // A subtile is 32 consecutive keys of the cached ones, or of the current block (fewer at the end of
+    // either).  Without a block table the cached keys are one run of rows, as the block's are: a subtile
+    // is read through a buffer descriptor that ends with its last row; rows behind that read as zero,
+    // touch no memory and are masked.
+    const int cached_keys = TABLE ? a.blocks.count * n : a.C;
+    const int cached_subs = (cached_keys + 31) >> 5;
     const int subs = cached_subs + ((a.nb + 31) >> 5);
-    int tab = 0;  // the first 64 entries of a selection, one per lane: a lookup is a lane read
-    auto first_of = [&](int e) IFX_INLINE -> int {
-        if (a.blocks.list != nullptr) return a.blocks.list[e];
-        return a.blocks.first[e];
-    };
-    if (listed && lane < a.blocks.count) tab = first_of(lane);
-    struct run {
-        int first, keys;  // first token (of the head's region, or of the block), keys from there to the run's end
-        bool cached;
-    };
-    auto run_of = [&](int sub) IFX_INLINE -> run {
-        if (sub < cached_subs) {
-            int e = 0, first = 0;
-            if (listed) {
-                e = sub / seg_subs;
-                first = e < 64 ? __builtin_amdgcn_readlane(tab, e) : __builtin_amdgcn_readfirstlane(first_of(e));
-            }
-            const int j = 32 * (sub - e * seg_subs);
-            return {first + j, seg_keys - j, true};
-        }
-        const int j = 32 * (sub - cached_subs);
-        return {j, a.nb - j, false};
-    };
+    auto keys_from = [&](int sub) IFX_INLINE -> int { return sub < cached_subs ? cached_keys - 32 * sub : a.nb - 32 * (sub - cached_subs); };
     auto rsrc_at = [&](uintptr_t u, int bytes) IFX_INLINE -> __amdgpu_buffer_rsrc_t {
         const uintptr_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
         return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(hi << 32 | lo), 0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
@@ -111,19 +88,70 @@ __global__ __launch_bounds__(64 * FEW_WAVES, 1) void attn_few_kernel(const attn_
     const uintptr_t kb = (uintptr_t)a.kb + (uintptr_t)head * (BF_D * 2), vb = (uintptr_t)a.vb + (uintptr_t)head * (BF_D * 2);
     const int pitch = H * (BF_D * 2);
     const int l16 = lane & 15, g = lane >> 4;
-    // K: row r (256 bytes), 16-byte chunk c at place c ^ (r % 16); codes: 128-byte rows, place c ^ (r % 8)
-    auto copy_k = [&](int sub) IFX_INLINE {
-        const run r = run_of(sub);
-        const int rows = r.keys < 32 ? r.keys : 32;
-        if (FP8 && r.cached) {
-            const __amdgpu_buffer_rsrc_t rs = rsrc_at(kc + (uintptr_t)r.first * KEYB, rows * KEYB);
-            const int at = (lane >> 3) * KEYB + (((lane & 7) ^ (lane >> 3)) << 4);
+
+    // With a table a subtile may begin and end inside blocks and hold several (a subtile per block left
+    // 8-token blocks with three quarters of every product empty: 60 listed ones, 64 heads: 15.7 us, now 8.5;
+    // 13.0 with one key group).
+    // Blocks are multiples of 8 tokens, so each of its four granules lies in one: four scalar byte
+    // offsets into the head's regions, 2^30 past the last key (beyond any region, reads as zero).
+    // 64 entries of the list from tab_first on are kept one per lane, a lookup is a lane read; a wavefront
+    // walks its subtiles in order, so the 64 move along a longer list.
+    struct granules {
+        int at[4];
+    };
+    int tab = 0, tab_first = 0;
+    auto load_entries = [&](int e) IFX_INLINE {
+        tab_first = e;
+        if (e + lane < a.blocks.count) {  // (two plain indexed reads, see ifx_attn_bf16.hpp)
+            if (a.blocks.list != nullptr)
+                tab = a.blocks.list[e + lane];
+            else
+                tab = a.blocks.first[e + lane];
+        }
+    };
+    if constexpr (TABLE) load_entries(0);
+    const int block_granules = n >> 3;
+    auto granules_of = [&](int sub) IFX_INLINE -> granules {
+        granules r = {};
+        if constexpr (TABLE) {
+            if (sub >= cached_subs) return r;
+            int e = 4 * sub / block_granules, w = 4 * sub - e * block_granules;
+            if (e + 3 >= tab_first + 64) load_entries(e);
 #pragma unroll
-            for (int x = 0; x < COPIES; ++x) __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lptr_t)(ktile + 1024 * x), 16, at, 1024 * x, 0, 0);
+            for (int k = 0; k < 4; ++k) {
+                r.at[k] = e < a.blocks.count ? (__builtin_amdgcn_readlane(tab, e - tab_first) + 8 * w) * KEYB : 1 << 30;
+                if (++w == block_granules) {
+                    w = 0;
+                    ++e;
+                }
+            }
+        }
+        return r;
+    };
+    // K: row r (256 bytes), 16-byte chunk c at place c ^ (r % 16); codes: 128-byte rows, place c ^ (r % 8)
+    auto copy_k = [&](int sub, const granules &from) IFX_INLINE {
+        const bool cached = sub < cached_subs;
+        const int left = keys_from(sub), rows = left < 32 ? left : 32;
+        if (cached && (FP8 || TABLE)) {
+            const __amdgpu_buffer_rsrc_t rs = TABLE ? rsrc_at(kc, (int)(a.k_tokens * KEYB)) : rsrc_at(kc + (uintptr_t)(32 * sub) * KEYB, rows * KEYB);
+#pragma unroll
+            for (int x = 0; x < COPIES; ++x) {
+                // (not const: with arguments that depend on FP8 the host pass rejects the builtin's size, silently)
+                int off_v, off_s;
+                if constexpr (FP8) {
+                    off_v = (lane >> 3) * KEYB + (((lane & 7) ^ (lane >> 3)) << 4);
+                    off_s = TABLE ? from.at[x & 3] : 1024 * x;
+                } else {
+                    off_v = g * KEYB + ((l16 ^ (4 * (x & 3) + g)) << 4);
+                    off_s = from.at[x >> 1] + 1024 * (x & 1);
+                }
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lptr_t)(ktile + 1024 * x), 16, off_v, off_s, 0, 0);
+            }
             return;
         }
-        const int stride = r.cached ? BF_D * 2 : pitch;
-        const __amdgpu_buffer_rsrc_t rs = rsrc_at((r.cached ? kc : kb) + (uintptr_t)r.first * (uintptr_t)stride, (rows - 1) * stride + BF_D * 2);
+        const int stride = cached ? BF_D * 2 : pitch;
+        const uintptr_t base = cached ? kc + (uintptr_t)(32 * sub) * (BF_D * 2) : kb + (uintptr_t)(32 * (sub - cached_subs)) * (uintptr_t)pitch;
+        const __amdgpu_buffer_rsrc_t rs = rsrc_at(base, (rows - 1) * stride + BF_D * 2);
 #pragma unroll
         for (int x = 0; x < 8; ++x) {
             const int at = g * stride + ((l16 ^ (4 * (x & 3) + g)) << 4);
@@ -137,32 +165,35 @@ __global__ __launch_bounds__(64 * FEW_WAVES, 1) void attn_few_kernel(const attn_
     typedef uint32_t raw_u32x2 __attribute__((__vector_size__(8)));
     typedef typename std::conditional<FP8, raw_u32x2, raw_u32x4>::type stored_v;
     stored_v Vc[8];
-    auto load_v = [&](int sub) IFX_INLINE {
-        const run r = run_of(sub);
-        const int rows = r.keys < 32 ? r.keys : 32;
-        if (r.cached) {
-            const __amdgpu_buffer_rsrc_t rs = rsrc_at(vc + (uintptr_t)r.first * KEYB, rows * KEYB);
-            const int at = lh * (8 * KEYB) + lq * (KEYB / 16);
+    auto load_v = [&](int sub, const granules &from) IFX_INLINE {
+        const int left = keys_from(sub), rows = left < 32 ? left : 32;
+        if (sub < cached_subs) {
+            const __amdgpu_buffer_rsrc_t rs = TABLE ? rsrc_at(vc, (int)(a.v_tokens * KEYB)) : rsrc_at(vc + (uintptr_t)(32 * sub) * KEYB, rows * KEYB);
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
+            for (int t = 0; t < 2; ++t) {
+                // lanes 0 .. 31: granule 2 t, lanes 32 .. 63: the next
+                const int at = lq * (KEYB / 16) + (TABLE ? (lh ? from.at[2 * t + 1] : from.at[2 * t]) : lh * (8 * KEYB));
+                const int step = TABLE ? 0 : t * (16 * KEYB);
 #pragma unroll
                 for (int sl = 0; sl < 4; ++sl) {
                     if constexpr (FP8)
-                        Vc[t * 4 + sl] = __builtin_amdgcn_raw_buffer_load_b64(rs, at, t * (16 * KEYB) + sl * (2 * KEYB), 0);
+                        Vc[t * 4 + sl] = __builtin_amdgcn_raw_buffer_load_b64(rs, at, step + sl * (2 * KEYB), 0);
                     else
-                        Vc[t * 4 + sl] = __builtin_amdgcn_raw_buffer_load_b128(rs, at, t * (16 * KEYB) + sl * (2 * KEYB), 0);
+                        Vc[t * 4 + sl] = __builtin_amdgcn_raw_buffer_load_b128(rs, at, step + sl * (2 * KEYB), 0);
                 }
+            }
             return;
         }
-        const __amdgpu_buffer_rsrc_t rs = rsrc_at(vb + (uintptr_t)r.first * (uintptr_t)pitch, (rows - 1) * pitch + BF_D * 2);
+        const __amdgpu_buffer_rsrc_t rs = rsrc_at(vb + (uintptr_t)(32 * (sub - cached_subs)) * (uintptr_t)pitch, (rows - 1) * pitch + BF_D * 2);
         const int at = g * pitch + ((l16 ^ (g << 2)) << 4);
 #pragma unroll
         for (int x = 0; x < 8; ++x) __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lptr_t)(vtile + 1024 * x), 16, at, 4 * x * pitch, 0, 0);
     };
 
     if (wave < subs) {
-        copy_k(wave);
-        load_v(wave);
+        const granules from = granules_of(wave);
+        copy_k(wave, from);
+        load_v(wave, from);
     }
     bf16x8 Q[8];
     {
@@ -206,7 +237,7 @@ __global__ __launch_bounds__(64 * FEW_WAVES, 1) void attn_few_kernel(const attn_
     for (int sub = wave; sub < subs; sub += FEW_WAVES) {
         const int next = sub + FEW_WAVES < subs ? sub + FEW_WAVES : sub;  // (always copied: the wait counts then know what is in flight)
         const bool cached = sub < cached_subs;
-        const int keys = run_of(sub).keys;
+        const int keys = keys_from(sub);
         bf16x8 A[8];
         // K: only V's eight loads, issued behind it, may still be on their way
         __builtin_amdgcn_s_waitcnt(0x0F70 | 8);
@@ -222,7 +253,8 @@ __global__ __launch_bounds__(64 * FEW_WAVES, 1) void attn_few_kernel(const attn_
         }
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the operands are in registers, the tile is free
         __builtin_amdgcn_sched_barrier(0);
-        copy_k(next);
+        const granules from = granules_of(next);
+        copy_k(next, from);
         __builtin_amdgcn_s_setprio(1);  // (MFMAs first: 5 % faster)
         f32x16 S = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -301,7 +333,7 @@ __global__ __launch_bounds__(64 * FEW_WAVES, 1) void attn_few_kernel(const attn_
 #pragma unroll
             for (int sl = 0; sl < 4; ++sl) O[sl] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(V[t * 4 + sl], P[t], O[sl], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
-        load_v(next);
+        load_v(next, from);
 #pragma unroll
         for (int r = 0; r < 16; ++r) l_acc[r & 3] += (float)P[r >> 3][r & 7];
         if (with_lse) {

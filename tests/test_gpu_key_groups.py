@@ -18,6 +18,12 @@ CASES = [
     # eight groups (32-row workgroups): H * ceil(n / 32) <= 256
     (8, 8, 1, 2, 1, None, True),        # 16 keys: seven wavefronts without a key
     (8, 8, 3, 70, 72, list(range(69, -1, -1)), True),  # more listed blocks than a wavefront has lanes, 8 keys each
+    (8, 8, 5, 200, 203, list(range(199, -1, -1)), True),  # the entries at hand move along the list, twice and more
+    (8, 40, 3, 140, 141, list(range(0, 140, 2)) + list(range(1, 140, 2)), False),  # two subtiles per entry
+    (8, 16, 40, 5, 6, [3, 0, 4, 1], True),  # two listed blocks to a subtile
+    (8, 24, 3, 67, 67, list(range(66, 0, -1)), True),  # blocks that straddle subtiles
+    (8, 56, 3, 4, 6, [3, 1, 2], False),
+    (8, 264, 2, 70, 71, list(range(69, -1, -1)), True),
     (8, 40, 2, 3, 5, [2, 0], False),    # blocks that end 8 keys into a subtile, no current block
     (8, 72, 5, 3, 3, None, True),
     (8, 264, 28, 2, 2, None, True),     # 252 workgroups
