@@ -123,15 +123,17 @@ int grid_for(int64_t items, int per_block = 256, int max_blocks = 256 * 16)
 
 // fp32 attention: head_dim rounded up to what the kernel is instantiated for, and that instance.
 int f32_padded_dim(int D) { return (D + 31) / 32 * 32; }
-void (*f32_kernel(int D))(const ifx::attn_f32_args)
+template <bool GATHER>
+void (*f32_kernel_of(int D))(const ifx::attn_f32_args)
 {
     switch (f32_padded_dim(D)) {
-    case 32: return ifx::attn_f32_kernel<32>;
-    case 64: return ifx::attn_f32_kernel<64>;
-    case 96: return ifx::attn_f32_kernel<96>;
-    default: return ifx::attn_f32_kernel<128>;
+    case 32: return ifx::attn_f32_kernel<32, GATHER>;
+    case 64: return ifx::attn_f32_kernel<64, GATHER>;
+    case 96: return ifx::attn_f32_kernel<96, GATHER>;
+    default: return ifx::attn_f32_kernel<128, GATHER>;
     }
 }
+void (*f32_kernel(int D, bool gather))(const ifx::attn_f32_args) { return gather ? f32_kernel_of<true>(D) : f32_kernel_of<false>(D); }
 
 // bf16 attention: the instance for a block table or none, an fp8 or a bf16 cache, one or two key groups.
 void (*bf16_kernel(bool table, bool fp8, int groups))(const ifx::attn_bf16_args)
@@ -498,9 +500,10 @@ int ifx_kv_cache_configure(ifx_kv_cache *c, int64_t block_tokens, int dtype, flo
     size_t kn_bytes = 0;
     if (e == hipSuccess) e = alloc_aux(c, c->stride_blocks, parts, &c->aux, &kn_bytes);
     if (e == hipSuccess) e = hipDeviceSynchronize();
-    if (e == hipSuccess && dtype == IFX_F32)
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(f32_kernel(D)), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)ifx::attn_f32_lds_bytes(f32_padded_dim(D), 8));
+    for (const bool gather : {false, true})
+        if (e == hipSuccess && dtype == IFX_F32)
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(f32_kernel(D, gather)), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)ifx::attn_f32_lds_bytes(f32_padded_dim(D), 8));
     if (e == hipSuccess && dtype != IFX_F32) {  // the instances this cache's calls will run
         const int groups = ifx::attn_groups_for((int)block_tokens, c->heads);
         const bool fp8 = dtype == IFX_FP8_E4M3;
@@ -861,7 +864,8 @@ static int attention_impl(ifx_kv_cache *c, int layer, const void *q, const void 
         a.scale = c->scale;
         a.tiles = tiles;
         a.blocks = table;
-        hipLaunchKernelGGL(f32_kernel(D), dim3((unsigned)(8 * tiles.per_xcd)), dim3(64 * waves), ifx::attn_f32_lds_bytes(f32_padded_dim(D), waves), s, a);
+        const bool gather = use_table && n < ifx::F32_KEYS && 4 * c->k_tokens * D < ifx::GATHER_MOST;
+        hipLaunchKernelGGL(f32_kernel(D, gather), dim3((unsigned)(8 * tiles.per_xcd)), dim3(64 * waves), ifx::attn_f32_lds_bytes(f32_padded_dim(D), waves), s, a);
     }
     IFX_HIP(hipGetLastError());
     return sample.end();

@@ -44,6 +44,7 @@ namespace ifx {
 
 constexpr int F32_MAXD = 128;
 constexpr int F32_ROWS = 16;  // query rows per workgroup
+constexpr int F32_KEYS = 16;  // keys of a subtile
 
 struct attn_f32_args {
     const float *q, *kc, *vc, *kb, *vb;  // [n, H, D]; layer regions [H][cache_tokens][D]; the block's K, V [n, H, D]
@@ -68,8 +69,14 @@ inline size_t attn_f32_lds_bytes(int padded_d, int waves)
     return (size_t)waves * F32_ROWS * ((size_t)(padded_d + 4) + 2) * sizeof(float);
 }
 
-template <int DP>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) void attn_f32_kernel(const attn_f32_args a)
+// GATHER: for listed blocks shorter than a subtile.  A subtile is then 16 consecutive keys of the listed
+// ones, from several blocks, where otherwise it lies in one and holds as few keys as the block (200
+// listed blocks of one token, 4 heads x 64: 45.6 us, now 17).  Each lane works out where one of the rows lies
+// and the copies and loads fetch that from it (a lane exchange per instruction, so not the form for
+// blocks that fill subtiles); the offsets are 32 bits, so a head's region must lie below GATHER_MOST.
+constexpr int64_t GATHER_MOST = 0x7f000000;
+template <int DP, bool GATHER = false>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(GATHER ? 2 : 3))) void attn_f32_kernel(const attn_f32_args a)
 {
     static_assert(DP % 32 == 0 && DP <= F32_MAXD, "");
     constexpr int KJ = DP / 16;          // 16-byte K chunks of a lane per subtile
@@ -93,16 +100,23 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) void a
     // of a selection, or of the current block.  It is read through a buffer descriptor that starts at
     // its first row and ends with its last one (rows behind that read as zero and are masked).
     const bool listed = a.blocks.magic != 0;
-    const int seg_keys = listed ? n : C;              // keys of a cached segment
-    const int seg_subs = (seg_keys + 15) >> 4;        // its subtiles
-    const int cached_subs = listed ? a.blocks.count * seg_subs : seg_subs;
+    const int seg_keys = GATHER ? a.blocks.count * n : listed ? n : C;  // keys of a cached segment
+    const int seg_subs = (seg_keys + 15) >> 4;                          // its subtiles
+    const int cached_subs = !GATHER && listed ? a.blocks.count * seg_subs : seg_subs;
     const int subs = cached_subs + ((a.n_blk + 15) >> 4);
-    int tab = 0;  // the first 64 entries of a selection, one per lane: a lookup is a lane read
-    auto first_of = [&](int e) __attribute__((always_inline)) -> int {
-        if (a.blocks.list != nullptr) return a.blocks.list[e];
-        return a.blocks.first[e];
+    // 64 entries of a selection from tab_first on, one per lane: a lookup is a lane read.  A wavefront
+    // walks its subtiles in order, so the 64 move along a longer list.
+    int tab = 0, tab_first = 0;
+    auto load_entries = [&](int e) __attribute__((always_inline)) {
+        tab_first = e;
+        if (e + lane < a.blocks.count) {  // (two plain indexed reads, see ifx_attn_bf16.hpp)
+            if (a.blocks.list != nullptr)
+                tab = a.blocks.list[e + lane];
+            else
+                tab = a.blocks.first[e + lane];
+        }
     };
-    if (listed && lane < a.blocks.count) tab = first_of(lane);
+    if (listed) load_entries(0);
     struct run {
         int64_t at;            // element offset of the first row, in the cache region or in the block's tensor
         int stride, keys;      // elements between rows; rows
@@ -110,10 +124,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) void a
     };
     auto run_of = [&](int sub) __attribute__((always_inline)) -> run {
         if (sub < cached_subs) {
+            if constexpr (GATHER) return {(int64_t)h * a.cache_tokens * D, D, seg_keys - 16 * sub, true};  // (the region's start)
             int e = 0, first = 0;
             if (listed) {
                 e = sub / seg_subs;
-                first = e < 64 ? __builtin_amdgcn_readlane(tab, e) : __builtin_amdgcn_readfirstlane(first_of(e));
+                if (e >= tab_first + 64) load_entries(e);
+                first = __builtin_amdgcn_readlane(tab, e - tab_first);
             }
             const int j = 16 * (sub - e * seg_subs);
             return {((int64_t)h * a.cache_tokens + first + j) * D, D, seg_keys - j, true};
@@ -128,19 +144,29 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) void a
         const uintptr_t u = (r.cached ? cache : block) + 4 * (uintptr_t)r.at;
         const uintptr_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
         const int rows = r.keys < 16 ? r.keys : 16;
-        return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(hi << 32 | lo), 0,
-                                                 __builtin_amdgcn_readfirstlane(4 * ((rows - 1) * r.stride + D)), 0x00020000);
+        const int bytes = GATHER && r.cached ? (int)(4 * a.cache_tokens * D) : 4 * ((rows - 1) * r.stride + D);
+        return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(hi << 32 | lo), 0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
     };
     // K copies: LDS slot e = 64 x + lane (x = 0 .. KJ - 1; row e / CH, place e % CH) receives the row's
     // chunk place ^ z(row).  Dimensions past D are asked for behind the run's end and read as zero, like Q's
     // there (at a dimension of the row an infinite element would meet Q's zero and make the score NaN).
     constexpr int ROWS_X = 64 % CH == 0 ? 64 / CH : 0;  // whole rows per copy instruction
-    // an offset behind any run: a run is at most 16 rows of 65535 heads of 128 floats, 2^29 bytes, and this and a
-    // row's offset added stay below 2^32
-    constexpr int PAST_RUN = 0x7f000000;
+    // an offset behind any run or region: a run is at most 16 rows of 65535 heads of 128 floats, 2^29 bytes, and
+    // this and a row's offset added stay below 2^32
+    constexpr int PAST_RUN = (int)GATHER_MOST;
+    // GATHER: the byte offset in the region of key i16 of subtile `sub` (other forms: unused)
+    const int per_n = GATHER ? 65536 / n + 1 : 0;  // x * per_n >> 16 is x / n for the x < 32 and n < 16 below
+    auto row_offset = [&](int sub) __attribute__((always_inline)) -> int {
+        if (!GATHER || sub >= cached_subs) return 0;
+        const int e0 = 16 * sub / n;
+        if (e0 + 15 >= tab_first + 64) load_entries(e0);
+        const int x = 16 * sub - e0 * n + i16, q = (x * per_n) >> 16, e = e0 + q;
+        const int first = __shfl(tab, e - tab_first);
+        return e < a.blocks.count ? 4 * D * (first + x - q * n) : PAST_RUN;
+    };
     auto z = [](int r) { return CH % 16 == 0 ? r : r >> 1; };
     float *const ktile = smem + wave * (F32_ROWS * DP);
-    auto copy_k = [&](int sub) __attribute__((always_inline)) {
+    auto copy_k = [&](int sub, int row_off) __attribute__((always_inline)) {
         const run r = run_of(sub);
         const __amdgpu_buffer_rsrc_t rs = rsrc_of(r, kc, kb);
 #pragma unroll
@@ -148,6 +174,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) void a
             const int e = 64 * x + lane, row = e / CH, d = 4 * ((e % CH) ^ z(row));
             // (not const: with arguments that depend on DP the host pass rejects the builtin's size, silently)
             int off_v = d < D ? 4 * ((ROWS_X ? lane / CH : row) * r.stride + d) : PAST_RUN, off_s = 4 * (ROWS_X * x) * r.stride;
+            if (GATHER && r.cached) {
+                const int off = __shfl(row_off, row);
+                off_v = d < D ? off + 4 * d : PAST_RUN;
+                off_s = 0;
+            }
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(ktile + 256 * x), 16, off_v, off_s, 0, 0);
         }
     };
@@ -163,23 +194,29 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) void a
 #pragma unroll
     for (int s = 0; s < QUADS; ++s) dv[s] = 64 * s + 4 * i16 < D ? 64 * s + 4 * i16 : 0;
     const int dv2 = 64 * QUADS + 2 * i16 < D ? 64 * QUADS + 2 * i16 : 0;
-    auto load_v = [&](int sub) __attribute__((always_inline)) -> int {  // returns the subtile's keys
+    auto load_v = [&](int sub, int row_off) __attribute__((always_inline)) -> int {  // returns the subtile's keys
         typedef uint32_t raw_u32x4 __attribute__((__vector_size__(16)));
         typedef uint32_t raw_u32x2 __attribute__((__vector_size__(8)));
         const run u = run_of(sub);
         const __amdgpu_buffer_rsrc_t rs = rsrc_of(u, vc, vb);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
+            int off = 4 * (4 * g * u.stride), off_s = 4 * r * u.stride;
+            if (GATHER && u.cached) {
+                off = __shfl(row_off, 4 * g + r);
+                off_s = 0;
+            }
 #pragma unroll
             for (int s = 0; s < QUADS; ++s)
-                V[r][s] = __builtin_bit_cast(f32x4, (raw_u32x4)__builtin_amdgcn_raw_buffer_load_b128(rs, 4 * (4 * g * u.stride + dv[s]), 4 * r * u.stride, 0));
+                V[r][s] = __builtin_bit_cast(f32x4, (raw_u32x4)__builtin_amdgcn_raw_buffer_load_b128(rs, off + 4 * dv[s], off_s, 0));
             if constexpr (PAIR)
-                V2[r] = __builtin_bit_cast(f32x2, (raw_u32x2)__builtin_amdgcn_raw_buffer_load_b64(rs, 4 * (4 * g * u.stride + dv2), 4 * r * u.stride, 0));
+                V2[r] = __builtin_bit_cast(f32x2, (raw_u32x2)__builtin_amdgcn_raw_buffer_load_b64(rs, off + 4 * dv2, off_s, 0));
         }
         return u.keys;
     };
 
-    if (wave < subs) copy_k(wave);
+    int row_off = row_offset(wave);
+    if (wave < subs) copy_k(wave, row_off);
     f32x4 Q[KJ];
     {
         const int i = row0 + i16;
@@ -204,10 +241,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) void a
         f32x4 K[KJ];
 #pragma unroll
         for (int j = 0; j < KJ; ++j) K[j] = *reinterpret_cast<const f32x4 *>(kread[j % Z_J] + 16 * (j - j % Z_J));
-        const int keys = load_v(sub);
+        const int keys = load_v(sub, row_off);
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this subtile's operands are in registers, the tile is free
         __builtin_amdgcn_sched_barrier(0);
-        copy_k(sub + S < subs ? sub + S : sub);  // (always: the wait counts then know what is in flight)
+        const int next = sub + S < subs ? sub + S : sub;  // (always copied: the wait counts then know what is in flight)
+        row_off = row_offset(next);
+        copy_k(next, row_off);
         f32x4 s = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int c = 0; c < KJ; ++c)

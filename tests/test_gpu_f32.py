@@ -20,6 +20,15 @@ pytestmark = pytest.mark.gpu
     (33, 5, 96, 2, 2, None, True),
     (129, 3, 128, 2, 3, [1], True),
     (8, 1, 128, 70, 72, list(range(69, -1, -1)), True),   # more listed blocks than a wavefront has lanes
+    (1, 4, 8, 200, 203, list(range(199, -1, -1)), True),  # one key per entry and subtile: the entries at hand move along the list
+    (16, 1, 40, 130, 131, list(range(0, 130, 2)) + list(range(1, 130, 2)), False),
+    # listed blocks shorter than a subtile: rows gathered from several blocks, at every head_dim the kernel is built for
+    (3, 2, 24, 150, 151, list(range(0, 150, 2)) + list(range(1, 150, 2)), True),
+    (5, 3, 64, 66, 70, list(range(65, -1, -1)), False),
+    (7, 2, 96, 9, 10, [8, 0, 3], True),
+    (15, 2, 128, 70, 71, list(range(1, 70)), True),
+    (13, 300, 72, 3, 5, [2, 0], True),      # 300 workgroups: 4 wavefronts each
+    (1, 1, 128, 2, 3, [1], True),
     (1370, 3, 128, 1, 1, None, True),   # 258 workgroups: the first size with 4 wavefronts each
     (1366, 3, 32, 1, 0, None, True),    # 258 of the smallest head_dim, no cached keys
 ])
