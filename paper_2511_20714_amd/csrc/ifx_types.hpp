@@ -27,7 +27,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // magic = floor(2^32 / block_tokens) + 1, so that the high word of j * magic is j / block_tokens
 // (the host checks this for every j that kernel can form).  It keeps the entries it is working on in
 // one register, a lane per entry, with one lane left for "past the end".  The kernels that deal the
-// keys out in subtiles divide instead, and only ask whether magic is 0.
+// keys out in subtiles divide instead; to the fp32 one magic only says whether there is a selection.
 constexpr int IFX_MAX_KEY_BLOCKS = 63;
 struct ifx_key_blocks {
     int first[IFX_MAX_KEY_BLOCKS + 1];
