@@ -360,6 +360,8 @@ int ifx_ring_grow(ifx_ring *ring, int64_t new_capacity_blocks, int in_place);
  * all; more: those of heads *whole_heads and up go to that many, and a second launch puts their
  * results together.  *rows: the most query rows of a workgroup (either pointer may be NULL).
  * ifx_attention_f32_key_parts: the same of an fp32 call over `keys` keys, all heads (listed != 0: of a selection).
+ * ifx_attention_area_bytes: device memory that a cache of such blocks with room for `capacity_blocks` of them holds for
+ * the partial results of one stream's calls: as much as the largest of them takes.
  * ifx_attention_group_grid: workgroups of one attention launch over blocks of `block_tokens` tokens
  * and `heads` heads with `groups` (1, 2, 8) key groups; IFX_ERR_INVALID_ARG (< 0) for anything else.
  * ifx_attention_group_item: what workgroup `workgroup` of that launch does, written to item[0..4]:
@@ -370,6 +372,7 @@ int ifx_ring_grow(ifx_ring *ring, int64_t new_capacity_blocks, int in_place);
 int ifx_attention_key_groups(int block_tokens, int heads);
 int ifx_attention_key_parts(int block_tokens, int heads, int64_t cached_tokens, int with_block, int *whole_heads, int *rows);
 int ifx_attention_f32_key_parts(int block_tokens, int heads, int head_dim, int64_t keys, int listed, int *rows);
+int64_t ifx_attention_area_bytes(int block_tokens, int heads, int head_dim, int dtype, int64_t capacity_blocks);
 int ifx_attention_group_grid(int block_tokens, int heads, int groups);
 int ifx_attention_group_item(int block_tokens, int heads, int groups, int workgroup, int *item);
 int ifx_attention_launch_grid(int block_tokens, int heads);

@@ -68,6 +68,7 @@ _SIGS = {
     "ifx_attention_key_groups": (_int, [_int, _int]),
     "ifx_attention_key_parts": (_int, [_int, _int, _i64, _int, ctypes.POINTER(_int), ctypes.POINTER(_int)]),
     "ifx_attention_f32_key_parts": (_int, [_int, _int, _int, _i64, _int, ctypes.POINTER(_int)]),
+    "ifx_attention_area_bytes": (_i64, [_int, _int, _int, _int, _i64]),
     "ifx_attention_group_grid": (_int, [_int, _int, _int]),
     "ifx_attention_group_item": (_int, [_int, _int, _int, _int, ctypes.POINTER(_int)]),
     "ifx_attention_launch_grid": (_int, [_int, _int]),
@@ -303,6 +304,11 @@ def ifx_attention_f32_key_parts(block_tokens: int, heads: int, head_dim: int, ke
     rows = _int()
     parts = _check(lib().ifx_attention_f32_key_parts(block_tokens, heads, head_dim, keys, int(bool(listed)), ctypes.byref(rows)))
     return parts, rows.value
+
+
+def ifx_attention_area_bytes(block_tokens: int, heads: int, head_dim: int, dtype: int, capacity_blocks: int) -> int:
+    """bytes that a cache holds for the partial results of one stream's calls"""
+    return _check(lib().ifx_attention_area_bytes(block_tokens, heads, head_dim, dtype, capacity_blocks))
 
 
 def ifx_attention_group_grid(block_tokens: int, heads: int, groups: int) -> int:

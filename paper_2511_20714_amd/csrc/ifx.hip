@@ -450,8 +450,7 @@ static void release_memory(ifx_kv_cache *c)
 static size_t split_bytes_for(int n, int heads, int head_dim, bool mfma, int64_t blocks)
 {
     if (mfma) return (size_t)ifx::attn_split_units(n, heads, attn_tiles(blocks * n, n)) * ifx::SPLIT_UNIT_BYTES;
-    const int64_t tiles = (n + ifx::F32_ROWS - 1) / ifx::F32_ROWS;
-    return (size_t)ifx::attn_f32_split_rows(n, heads, head_dim, (blocks + 1) * tiles) * ifx::attn_f32_split_row_bytes(f32_padded_dim(head_dim));
+    return (size_t)ifx::attn_f32_split_rows(n, heads, head_dim, blocks) * ifx::attn_f32_split_row_bytes(f32_padded_dim(head_dim));
 }
 
 // Side tables for `blocks` slots per layer (key norms for bf16, block lists), allocated and zeroed, and behind them the
@@ -1326,6 +1325,15 @@ int ifx_attention_f32_key_parts(int block_tokens, int heads, int head_dim, int64
     const ifx::f32_plan p = ifx::attn_f32_plan(block_tokens, heads, head_dim, (keys + 15) / 16, listed != 0);
     if (rows) *rows = p.large ? ifx::F32L_ROWS : ifx::F32_ROWS;
     return p.parts;
+}
+
+int64_t ifx_attention_area_bytes(int block_tokens, int heads, int head_dim, int dtype, int64_t capacity_blocks)
+{
+    const bool mfma = dtype == IFX_BF16 || dtype == IFX_FP8_E4M3;
+    if (block_tokens < 1 || heads < 1 || head_dim < 1 || head_dim > ifx::F32_MAXD || (mfma && head_dim != ifx::BF_D) || (!mfma && dtype != IFX_F32) ||
+        capacity_blocks < 0 || capacity_blocks > ((int64_t)1 << 30) / block_tokens)
+        return fail(IFX_ERR_INVALID_ARG, "area_bytes: block_tokens and heads must be positive, head_dim and dtype a cache's, at most 2^30 tokens");
+    return (int64_t)split_bytes_for(block_tokens, heads, head_dim, mfma, capacity_blocks);
 }
 
 int ifx_attention_group_grid(int block_tokens, int heads, int groups)

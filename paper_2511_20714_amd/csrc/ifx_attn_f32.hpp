@@ -127,16 +127,33 @@ inline f32_plan attn_f32_plan(int n, int heads, int head_dim, int64_t subs, bool
     if (parts > 1) large += 4.f + 0.5e-6f * (float)(row_tiles * 16 * parts) * (4.f * padded_d + 8.f);
     return large < 0.92f * us ? f32_plan{true, (int)parts} : small;
 }
-// Rows of partial results that calls over up to `subs` subtiles may leave, and their size.
-inline int64_t attn_f32_split_rows(int n, int heads, int head_dim, int64_t subs)
+// The most parts that attn_f32_plan deals keys of any number to.
+inline int attn_f32_most_parts(int n, int heads)
 {
-    int most = 1;
-    for (int64_t s = 8; s <= subs; s += 1 + s / 64)
-        for (const bool listed : {false, true}) {
-            const int parts = attn_f32_plan(n, heads, head_dim, s, listed).parts;
-            if (parts > most) most = parts;
+    const int64_t row_tiles = (int64_t)((n + 15) / 16) * heads, workgroups = (int64_t)((n + 255) / 256) * heads;
+    int most = workgroups <= 128 ? (int)(256 / workgroups) : 1;
+    if (row_tiles <= 128 && 256 / row_tiles > most) most = (int)(256 / row_tiles);
+    const int dealt = row_tiles <= 480 ? 5 : row_tiles <= 700 ? 3 : 1;
+    return dealt > most ? dealt : most;
+}
+// Rows of partial results that calls over up to `blocks` cached blocks may leave: of every number of them, with the current
+// block and without (a plan's parts rise and fall with the keys); beyond the first thousands the most there can be.
+inline int64_t attn_f32_split_rows(int n, int heads, int head_dim, int64_t blocks)
+{
+    const int limit = attn_f32_most_parts(n, heads);
+    const int64_t tiles = (n + 15) / 16;
+    constexpr int64_t EACH = 4096;
+    int most = blocks > EACH ? limit : 1;
+    for (int64_t i = 0; i <= blocks && most < limit; ++i)
+        for (const int64_t block : {(int64_t)0, tiles}) {
+            // every block in slot order, or listed: those of 16 tokens and more in subtiles of their own, shorter ones either way
+            const int64_t dense = (i * n + 15) / 16 + block, own = i * tiles + block;
+            const int parts[3] = {attn_f32_plan(n, heads, head_dim, dense, false).parts, attn_f32_plan(n, heads, head_dim, own, true).parts,
+                                  n < 16 ? attn_f32_plan(n, heads, head_dim, dense, true).parts : 1};
+            for (const int p : parts)
+                if (p > most) most = p;
         }
-    return most > 1 ? (int64_t)((n + 15) / 16) * heads * most * F32_ROWS : 0;
+    return most > 1 ? tiles * heads * most * F32_ROWS : 0;
 }
 inline size_t attn_f32_split_row_bytes(int padded_d) { return (size_t)padded_d * 4 + 8; }
 

@@ -319,6 +319,42 @@ def test_f32_key_parts_where_they_pay(n, heads, head_dim, keys, listed, parts, r
             ifx.ifx_attention_f32_key_parts(*bad)
 
 
+@pytest.mark.parametrize("head_dim", [8, 64, 72, 128])
+def test_f32_parts_fit_their_memory(head_dim):
+    """At every number of resident blocks, over all of them or listed ones, with the block and without: the parts of an fp32
+    call leave at most as many rows (of head_dim rounded up to 32 fp32 numbers, a maximum and a sum) as a stream's memory holds."""
+    row_bytes = 4 * ((head_dim + 31) // 32 * 32) + 8
+    in_parts = 0
+    shapes = [(n, heads, cap) for n in (*range(64, 1601, 56), 1080, 1568) for heads in range(1, 17) for cap in (1, 3, 4)]
+    shapes += [(816, 2, 4), (240, 13, 8), (472, 6, 2), (464, 2, 15), (512, 6, 4), (544, 5, 3), (7, 3, 300), (5, 1, 40), (1, 12, 700), (16, 2, 64), (17, 2, 150)]
+    for n, heads, cap in shapes:
+        tiles = (n + 15) // 16
+        holds = ifx.ifx_attention_area_bytes(n, heads, head_dim, ifx.IFX_F32, cap)
+        for resident in (range(cap + 1) if cap < 100 else (0, 1, 2, 17, cap // 2, cap - 1, cap)):
+            for block_subs in (0, tiles):
+                dense, own = (resident * n + 15) // 16 + block_subs, resident * tiles + block_subs
+                for subs, listed in ((dense, False), (own, True), (dense if n < 16 else own, True)):
+                    parts, _ = ifx.ifx_attention_f32_key_parts(n, heads, head_dim, 16 * subs, listed)
+                    if parts > 1:
+                        in_parts += 1
+                        assert parts * heads * tiles * 16 * row_bytes <= holds, (n, heads, cap, resident, block_subs, listed, parts)
+    assert in_parts > 1000
+
+
+@pytest.mark.parametrize("n,heads,cap", [(264, 2, 7), (1560, 1, 6), (1560, 12, 6), (4680, 14, 3), (10800, 7, 2), (200, 40, 6), (8, 3, 40)])
+def test_parts_fit_their_memory(n, heads, cap):
+    """The same of bf16 and fp8 calls: units of 32 rows, 16 KiB and 16 bytes a row."""
+    holds = ifx.ifx_attention_area_bytes(n, heads, 128, ifx.IFX_BF16, cap)
+    assert holds == ifx.ifx_attention_area_bytes(n, heads, 128, ifx.IFX_FP8_E4M3, cap)
+    for resident in range(cap + 1):
+        for with_block in (False, True):
+            parts, whole, _ = ifx.ifx_attention_key_parts(n, heads, resident * n, with_block)
+            assert parts == 1 or parts * (heads - whole) * ((n + 31) // 32) * (16384 + 512) <= holds
+    for bad in ((0, 1, 128, 1, 1), (8, 0, 128, 1, 1), (8, 1, 64, 1, 1), (8, 1, 128, 7, 1), (8, 1, 128, 1, -1), (8, 1, 136, 0, 1), (8, 1, 128, 1, 1 << 28)):
+        with pytest.raises(ifx.IfxError):
+            ifx.ifx_attention_area_bytes(*bad)
+
+
 @pytest.mark.parametrize("heads", [1, 2, 3, 5, 7, 8, 9, 12, 13, 17, 40, 130, 257])
 @pytest.mark.parametrize("groups", [1, 2, 8])
 def test_attention_group_items_tile_every_head(heads, groups):
