@@ -128,6 +128,60 @@ def test_f32_in_pieces_beyond_bf16s_ease(gpu_device, what):
     assert np.abs(synth.to_f64_numpy(lse)[rows, heads] - want_lse).max() <= 2e-5
 
 
+@pytest.mark.parametrize("what", ["values near the smallest", "keys near the smallest", "queries near the smallest", "values near the largest"])
+def test_f32_in_pieces_of_every_size(gpu_device, what):
+    """Elements as small and as large as fp32 has them, rows that a few keys dominate (queries x 4): the tolerance of elements
+    near 1.  An element of 2^-124 held to 2^-134 (a bf16's last subnormal place) is off by up to 1e-3; weights of up to e^2
+    take a sum of these values beyond the largest number, where weights of up to 1 stay below it."""
+    dev, n, H, D = gpu_device, 1560, 3, 128
+    assert ifx.ifx_attention_f32_key_parts(n, H, D, 2 * n)[1] == 256
+    (_, k0, v0), (q, k1, v1) = (synth.draw_qkv(97, b, 0, 0, n, H, D, torch.float32, dev) for b in (0, 999))
+    q, vscale, scale = 4.0 * q, 1.0, 1.0 / np.sqrt(D)
+    if what == "values near the smallest":
+        vscale = 2.0 ** -124
+    elif what == "keys near the smallest":
+        k0, k1, q, scale = k0 * 2.0 ** -122, k1 * 2.0 ** -122, q * 2.0 ** 60, scale * 2.0 ** 62
+    elif what == "queries near the smallest":
+        q, k0, k1, scale = q * 2.0 ** -122, k0 * 2.0 ** 60, k1 * 2.0 ** 60, scale * 2.0 ** 62
+    else:
+        q, vscale = q / 4, 2.0 ** 119
+        v0, v1 = ((0.5 + v.abs() / 8).clamp(max=1.0) for v in (v0, v1))
+    v0, v1 = v0 * vscale, v1 * vscale
+    with ifx.KVCache(1, H, D, n, n, ifx.IFX_F32, softmax_scale=float(scale)) as cache:
+        cache.commit(0, k0, v0)
+        out, lse = torch.empty_like(q), torch.empty((n, H), device=dev)
+        cache.attention_blocks(0, q, k1, v1, None, out, lse)
+        torch.cuda.synchronize()
+    rows, heads = rows_of(n, H)
+    want, want_lse = oracle.attention_rows(synth.to_f64_numpy(q), synth.to_f64_numpy(k0), synth.to_f64_numpy(v0), synth.to_f64_numpy(k1),
+                                           synth.to_f64_numpy(v1), rows, heads, scale=float(np.float32(scale)))
+    assert np.abs(synth.to_f64_numpy(out)[rows, heads] - want).max() <= 1e-5 * vscale
+    assert np.abs(synth.to_f64_numpy(lse)[rows, heads] - want_lse).max() <= 4e-5
+
+
+def test_f32_in_pieces_weights_near_the_smallest(gpu_device):
+    """Values that read single weights out: e^-80 has its last pieces below a bf16's range, e^-89 is subnormal (22 bits)."""
+    dev, n, H, D = gpu_device, 1560, 3, 64
+    assert ifx.ifx_attention_f32_key_parts(n, H, D, 2 * n)[1] == 256
+    q, k0, k1, v0, v1 = (torch.zeros((n, H, D), device=dev) for _ in range(5))
+    q[..., 0] = 8.0  # times the scale: 1
+    faint = {5: -80.0, 700: -86.0, 1559: -89.0}
+    for d, (j, s) in enumerate(faint.items()):
+        k0[j, :, 0], v0[j, :, d] = s, 2.0 ** 60
+        k1[j, :, 0], v1[j, :, 8 + d] = s, 2.0 ** 60
+    with ifx.KVCache(1, H, D, n, n, ifx.IFX_F32) as cache:
+        cache.commit(0, k0, v0)
+        out = torch.empty_like(q)
+        cache.attention(0, q, k1, v1, out)
+        torch.cuda.synchronize()
+    got = synth.to_f64_numpy(out)
+    want = np.zeros(D)
+    for d, s in enumerate(faint.values()):
+        want[d] = want[8 + d] = np.exp(s) * 2.0 ** 60 / (2 * n - 6)
+    # half a unit in the last place of 86 log2 e is 2^-18: 2.6e-6 of e^-86; the other steps 5e-7
+    assert (np.abs(got - want) <= 4e-6 * want).all()
+
+
 def test_f32_streams_without_an_area(gpu_device):
     """Two streams of a cache have memory for parts; the third runs the call whole, on the kernel of 16-row tiles: the
     same but for fp32's rounding."""
