@@ -96,8 +96,8 @@ inline int attn_f32_parts(int64_t workgroups, int padded_d, int64_t subs)
 }
 // Which kernel takes a call, and to how many workgroups per row tile its keys are dealt.  attn_f32l_kernel (256-row
 // workgroups, ifx_attn_f32_large.hpp) where its workgroups, in parts, fill the chip for long enough.  Both sides measured (us, this
-// kernel in its parts and that one): 1560 rows x 12 heads x 128, 3120 keys 296, 181; x 16, 4680 keys 594, 331; x 2, 7800 keys
-// 143, 95; x 3, 3120 keys 92, 68; 1560 x 9 x 64, 4680 keys 198, 131.  It takes no selection of blocks.
+// kernel in its parts and that one): 1560 rows x 12 heads x 128, 3120 keys 296, 176; x 16, 4680 keys 594, 339; x 2, 7800 keys
+// 143, 88; x 3, 3120 keys 92, 64; 1560 x 9 x 64, 4680 keys 198, 128.  It takes no selection of blocks.
 struct f32_plan {
     bool large;
     int parts;
@@ -449,7 +449,7 @@ __global__ __launch_bounds__(256) void combine_f32_kernel(const attn_f32_args a)
         sum += f * ml[1];
         o += f * *reinterpret_cast<const f32x4 *>(a.partial + at * DP + 4 * c);
     }
-    if (a.lse != nullptr && c == 0) a.lse[(int64_t)i * a.H + h] = M + logf(sum);
+    if (a.lse != nullptr && c == 0) a.lse[(int64_t)i * a.H + h] = (float)((double)M + log((double)sum));
     const float inv = 1.0f / sum;
     *reinterpret_cast<f32x4 *>(a.out + ((int64_t)i * a.H + h) * a.D + 4 * c) = o * inv;
 }

@@ -128,11 +128,10 @@ def test_f32_in_pieces_beyond_bf16s_ease(gpu_device, what):
     assert np.abs(synth.to_f64_numpy(lse)[rows, heads] - want_lse).max() <= 2e-5
 
 
-@pytest.mark.parametrize("what", ["values near the smallest", "keys near the smallest", "queries near the smallest", "values near the largest"])
+@pytest.mark.parametrize("what", ["values near the smallest", "keys near the smallest", "queries near the smallest"])
 def test_f32_in_pieces_of_every_size(gpu_device, what):
-    """Elements as small and as large as fp32 has them, rows that a few keys dominate (queries x 4): the tolerance of elements
-    near 1.  An element of 2^-124 held to 2^-134 (a bf16's last subnormal place) is off by up to 1e-3; weights of up to e^2
-    take a sum of these values beyond the largest number, where weights of up to 1 stay below it."""
+    """Elements as small as fp32 has them, rows that a few keys dominate (queries x 4): the tolerance of elements near 1.  An
+    element of 2^-124 held to 2^-134 (a bf16's last subnormal place) is off by up to 1e-3."""
     dev, n, H, D = gpu_device, 1560, 3, 128
     assert ifx.ifx_attention_f32_key_parts(n, H, D, 2 * n)[1] == 256
     (_, k0, v0), (q, k1, v1) = (synth.draw_qkv(97, b, 0, 0, n, H, D, torch.float32, dev) for b in (0, 999))
@@ -141,11 +140,8 @@ def test_f32_in_pieces_of_every_size(gpu_device, what):
         vscale = 2.0 ** -124
     elif what == "keys near the smallest":
         k0, k1, q, scale = k0 * 2.0 ** -122, k1 * 2.0 ** -122, q * 2.0 ** 60, scale * 2.0 ** 62
-    elif what == "queries near the smallest":
-        q, k0, k1, scale = q * 2.0 ** -122, k0 * 2.0 ** 60, k1 * 2.0 ** 60, scale * 2.0 ** 62
     else:
-        q, vscale = q / 4, 2.0 ** 119
-        v0, v1 = ((0.5 + v.abs() / 8).clamp(max=1.0) for v in (v0, v1))
+        q, k0, k1, scale = q * 2.0 ** -122, k0 * 2.0 ** 60, k1 * 2.0 ** 60, scale * 2.0 ** 62
     v0, v1 = v0 * vscale, v1 * vscale
     with ifx.KVCache(1, H, D, n, n, ifx.IFX_F32, softmax_scale=float(scale)) as cache:
         cache.commit(0, k0, v0)
@@ -157,6 +153,45 @@ def test_f32_in_pieces_of_every_size(gpu_device, what):
                                            synth.to_f64_numpy(v1), rows, heads, scale=float(np.float32(scale)))
     assert np.abs(synth.to_f64_numpy(out)[rows, heads] - want).max() <= 1e-5 * vscale
     assert np.abs(synth.to_f64_numpy(lse)[rows, heads] - want_lse).max() <= 4e-5
+
+
+def test_f32_in_pieces_values_near_the_largest(gpu_device):
+    """718 of 750 keys score 1.9, the first 32 nothing: against the largest score the sum of weighted values is 722 x 2^118, below
+    2^128; against a first reference of 0 it is 4800 x 2^118."""
+    dev, n, H, D, cap = gpu_device, 250, 130, 128, 2
+    assert ifx.ifx_attention_f32_key_parts(n, H, D, (cap + 1) * n) == (1, 256)
+    q, k0, k1 = (torch.zeros((n, H, D), device=dev) for _ in range(3))
+    v = torch.full((n, H, D), 2.0 ** 118, device=dev)
+    q[..., 0] = 1.0
+    k0[32:, :, 0] = k1[..., 0] = 1.9
+    with ifx.KVCache(1, H, D, cap * n, n, ifx.IFX_F32, softmax_scale=1.0) as cache:
+        cache.commit(0, k0, v)
+        cache.commit(0, k1, v)
+        out, lse = torch.empty_like(q), torch.empty((n, H), device=dev)
+        cache.attention_blocks(0, q, k1, v, None, out, lse)
+        torch.cuda.synchronize()
+    assert (out / 2.0 ** 118 - 1).abs().max() <= 2e-6
+    assert np.abs(synth.to_f64_numpy(lse) - np.log(32 + 718 * np.exp(float(np.float32(1.9))))).max() <= 2e-6
+
+
+@pytest.mark.parametrize("n,H,D,cap", [(1560, 3, 128, 1), (250, 130, 128, 2)])  # in 12 parts, whole
+def test_f32_in_pieces_log_sum_exp(gpu_device, n, H, D, cap):
+    """Half a unit in the last place of a number from 8 on is 4.8e-7; the scores' own rounding adds as much at most.  A logarithm
+    rounded before the reference is added to it comes out up to 1.5e-6 off."""
+    dev = gpu_device
+    assert ifx.ifx_attention_f32_key_parts(n, H, D, (cap + 1) * n)[1] == 256
+    blocks = [synth.draw_qkv(101, b, 0, 0, n, H, D, torch.float32, dev) for b in range(cap + 1)]
+    with ifx.KVCache(1, H, D, cap * n, n, ifx.IFX_F32) as cache:
+        for _, k, v in blocks[:cap]:
+            cache.commit(0, k, v)
+        q, k, v = blocks[cap]
+        out, lse = torch.empty_like(q), torch.empty((n, H), device=dev)
+        cache.attention_blocks(0, q, k, v, None, out, lse)
+        torch.cuda.synchronize()
+    keys = torch.cat([b[1] for b in blocks]).double().cpu()
+    for h in range(0, H, 13):
+        want = torch.logsumexp(q[:, h].double().cpu() @ keys[:, h].T.contiguous() * float(np.float32(1) / np.sqrt(np.float32(D))), -1)
+        assert (lse[:, h].double().cpu() - want).abs().max() <= 1e-6, h
 
 
 def test_f32_in_pieces_weights_near_the_smallest(gpu_device):
