@@ -194,6 +194,36 @@ def test_f32_in_pieces_log_sum_exp(gpu_device, n, H, D, cap):
         assert (lse[:, h].double().cpu() - want).abs().max() <= 1e-6, h
 
 
+@pytest.mark.parametrize("what", ["infinite keys", "infinite queries", "values near the largest"])
+def test_f32_in_pieces_time_of_other_inputs(gpu_device, what):
+    """Scores and sums taken again in fp32: 2 to 4 times an ordinary call; a lane at a time it was 70 times one."""
+    dev, n, H, D = gpu_device, 1560, 12, 128
+    assert ifx.ifx_attention_f32_key_parts(n, H, D, 2 * n)[1] == 256
+    (q, k0, v0), (_, k1, v1) = (synth.draw_qkv(103, b, 0, 0, n, H, D, torch.float32, dev) for b in (0, 1))
+    odd = [x.clone() for x in (q, k0, v0)]
+    if what == "values near the largest":
+        odd[2] *= 2.0 ** 100
+    else:
+        odd[0][..., 0] = odd[0][..., 0].abs() + 0.5
+        odd[1 if what == "infinite keys" else 0][::7, :, 0] = -float("inf")
+    out = torch.empty_like(q)
+
+    def best_of(queries, keys, values):
+        with ifx.KVCache(1, H, D, n, n, ifx.IFX_F32) as cache:
+            cache.commit(0, keys, values)
+            times = []
+            for _ in range(6):
+                start, stop = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+                start.record()
+                cache.attention(0, queries, k1, v1, out)
+                stop.record()
+                torch.cuda.synchronize()
+                times.append(start.elapsed_time(stop))
+        return min(times)
+
+    assert best_of(*odd) <= 12 * best_of(q, k0, v0)
+
+
 def test_f32_in_pieces_weights_near_the_smallest(gpu_device):
     """Values that read single weights out: e^-80 has its last pieces below a bf16's range, e^-89 is subnormal (22 bits)."""
     dev, n, H, D = gpu_device, 1560, 3, 64
