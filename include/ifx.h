@@ -97,9 +97,13 @@ ifx_kv_cache *ifx_kv_cache_create(int layers, int heads, int head_dim, int64_t c
  * One kernel launch; or, where the rows are too few for the chip and the keys
  * many (ifx_attention_key_parts, ifx_attention_f32_key_parts), two: the keys are dealt to several
  * workgroups per row tile and their results, in memory that the cache holds
- * for each of the first two streams such calls come on, put together.  On other
- * streams, on one being captured and on hipStreamPerThread such a call is one
- * launch too: the same result up to the rounding of another summation order.
+ * for two streams at a time, put together.  The first two streams that such
+ * calls come on have it; another stream gets the memory of one (other than the
+ * null stream) whose last call has finished and which has made none while eight
+ * calls went without.  On a stream without it, on one being captured and on
+ * hipStreamPerThread such a call is one launch too: the same result up to the
+ * rounding of another summation order.  Off the null stream it records an
+ * event (created by ifx_kv_cache_configure) behind its launches.
  * bf16: head_dim 128 only.  Non-finite values (NaN, +-inf) in q, k_blk, v_blk
  * or in committed blocks are not detected: the call still returns IFX_OK, never
  * faults and writes all of `out`, but the outputs of every (query, head) whose

@@ -86,16 +86,18 @@ struct ifx_kv_cache {
     int parts = 0;              // bf16: workgroups per head that copy K rows in a commit
     int *blk_list = nullptr;    // [layers][stride_blocks]: first tokens of a selection too long for the kernel arguments,
                                 // written by the attention call that uses it, in stream order
-    // Memory for the partial results of attention whose keys are dealt to several workgroups: one area of
-    // split_bytes for each of the first SPLIT_AREAS streams that make such a call.  Calls on one
-    // stream follow one another, and an area never changes its stream; a handle that hipStreamCreate gives out
-    // again belongs to a stream whose work has finished (hipStreamDestroy waits: 107 ms with a
-    // kernel of that length in flight).  Held by split_mutex while a call enqueues its two launches.
+    // Memory for the partial results of attention whose keys are dealt to several workgroups: areas of split_bytes,
+    // each a stream's at a time (split_area).  split_mutex is held while a call enqueues its two launches.
+    struct area {
+        hipStream_t stream = nullptr;
+        bool taken = false;
+        int missed = 0;             // calls that found no area since this stream's last one (negative: it stays this stream's)
+        hipEvent_t done = nullptr;  // behind that one; not recorded on the null stream
+    };
     unsigned char *split_mem = nullptr;
     size_t split_bytes = 0;
     static constexpr int SPLIT_AREAS = 2;
-    hipStream_t split_stream[SPLIT_AREAS] = {};
-    int split_streams = 0;
+    area areas[SPLIT_AREAS];
     std::mutex split_mutex;
     std::vector<ifx_ring> rings;
     bool profile = false;
@@ -179,10 +181,20 @@ void (*bf16_kernel(bool table, bool fp8, int groups, bool split))(const ifx::att
     return split ? bf16_kernel_of<1, true>(table, fp8) : bf16_kernel_of<1, false>(table, fp8);
 }
 
-// The area of partial results of calls on stream s, or nullptr: a stream without one, a stream being
-// captured (its launches run again at times that no stream orders), a handle that stands for several streams, or no room.
-// With split_mutex held.
-unsigned char *split_area(ifx_kv_cache *c, hipStream_t s, size_t bytes)
+// An area goes from one stream to another when so many calls have found none since the first one's last call, and that has
+// finished.  (Streams that take turns keep theirs, and with them the bits of their results; of streams made one
+// after another each has the area from its ninth call on, in a step over 30 layers the ninth layer.)
+constexpr int SPLIT_MISSED = 8;
+
+bool null_stream(hipStream_t s) { return s == nullptr || s == hipStreamLegacy; }
+
+// The area that the calls on stream s have, or now get, for their partial results; nullptr: none is free, the stream is being
+// captured (its launches run again at times that no stream orders), its handle stands for several streams, or
+// there is no room.  With split_mutex held.
+// Calls on one stream follow one another.  But a handle may be that of a stream made after the area's was destroyed, whose
+// calls need not have finished: so the stream waits for the event behind the last one, which costs nothing where that was its own.
+// The null stream is never destroyed and needs no event; recording one takes 1.2 us a call.
+ifx_kv_cache::area *split_area(ifx_kv_cache *c, hipStream_t s, size_t bytes)
 {
     if (!c->split_mem || bytes > c->split_bytes || s == hipStreamPerThread) return nullptr;
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
@@ -191,12 +203,60 @@ unsigned char *split_area(ifx_kv_cache *c, hipStream_t s, size_t bytes)
         return nullptr;
     }
     if (capturing != hipStreamCaptureStatusNone) return nullptr;
-    int i = 0;
-    while (i < c->split_streams && c->split_stream[i] != s) ++i;
-    if (i == ifx_kv_cache::SPLIT_AREAS) return nullptr;
-    if (i == c->split_streams) c->split_stream[c->split_streams++] = s;
-    return c->split_mem + (size_t)i * c->split_bytes;
+    if (null_stream(s)) s = nullptr;
+    ifx_kv_cache::area *unused = nullptr, *left = nullptr;
+    for (auto &a : c->areas) {
+        if (a.taken && a.stream == s) {
+            if (s != nullptr && hipStreamWaitEvent(s, a.done, 0) != hipSuccess) {
+                (void)hipGetLastError();
+                return nullptr;
+            }
+            a.missed = a.missed < 0 ? a.missed : 0;
+            return &a;
+        }
+        if (!a.taken && !unused) unused = &a;
+        if (a.taken && a.stream != nullptr && a.missed >= SPLIT_MISSED && (!left || a.missed > left->missed)) left = &a;
+    }
+    if (!unused && left) {
+        // (in the thread's usual mode a query ends every capture that another thread has under way)
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        if (hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess) {
+            if (hipEventQuery(left->done) == hipSuccess) unused = left;
+            (void)hipThreadExchangeStreamCaptureMode(&mode);
+        }
+        if (!unused) (void)hipGetLastError();
+    }
+    if (!unused) {
+        for (auto &a : c->areas) a.missed += a.missed >= 0 && a.missed < (1 << 30);
+        return nullptr;
+    }
+    unused->taken = true;
+    unused->stream = s;
+    unused->missed = 0;
+    return unused;
 }
+
+// The area during one call; behind what the call enqueued, its event.
+class area_use {
+  public:
+    area_use() = default;
+    area_use(const area_use &) = delete;
+    area_use &operator=(const area_use &) = delete;
+    unsigned char *take(ifx_kv_cache *c, hipStream_t s, size_t bytes)
+    {
+        a_ = split_area(c, s, bytes);
+        return a_ ? c->split_mem + (size_t)(a_ - c->areas) * c->split_bytes : nullptr;
+    }
+    ~area_use()
+    {
+        if (!a_ || a_->stream == nullptr || hipEventRecord(a_->done, a_->stream) == hipSuccess) return;
+        (void)hipGetLastError();
+        a_->missed = -1;
+    }
+
+  private:
+    ifx_kv_cache::area *a_ = nullptr;
+};
 
 template <bool SPLIT>
 void (*few_kernel_of(bool table, bool fp8))(const ifx::attn_few_args)
@@ -482,6 +542,10 @@ static void take_aux(ifx_kv_cache *c, const aux_memory &m)
     c->blk_list = reinterpret_cast<int *>(p + m.kn_bytes);
     c->split_mem = m.split_bytes ? p + m.split_at : nullptr;
     c->split_bytes = m.split_bytes;
+    for (auto &a : c->areas) {  // (nothing is enqueued on the memory: it is new)
+        a.taken = false;
+        a.missed = 0;
+    }
 }
 
 int ifx_kv_cache_reserve(ifx_kv_cache *c, int64_t max_capacity_tokens)
@@ -586,6 +650,8 @@ int ifx_kv_cache_configure(ifx_kv_cache *c, int64_t block_tokens, int dtype, flo
         e = alloc_aux(c, c->stride_blocks, parts, block_tokens, dtype != IFX_F32, &aux);
         take_aux(c, aux);
     }
+    for (auto &a : c->areas)
+        if (e == hipSuccess && !a.done) e = hipEventCreateWithFlags(&a.done, hipEventDisableTiming | hipEventDisableSystemFence);
     if (e == hipSuccess) e = hipDeviceSynchronize();
     for (const bool gather : {false, true})
         for (const bool split : {false, true})
@@ -651,6 +717,8 @@ void ifx_kv_cache_destroy(ifx_kv_cache *c)
             (void)hipEventDestroy(ev.start);
             (void)hipEventDestroy(ev.stop);
         }
+    for (auto &a : c->areas)
+        if (a.done) (void)hipEventDestroy(a.done);
     delete c;
 }
 
@@ -896,6 +964,7 @@ static int attention_impl(ifx_kv_cache *c, int layer, const void *q, const void 
     if (rc) return rc;
     ifx::attn_plan plan = {0, H, 1};
     std::unique_lock<std::mutex> split_lock(c->split_mutex, std::defer_lock);
+    area_use use;  // (ends before the lock)
     unsigned char *area = nullptr;
     int64_t units = 0;
     if (c->mfma()) {
@@ -903,7 +972,7 @@ static int attention_impl(ifx_kv_cache *c, int layer, const void *q, const void 
         if (plan.parts > 1) {
             split_lock.lock();
             units = (int64_t)(H - plan.whole_heads) * plan.parts * ((n + 31) / 32);
-            area = split_area(c, s, (size_t)units * ifx::SPLIT_UNIT_BYTES);
+            area = use.take(c, s, (size_t)units * ifx::SPLIT_UNIT_BYTES);
             if (!area) plan = {ifx::attn_groups_for(n, H), H, 1};
         }
     }
@@ -968,7 +1037,7 @@ static int attention_impl(ifx_kv_cache *c, int layer, const void *q, const void 
         const int64_t split_rows = (int64_t)H * parts * tiles.tiles * ifx::F32_ROWS;
         if (parts > 1) {
             split_lock.lock();
-            area = split_area(c, s, (size_t)split_rows * ifx::attn_f32_split_row_bytes(f32_padded_dim(D)));
+            area = use.take(c, s, (size_t)split_rows * ifx::attn_f32_split_row_bytes(f32_padded_dim(D)));
             if (!area) {  // (whole, the large kernel's workgroups would be too few)
                 parts = 1;
                 fp.large = false;
