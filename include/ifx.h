@@ -195,7 +195,10 @@ int ifx_block_attention_blocks(ifx_kv_cache *cache, int layer, const void *q, co
  * ifx_block_attention_blocks for callers that cannot allocate device memory
  * or must not touch memory that something else allocated for them: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
- * Same arguments, same result, bit for bit.  The block list does not go to
+ * Same arguments, same result, bit for bit where both calls come in parts or
+ * neither does (see ifx_block_attention; the same stream, and neither of them
+ * captured); else up to the rounding of another summation order: a captured
+ * call never comes in parts.  The block list does not go to
  * the cache's own per-layer list but, whenever the selection needs a list at
  * all (any selection that is not "every resident block in slot order"), to a
  * fixed array of IFX_NOALLOC_MAX_LISTED_BLOCKS entries (16 KiB) inside the

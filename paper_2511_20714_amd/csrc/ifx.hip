@@ -900,7 +900,7 @@ static int enqueue_list(int *dst, const std::vector<int> &first_token, hipStream
 
 // Attention of q against the resident blocks `blocks[0 .. n_blocks)` (logical numbers, 0 = oldest,
 // already validated; nullptr: all resident blocks in slot order) and, when k_blk / v_blk are given,
-// the current block, read where the caller has it.  One attention launch; a selection of more than
+// the current block, read where the caller has it.  One attention launch, or two where the keys come in parts; a selection of more than
 // IFX_MAX_KEY_BLOCKS blocks is first written to `list_mem` (device, room for max_list entries:
 // the layer's own list, or the caller's), a tiny launch per LIST_CHUNK entries.
 static int attention_impl(ifx_kv_cache *c, int layer, const void *q, const void *k_blk, const void *v_blk,
