@@ -96,7 +96,8 @@ constexpr float BF_HEADROOM = 7.0f;
 constexpr float BF_HEADROOM_EXACT = 31.0f;
 // log2 units; 2^-88 is still a normal bf16 / fp32.  Sharper rows, which a few keys dominate, take the exact sums: at a
 // bound of 49 (queries x 3) such a row's unrounded sum had cost an output of 792 rows x 29 heads a second half unit in
-// the last place (1.1e-2, over 5 % of the outputs' root mean square).
+// the last place (1.1e-2, over 5 % of the outputs' root mean square).  They cost 4 %: 4680 rows x 12 heads x 32760 keys 753 us
+// with queries x 2.6 (bound 42), 784 x 2.8 (46).
 constexpr float BF_BOUND_LIMIT = 44.0f;
 // SPLIT: a unit of partial results is 32 rows x 128 dimensions as a wavefront's accumulators hold them, 64
 // lanes' 4 floats after one another, then the next 4 (16 KiB); and for each of the 32 rows the reference, the sum of
