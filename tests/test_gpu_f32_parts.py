@@ -265,3 +265,31 @@ def test_f32_streams_without_an_area(gpu_device):
         torch.cuda.synchronize()
     assert torch.equal(outs[0], outs[1])
     assert (outs[0] - outs[2]).abs().max() <= 1e-5
+
+
+@pytest.mark.parametrize("n,H,D,cap,parts", [
+    (552, 2, 128, 8, 39),   # four tiles of keys to a workgroup, 18 wavefronts of rows in three
+    (736, 6, 72, 2, 14),    # four or five
+    (656, 4, 64, 5, 21),    # five or six; workgroups of 7 wavefronts
+    (576, 4, 40, 8, 21),    # seven or eight, padded to 64
+    (248, 33, 128, 2, 6),   # four, and none cached in the last part
+])
+def test_f32_in_pieces_step_by_step(gpu_device, n, H, D, cap, parts):
+    """Few tiles, even and odd numbers of them, for wavefronts that run a step apart."""
+    dev = gpu_device
+    assert ifx.ifx_attention_f32_key_parts(n, H, D, (cap + 1) * n) == (parts, 256)
+    hs = np.array([0, H - 1])
+    blocks = [synth.draw_qkv(97, b, 0, 0, n, H, D, torch.float32, dev) for b in range(cap + 1)]
+    with ifx.KVCache(1, H, D, cap * n, n, ifx.IFX_F32) as cache:
+        for _, k, v in blocks[:cap]:
+            cache.commit(0, k, v)
+        q = blocks[cap][0]
+        out, lse = torch.full((n + 1, H, D), float("nan"), device=dev), torch.full((n + 1, H), float("nan"), device=dev)
+        cache.attention_blocks(0, *blocks[cap], None, out[:n], lse[:n])
+        torch.cuda.synchronize()
+    assert torch.isfinite(out[:n]).all() and torch.isfinite(lse[:n]).all() and torch.isnan(out[n]).all() and torch.isnan(lse[n]).all()
+    rows, heads = rows_of(n, 2)
+    want, want_lse = oracle.attention_rows(synth.to_f64_numpy(q)[:, hs], np.concatenate([synth.to_f64_numpy(b[1])[:, hs] for b in blocks]),
+                                           np.concatenate([synth.to_f64_numpy(b[2])[:, hs] for b in blocks]), None, None, rows, heads)
+    assert np.abs(synth.to_f64_numpy(out[:n])[rows, hs[heads]] - want).max() <= 1e-5
+    assert np.abs(synth.to_f64_numpy(lse[:n])[rows, hs[heads]] - want_lse).max() <= 2e-5
