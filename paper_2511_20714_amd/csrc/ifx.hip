@@ -258,13 +258,18 @@ class area_use {
     ifx_kv_cache::area *a_ = nullptr;
 };
 
-template <bool SPLIT>
+template <bool SPLIT, int SLABS>
 void (*few_kernel_of(bool table, bool fp8))(const ifx::attn_few_args)
 {
-    return table ? fp8 ? ifx::attn_few_kernel<true, true, SPLIT> : ifx::attn_few_kernel<false, true, SPLIT>
-                 : fp8 ? ifx::attn_few_kernel<true, false, SPLIT> : ifx::attn_few_kernel<false, false, SPLIT>;
+    return table ? fp8 ? ifx::attn_few_kernel<true, true, SPLIT, SLABS> : ifx::attn_few_kernel<false, true, SPLIT, SLABS>
+                 : fp8 ? ifx::attn_few_kernel<true, false, SPLIT, SLABS> : ifx::attn_few_kernel<false, false, SPLIT, SLABS>;
 }
-void (*few_kernel(bool table, bool fp8, bool split))(const ifx::attn_few_args) { return split ? few_kernel_of<true>(table, fp8) : few_kernel_of<false>(table, fp8); }
+// slab_groups: workgroups per row tile without parts
+void (*few_kernel(bool table, bool fp8, bool split, int slab_groups))(const ifx::attn_few_args)
+{
+    if (split) return few_kernel_of<true, 4>(table, fp8);
+    return slab_groups == 4 ? few_kernel_of<false, 1>(table, fp8) : slab_groups == 2 ? few_kernel_of<false, 2>(table, fp8) : few_kernel_of<false, 4>(table, fp8);
+}
 
 // One timing sample (a pair of HIP events around what a call enqueues), taken only while
 // profiling is on and the stream is not being captured (an event recorded into a graph has no
@@ -666,12 +671,12 @@ int ifx_kv_cache_configure(ifx_kv_cache *c, int64_t block_tokens, int dtype, flo
         const bool fp8 = dtype == IFX_FP8_E4M3;
         for (const bool table : {false, true}) {
             if (e == hipSuccess)
-                e = groups == 8 ? hipFuncSetAttribute(reinterpret_cast<const void *>(few_kernel(table, fp8, false)),
+                e = groups == 8 ? hipFuncSetAttribute(reinterpret_cast<const void *>(few_kernel(table, fp8, false, ifx::few_slab_groups((int)block_tokens, c->heads))),
                                                       hipFuncAttributeMaxDynamicSharedMemorySize, ifx::FEW_LDS_BYTES)
                                 : hipFuncSetAttribute(reinterpret_cast<const void *>(bf16_kernel(table, fp8, groups, false)),
                                                       hipFuncAttributeMaxDynamicSharedMemorySize, ifx::BF_LDS_BYTES);
             if (e == hipSuccess && groups == 8)
-                e = hipFuncSetAttribute(reinterpret_cast<const void *>(few_kernel(table, fp8, true)), hipFuncAttributeMaxDynamicSharedMemorySize,
+                e = hipFuncSetAttribute(reinterpret_cast<const void *>(few_kernel(table, fp8, true, 1)), hipFuncAttributeMaxDynamicSharedMemorySize,
                                         ifx::FEW_LDS_BYTES);
             if (e == hipSuccess)
                 e = hipFuncSetAttribute(reinterpret_cast<const void *>(bf16_kernel(table, fp8, 1, true)),
@@ -997,9 +1002,10 @@ static int attention_impl(ifx_kv_cache *c, int layer, const void *q, const void 
         a.split = ifx::attn_split_for(n, H, plan);
         a.partial = partial;
         a.stats = stats;
-        a.tiles = ifx::row_tiles_for(n, H * plan.parts, ifx::FEW_ROWS);
+        const int slab_groups = plan.parts > 1 ? 1 : ifx::few_slab_groups(n, H);
+        a.tiles = ifx::row_tiles_for(n, H * plan.parts, ifx::FEW_ROWS, slab_groups);
         a.blocks = table;
-        hipLaunchKernelGGL(few_kernel(use_table, c->dtype == IFX_FP8_E4M3, plan.parts > 1), dim3((unsigned)(8 * a.tiles.per_xcd)), dim3(64 * ifx::FEW_WAVES), ifx::FEW_LDS_BYTES, s, a);
+        hipLaunchKernelGGL(few_kernel(use_table, c->dtype == IFX_FP8_E4M3, plan.parts > 1, slab_groups), dim3((unsigned)(8 * a.tiles.per_xcd)), dim3(64 * ifx::FEW_WAVES), ifx::FEW_LDS_BYTES, s, a);
     } else if (c->mfma()) {
         ifx::attn_bf16_args a;
         a.q = static_cast<const __bf16 *>(q);

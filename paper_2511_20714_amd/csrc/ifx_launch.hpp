@@ -84,6 +84,19 @@ inline int attn_groups_for(int n, int heads)
     return whole > 256 && halved <= (row_wavefronts > 36 ? 680 : 512) ? 2 : 1;
 }
 
+// Workgroups that share a 32-row tile of a call of eight key groups without parts: each takes all of the tile's scores and its
+// own of the 4 slabs of 32 output dimensions, and reads 256 of a key's 512 bytes for the scores and 64 or 128 for the values.
+// What a step takes there is what one CU's L1 passes on, so on CUs that would be idle the tile ends sooner, and the wavefronts'
+// shares are put together a slab or two at a time; nothing is exchanged between the workgroups.  As many as
+// leave all of them one round on 256 CUs.  us, by one workgroup and shared (with the scalar work of a step also taken down
+// in that change), bf16 cache: 264 rows x 2 heads, 792 keys 9.6 -> 7.7; 1584 keys 12.7 -> 9.8; 88 x 4, 352 7.5 -> 6.2; two to a
+// tile: 136 x 20, 680 9.7 -> 8.4; 760 x 3, 1520 12.9 -> 11.1; 1000 x 4, 2000 15.1 -> 13.7; fp8: 208 x 11, 1664 14.1 -> 11.9.
+inline int few_slab_groups(int n, int heads)
+{
+    const int64_t workgroups = (int64_t)((n + 31) / 32) * heads;
+    return workgroups <= 64 ? 4 : workgroups <= 128 ? 2 : 1;
+}
+
 // How a bf16 call's keys are dealt: `groups` inside a workgroup (attn_groups_for), and those of heads
 // [whole_heads, heads) to `parts` workgroups per row tile (of 256 rows, one group, or of 32, eight); parts == 1: no head's.
 struct attn_plan {
@@ -119,9 +132,10 @@ inline attn_plan attn_split_candidate(int n, int heads)
 //    16 x 2400 30 -> 28, 800 x 10 x 6400 39 -> 38, 400 x 5 x 2000 15 -> 20.
 //  - 32-row workgroups are at most half a round: the same with those, whose partial results are fewer.  What a step of
 //    such a workgroup takes is the 128 KiB of keys that its CU's L1 can pass on (45 of 64 bytes per cycle), so only more
-//    CUs shorten it: 1560 x 1 x 10920 54 -> 21.6 (40 with 256-row ones), x 2 56 -> 36 (39), 1000 x 2 x 8000 41 -> 21,
-//    400 x 2 x 3200 20.4 -> 13.1, 264 x 2 x 2112 15.0 -> 12.2; level from 5 or 6 steps down: 264 x 2 x 1320 11.6 -> 11.6,
-//    400 x 5 x 2000 15.3 -> 14.5, 264 x 2 x 792 9.6 -> 10.7.
+//    CUs shorten it.  Against tiles shared by slabs (few_slab_groups): 1560 x 1 x 10920 41 -> 22, x 2 47 -> 38, 1000 x 2
+//    x 8000 35 -> 21, 680 x 1 x 3400 15.2 -> 13.3, 400 x 2 x 3200 15.0 -> 13.2, 1000 x 4 x 4000 22.3 -> 21.4; level at 10 to 12
+//    steps: 680 x 1 x 2720 13.3 -> 13.0, 1000 x 2 x 3000 16.9 -> 15.3, 552 x 3 x 2760 15.4 -> 14.7, 400 x 5 x 2800 15.3 -> 15.7, 264 x 2 x
+//    2112 11.3 -> 12.1; and behind below: 1000 x 1 x 2000 11.6 -> 13.4, 760 x 3 x 2280 13.4 -> 15.0, 264 x 2 x 792 7.7 -> 10.7.
 //  - a last round would be nearly empty: whole heads fill the rounds, the keys of the rest go to as many
 //    workgroups as its CUs.  4680 x 14 x 18720 648 -> 496, x 15 653 -> 526, x 16 654 -> 560, x 17 658 -> 595, x 18
 //    675 -> 642; x 28 x 14040 899 -> 753; 10800 x 7 x 32400 1120 -> 981; 1560 x 40 x 10920 379 -> 295; but 1560 x 37
@@ -141,8 +155,10 @@ inline attn_plan attn_plan_for(int n, int heads, int tiles)
     const float few_steps = (float)((tiles + 3) / 4);  // of a wavefront, 32 keys each
     float us = 8.f + tiles * 1.0f;                     // one group
     if (whole.groups == 8) {
-        const float busy = rows / 256.f;
-        us = 5.3f + few_steps * 1.13f * (1.f + 0.2f * busy * busy);
+        // (four to a tile: 0.6 to 0.9 a step, the more the fuller the chip; at 0.97 the line lies where parts are level)
+        const int sharing = few_slab_groups(n, heads);
+        const float busy = rows * (float)sharing / 256.f;
+        us = 5.3f + few_steps * (sharing == 4 ? 0.97f : sharing == 2 ? 0.67f + 0.39f * busy : 1.13f * (1.f + 0.2f * busy * busy));
     } else if (whole.groups == 2) {
         const float busy = (float)((row_waves + 3) / 4 * heads) / 256.f;
         us = 8.f + tiles * (busy <= 0.4f ? 0.52f : 0.52f + 0.4f * (busy - 0.4f));
@@ -250,10 +266,11 @@ struct row_tile {
     int head, tile;  // head < 0: nothing to do
 };
 
-inline row_tiles row_tiles_for(int n, int heads, int rows)
+// sharing: workgroups per tile of rows
+inline row_tiles row_tiles_for(int n, int heads, int rows, int sharing = 1)
 {
     row_tiles t;
-    t.tiles = (n + rows - 1) / rows;
+    t.tiles = (n + rows - 1) / rows * sharing;
     t.per_xcd = (int)(((int64_t)t.tiles * heads + 7) / 8);
     return t;
 }
