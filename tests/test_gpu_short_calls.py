@@ -1,4 +1,6 @@
-"""GPU parity of short calls: 32-row tiles whose output dimensions are shared by four, two or one workgroups."""
+"""GPU parity of short calls: 32-row tiles whose output dimensions are shared by four, two or one workgroups; and, with one and
+two key groups, whose first tiles are asked for before anything else is known: one to four tiles of cached keys or of
+the block alone, listed blocks, more key norms than the first loads take."""
 import numpy as np
 import pytest
 import torch
@@ -51,3 +53,17 @@ def test_shared_row_tiles(gpu_device, n, H, cap, blocks, with_block, dtype):
     assert ifx.ifx_attention_key_groups(n, H) == 8 and ifx.ifx_attention_key_parts(n, H, keys, with_block)[0] == 1
     for gain in (1.0, 5.0):
         assert check(gpu_device, dtype, n, H, cap, blocks, with_block, gain) <= 2e-5
+
+
+@pytest.mark.parametrize("dtype", [ifx.IFX_BF16, ifx.IFX_FP8_E4M3])
+@pytest.mark.parametrize("groups,n,H,cap,blocks,with_block", [
+    (1, 8, 257, 0, None, True), (1, 72, 100, 0, None, True), (1, 136, 64, 0, None, True),   # one, two and three tiles of the block alone
+    (1, 8, 257, 1, None, False), (1, 8, 257, 9, [8, 0, 4], True), (1, 136, 64, 2, None, True),
+    (1, 8, 257, 600, None, True),                                                            # 600 key norms
+    (2, 264, 30, 0, None, True), (2, 168, 43, 1, None, True), (2, 264, 30, 3, [2, 0], False), (2, 520, 16, 1, None, False),
+])
+def test_first_tiles(gpu_device, groups, n, H, cap, blocks, with_block, dtype):
+    assert ifx.ifx_attention_key_groups(n, H) == groups
+    for gain in (1.0, 5.0):  # under the norm bound, and past it
+        # past it a row's sum is of weights rounded to bf16: off by 2^-9
+        assert check(gpu_device, dtype, n, H, cap, blocks, with_block, gain) <= (2e-5 if gain == 1.0 and cap else 4e-3)
