@@ -10,26 +10,50 @@
 
 namespace ifx {
 
+// What streams past the caches (non-temporal accesses).  A commit's source has been used for the last time, and its
+// destination, next read by the attention call after it, is most of it dirty in the L2s when the kernel ends, which then write
+// it back: both stream (plain, then streaming: a block of 4680 tokens x 12 heads 14.3 -> 12.6 us, of 1560 6.7 -> 5.9, 30 layers
+// 315 -> 297 and 103 -> 94; into fp8 11.6 -> 10.0, 225 -> 212; attention, commit, attention the same as before within 2 %).
+// A read-back's source is read once; what it writes is what its caller reads next, which a streaming store would
+// send to memory first (read-back and a copy of it 23.8 us, 27.3 with streaming stores, 23.4 with streaming loads alone;
+// the read-back alone 14.2, 12.2, 13.5): loads only.  The same holds for merge_kernel, which reads results just written: neither.
+template <typename T>
+__device__ __forceinline__ T load_once(const T *p)
+{
+    return __builtin_nontemporal_load(p);
+}
+template <typename T>
+__device__ __forceinline__ void store_past(T *p, const T &v)
+{
+    __builtin_nontemporal_store(v, p);
+}
+
 // Rows of one head, 16-byte chunk by chunk: token t's row of `cpr` chunks from src + t * src_stride to
 // dst + t * dst_stride (both in chunks), tokens [t0, t_end).  A workgroup of 256 threads takes
 // 256 / cpr rows a round, U rounds in flight; the split of a thread's number into (row, chunk) is
 // done once, so the loop is loads, stores and additions (a flat index divided by the row and head
 // counts in 64 bits for every chunk: 15 layers of 4680 x 12 x 128 committed in 372 us, now 337).
-template <int U>
+template <int U, bool COMMIT>
 __device__ __forceinline__ void copy_rows_body(const u32x4 *__restrict__ src, int64_t src_stride, u32x4 *__restrict__ dst, int64_t dst_stride,
                                                int t0, int t_end, int cpr)
 {
     const int r = (int)threadIdx.x / cpr, c = (int)threadIdx.x - r * cpr, rows = 256 / cpr;
     if (r >= rows) return;
+    auto put = [&](int t, const u32x4 &v) {
+        if constexpr (COMMIT)
+            store_past(dst + (int64_t)t * dst_stride + c, v);
+        else
+            dst[(int64_t)t * dst_stride + c] = v;
+    };
     int t = t0 + r;
     for (; t + (U - 1) * rows < t_end; t += U * rows) {
         u32x4 v[U];
 #pragma unroll
-        for (int k = 0; k < U; ++k) v[k] = src[(int64_t)(t + k * rows) * src_stride + c];
+        for (int k = 0; k < U; ++k) v[k] = load_once(src + (int64_t)(t + k * rows) * src_stride + c);
 #pragma unroll
-        for (int k = 0; k < U; ++k) dst[(int64_t)(t + k * rows) * dst_stride + c] = v[k];
+        for (int k = 0; k < U; ++k) put(t + k * rows, v[k]);
     }
-    for (; t < t_end; t += rows) dst[(int64_t)t * dst_stride + c] = src[(int64_t)t * src_stride + c];
+    for (; t < t_end; t += rows) put(t, load_once(src + (int64_t)t * src_stride + c));
 }
 
 // Largest squared key norms: knorm[head][slot][part] = float bits of max_t |k[t,head,:]|^2 over
@@ -132,10 +156,10 @@ __device__ __forceinline__ void k_rows_norm_body(int h, int p, int parts, uint32
         float ss;
         if constexpr (FP8) {
             const u32x2 codes = bf16x8_to_e4m3(v);
-            drow8[(int64_t)tok * 16] = codes;
+            store_past(drow8 + (int64_t)tok * 16, codes);
             ss = e4m3x8_sumsq(codes);
         } else {
-            drow[(int64_t)tok * 16] = v;
+            store_past(drow + (int64_t)tok * 16, v);
             ss = bf16x2_sumsq(v[0]) + bf16x2_sumsq(v[1]) + bf16x2_sumsq(v[2]) + bf16x2_sumsq(v[3]);
         }
         const uint32_t tot = __builtin_bit_cast(uint32_t, row16_sum_to_lane15(ss)) & 0x7fffffffu;
@@ -144,11 +168,11 @@ __device__ __forceinline__ void k_rows_norm_body(int h, int p, int parts, uint32
     for (; t + (U - 1) * 16 < t_end; t += U * 16) {
         u32x4 v[U];
 #pragma unroll
-        for (int k = 0; k < U; ++k) v[k] = srow[(int64_t)(t + k * 16) * H * 16];
+        for (int k = 0; k < U; ++k) v[k] = load_once(srow + (int64_t)(t + k * 16) * H * 16);
 #pragma unroll
         for (int k = 0; k < U; ++k) put(t + k * 16, v[k]);
     }
-    for (; t < t_end; t += 16) put(t, srow[(int64_t)t * H * 16]);
+    for (; t < t_end; t += 16) put(t, load_once(srow + (int64_t)t * H * 16));
     if (c == 15) group_max[g] = best;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -188,7 +212,7 @@ __device__ __forceinline__ void v_to_granules_body(int bid, int nblocks, unsigne
             const int u = u0 + k * stride;
             if (u < units) {
                 const int half = u & 1, h = (u >> 1) % H, g = (u >> 1) / H;
-                v[k] = src[(((int64_t)g * 8 + (lane >> 3)) * H + h) * 16 + half * 8 + (lane & 7)];
+                v[k] = load_once(src + (((int64_t)g * 8 + (lane >> 3)) * H + h) * 16 + half * 8 + (lane & 7));
             }
         }
 #pragma unroll
@@ -205,9 +229,9 @@ __device__ __forceinline__ void v_to_granules_body(int bid, int nblocks, unsigne
                 const s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
                 const int64_t at = ((int64_t)h * gran_per_head + g0 + g) * 128 + half * 64 + lane;
                 if constexpr (FP8)
-                    static_cast<u32x2 *>(dst)[at] = bf16x8_to_e4m3(__builtin_bit_cast(u32x4, both));
+                    store_past(static_cast<u32x2 *>(dst) + at, bf16x8_to_e4m3(__builtin_bit_cast(u32x4, both)));
                 else
-                    static_cast<u32x4 *>(dst)[at] = __builtin_bit_cast(u32x4, both);
+                    store_past(static_cast<u32x4 *>(dst) + at, __builtin_bit_cast(u32x4, both));
             }
         }
     }
@@ -257,15 +281,15 @@ __global__ __launch_bounds__(256) void store_block_f32_kernel(const commit_layer
     const int h = (int)blockIdx.x % H, p = (int)blockIdx.x / H;
     const int chunk = (n + parts - 1) / parts;
     const int t0 = p * chunk, t_end = n - t0 < chunk ? n : t0 + chunk;
-    copy_rows_body<4>((const u32x4 *)(is_v ? L.v_src : L.k_src) + (int64_t)h * cpr, (int64_t)H * cpr,
+    copy_rows_body<4, true>((const u32x4 *)(is_v ? L.v_src : L.k_src) + (int64_t)h * cpr, (int64_t)H * cpr,
                       (u32x4 *)(is_v ? L.v_dst : L.k_dst) + ((int64_t)h * cache_tokens + L.tok0) * cpr, cpr, t0, t_end, cpr);
 }
 
 // ---- read-back: resident blocks to the caller's [tokens, H, head_dim] tensors ------------------
 // Bound by HBM, like the commit whose mirror it is: one launch for K and V of up to READ_MAX_BLOCKS
 // blocks (grid y), entry b from physical slot slot[b] to the b-th block of the output.
-// One 4680-token block of 12 heads: 13.9 us (57.5 MB moved, 4.1 TB/s; 30 such commits in one launch
-// run at 5.5), 26.9 with a launch each for K and V, 64-bit divisions for every chunk and V gathered
+// One 4680-token block of 12 heads: 13.5 us (57.5 MB moved, 4.3 TB/s; 30 such commits in one launch
+// run at 5.8), 26.9 with a launch each for K and V, 64-bit divisions for every chunk and V gathered
 // by 2-byte loads.  10800 tokens of 40 heads: 165 -> 92 us (4.8 TB/s).
 constexpr int READ_MAX_BLOCKS = 64;
 struct read_slots {
@@ -281,7 +305,7 @@ __global__ __launch_bounds__(256) void read_blocks_f32_kernel(const u32x4 *__res
     const int h = (int)blockIdx.x % H, p = (int)blockIdx.x / H;
     const int chunk = (n + parts - 1) / parts;
     const int t0 = p * chunk, t_end = n - t0 < chunk ? n : t0 + chunk;
-    copy_rows_body<4>((is_v ? v_region : k_region) + ((int64_t)h * cache_tokens + (int64_t)slots.slot[b] * n) * cpr, cpr,
+    copy_rows_body<4, false>((is_v ? v_region : k_region) + ((int64_t)h * cache_tokens + (int64_t)slots.slot[b] * n) * cpr, cpr,
                       (is_v ? v_dst : k_dst) + ((int64_t)b * n * H + h) * cpr, (int64_t)H * cpr, t0, t_end, cpr);
 }
 
@@ -331,11 +355,11 @@ __global__ __launch_bounds__(256) void read_blocks_bf16_kernel(const void *__res
         for (; t + (U - 1) * 16 < t_end; t += U * 16) {
             stored v[U];
 #pragma unroll
-            for (int k = 0; k < U; ++k) v[k] = srow[(int64_t)(t + k * 16) * 16];
+            for (int k = 0; k < U; ++k) v[k] = load_once(srow + (int64_t)(t + k * 16) * 16);
 #pragma unroll
             for (int k = 0; k < U; ++k) drow[(int64_t)(t + k * 16) * H * 16] = as_bf16(v[k]);
         }
-        for (; t < t_end; t += 16) drow[(int64_t)t * H * 16] = as_bf16(srow[(int64_t)t * 16]);
+        for (; t < t_end; t += 16) drow[(int64_t)t * H * 16] = as_bf16(load_once(srow + (int64_t)t * 16));
         return;
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -353,7 +377,7 @@ __global__ __launch_bounds__(256) void read_blocks_bf16_kernel(const void *__res
             const int u = u0 + k * stride;
             if (u < units) {
                 const int half = u & 1, h = (u >> 1) % H, gr = (u >> 1) / H;
-                v[k] = static_cast<const stored *>(v_region)[((int64_t)h * gran_per_head + g0 + gr) * 128 + half * 64 + lane];
+                v[k] = load_once(static_cast<const stored *>(v_region) + ((int64_t)h * gran_per_head + g0 + gr) * 128 + half * 64 + lane);
             }
         }
 #pragma unroll
