@@ -351,6 +351,16 @@ int f32_copy_parts(const ifx_kv_cache *c, int64_t rows_of_launch)
     return (int)(most < enough ? most : enough);
 }
 
+// Whether a commit launch of n_layers layers reads and writes past the caches, and a read-back of `blocks` a layer reads past them.
+bool commit_streams(const ifx_kv_cache *c, int n_layers)
+{
+    return ifx::commit_streams((int64_t)n_layers * c->n * c->heads * c->head_dim * 2 * (int64_t)(c->io_elem() + c->elem));
+}
+bool read_streams(const ifx_kv_cache *c, int64_t blocks)
+{
+    return ifx::read_streams(blocks * c->layers * c->n * c->heads * c->head_dim * 2 * (int64_t)c->elem);
+}
+
 // fp32, one launch for the blocks of layers [first_layer, first_layer + n_layers), n_layers <= COMMIT_MAX_LAYERS.
 int launch_store_blocks_f32(ifx_kv_cache *c, int first_layer, int n_layers, const void *const *k_blks, const void *const *v_blks, hipStream_t s)
 {
@@ -361,7 +371,7 @@ int launch_store_blocks_f32(ifx_kv_cache *c, int first_layer, int n_layers, cons
         args.l[i] = ifx::commit_layer{k_blks[i], v_blks[i], c->k_of(layer), c->v_of(layer), nullptr, slot * c->n, (int)slot};
     }
     const int parts = f32_copy_parts(c, (int64_t)c->heads * 2 * n_layers);
-    hipLaunchKernelGGL(ifx::store_block_f32_kernel, dim3((unsigned)(c->heads * parts), (unsigned)(2 * n_layers)), dim3(256), 0, s, args, (int)c->n,
+    hipLaunchKernelGGL(commit_streams(c, n_layers) ? ifx::store_block_f32_kernel<true> : ifx::store_block_f32_kernel<false>, dim3((unsigned)(c->heads * parts), (unsigned)(2 * n_layers)), dim3(256), 0, s, args, (int)c->n,
                        c->heads, c->head_dim / 4, c->k_tokens, parts);
     IFX_HIP(hipGetLastError());
     return IFX_OK;
@@ -385,12 +395,11 @@ int launch_store_blocks_bf16(ifx_kv_cache *c, int first_layer, int n_layers, con
         args.l[i] = ifx::commit_layer{k_blks[i], v_blks[i], c->k_of(layer), c->v_of(layer), c->knorm_of(layer), slot * n, (int)slot};
     }
     const dim3 grid((unsigned)(H * c->parts + v_blocks), (unsigned)n_layers);
-    if (c->dtype == IFX_FP8_E4M3)
-        hipLaunchKernelGGL((ifx::store_block_bf16_kernel<4, true>), grid, dim3(256), 0, s, args, n, H, c->k_tokens, c->v_tokens, c->parts,
-                           (int)c->stride_blocks);
-    else
-        hipLaunchKernelGGL((ifx::store_block_bf16_kernel<4, false>), grid, dim3(256), 0, s, args, n, H, c->k_tokens, c->v_tokens, c->parts,
-                           (int)c->stride_blocks);
+    const bool fp8 = c->dtype == IFX_FP8_E4M3, stream = commit_streams(c, n_layers);
+    void (*const kernel)(const ifx::commit_layers, int64_t, int, int64_t, int64_t, int, int) =
+        fp8 ? stream ? ifx::store_block_bf16_kernel<4, true, true> : ifx::store_block_bf16_kernel<4, true, false>
+            : stream ? ifx::store_block_bf16_kernel<4, false, true> : ifx::store_block_bf16_kernel<4, false, false>;
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, args, n, H, c->k_tokens, c->v_tokens, c->parts, (int)c->stride_blocks);
     IFX_HIP(hipGetLastError());
     return IFX_OK;
 }
@@ -1265,6 +1274,7 @@ int ifx_kv_cache_read(const ifx_kv_cache *c, int layer, void *k_out, void *v_out
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int n = (int)c->n, H = c->heads;
     const size_t blk_bytes = (size_t)c->n * H * c->head_dim * c->io_elem();
+    const bool stream_past = read_streams(c, ring.resident());
     // block b of the order asked for comes from slot slot_of_logical(b) or b
     for (int64_t done = 0; done < ring.resident();) {
         const int count = (int)(ring.resident() - done < ifx::READ_MAX_BLOCKS ? ring.resident() - done : ifx::READ_MAX_BLOCKS);
@@ -1275,15 +1285,14 @@ int ifx_kv_cache_read(const ifx_kv_cache *c, int layer, void *k_out, void *v_out
         if (c->mfma()) {
             const int v_blocks = grid_for((c->n / 8) * H * 2, 16, 2048);  // as in the commit
             const dim3 grid((unsigned)(H * c->parts + v_blocks), (unsigned)count);
-            if (c->dtype == IFX_FP8_E4M3)
-                hipLaunchKernelGGL((ifx::read_blocks_bf16_kernel<4, true>), grid, dim3(256), 0, s, c->k_of(layer), c->v_of(layer), kd, vd, slots, n,
-                                   H, c->k_tokens, c->v_tokens, c->parts);
-            else
-                hipLaunchKernelGGL((ifx::read_blocks_bf16_kernel<4, false>), grid, dim3(256), 0, s, c->k_of(layer), c->v_of(layer), kd, vd, slots,
-                                   n, H, c->k_tokens, c->v_tokens, c->parts);
+            const bool fp8 = c->dtype == IFX_FP8_E4M3;
+            void (*const kernel)(const void *, const void *, u32x4 *, u32x4 *, const ifx::read_slots, int, int, int64_t, int64_t, int) =
+                fp8 ? stream_past ? ifx::read_blocks_bf16_kernel<4, true, true> : ifx::read_blocks_bf16_kernel<4, true, false>
+                    : stream_past ? ifx::read_blocks_bf16_kernel<4, false, true> : ifx::read_blocks_bf16_kernel<4, false, false>;
+            hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, c->k_of(layer), c->v_of(layer), kd, vd, slots, n, H, c->k_tokens, c->v_tokens, c->parts);
         } else {
             const int parts = f32_copy_parts(c, (int64_t)H * 2 * count);
-            hipLaunchKernelGGL(ifx::read_blocks_f32_kernel, dim3((unsigned)(H * parts), (unsigned)(2 * count)), dim3(256), 0, s,
+            hipLaunchKernelGGL(stream_past ? ifx::read_blocks_f32_kernel<true> : ifx::read_blocks_f32_kernel<false>, dim3((unsigned)(H * parts), (unsigned)(2 * count)), dim3(256), 0, s,
                                reinterpret_cast<const u32x4 *>(c->k_of(layer)), reinterpret_cast<const u32x4 *>(c->v_of(layer)), kd, vd, slots, n, H,
                                c->head_dim / 4, c->k_tokens, parts);
         }

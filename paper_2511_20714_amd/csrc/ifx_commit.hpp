@@ -10,22 +10,37 @@
 
 namespace ifx {
 
-// What streams past the caches (non-temporal accesses).  A commit's source has been used for the last time, and its
-// destination, next read by the attention call after it, is most of it dirty in the L2s when the kernel ends, which then write
-// it back: both stream (plain, then streaming: a block of 4680 tokens x 12 heads 14.3 -> 12.6 us, of 1560 6.7 -> 5.9, 30 layers
-// 315 -> 297 and 103 -> 94; into fp8 11.6 -> 10.0, 225 -> 212; attention, commit, attention the same as before within 2 %).
-// A read-back's source is read once; what it writes is what its caller reads next, which a streaming store would
-// send to memory first (read-back and a copy of it 23.8 us, 27.3 with streaming stores, 23.4 with streaming loads alone;
-// the read-back alone 14.2, 12.2, 13.5): loads only.  The same holds for merge_kernel, which reads results just written: neither.
-template <typename T>
-__device__ __forceinline__ T load_once(const T *p)
+// What streams past the caches (non-temporal accesses, STREAM).  Plain stores leave a commit's destination in the caches,
+// where the attention call after it finds it, and its source stays there for whoever reads it again.  Only of what the
+// memory-side cache cannot hold is nothing found later, and there the dirty lines are in the way: commits that move more
+// than it holds (commit_streams) stream on both sides.  us, plain -> streaming, above the line: 30 layers of 4680 tokens x 12
+// heads 315 -> 297, fp32 20 layers of 2000 x 8 committed and read back 301 -> 276, attention and commit of 10 layers of
+// 3600 x 12 1631 -> 1615, of 6 of 1560 x 40 and of 30 of 1560 x 12 level; below it, attention and commit: 4 layers of 480 x 12
+// 77.6 -> 85.0, 2 of 776 x 8 38.5 -> 40.5, 2 of 1560 x 24 195 -> 204, 12 of 720 x 20 498 -> 509.
+// A read-back's source streams where the caches will not have kept it, because what the layers hold, and as much that
+// it was made from, is more (read_streams): 8 layers of 4680 x 12 committed and read back 195 -> 178 us, 30 711 -> 678; 4,
+// below the line, 81.5 -> 86.  What a read-back or a merge writes is what its caller reads next: never (read-back and a copy of
+// it 23.8 us, 27.3 with streaming stores).
+// The line lies a little above the cache's 256 MiB: 5 layers of 4680 x 12 (274 MiB) committed and read back 111 -> 113, 6
+// (329) 148 -> 135, fp32 10 of 2000 x 8 (313) 143 -> 137.
+constexpr int64_t STREAM_FROM = (int64_t)300 << 20;
+inline bool commit_streams(int64_t bytes_read_and_written) { return bytes_read_and_written > STREAM_FROM; }
+inline bool read_streams(int64_t bytes_all_layers_hold) { return 2 * bytes_all_layers_hold > STREAM_FROM; }
+template <bool STREAM, typename T>
+__device__ __forceinline__ T load_from(const T *p)
 {
-    return __builtin_nontemporal_load(p);
+    if constexpr (STREAM)
+        return __builtin_nontemporal_load(p);
+    else
+        return *p;
 }
-template <typename T>
-__device__ __forceinline__ void store_past(T *p, const T &v)
+template <bool STREAM, typename T>
+__device__ __forceinline__ void store_to(T *p, const T &v)
 {
-    __builtin_nontemporal_store(v, p);
+    if constexpr (STREAM)
+        __builtin_nontemporal_store(v, p);
+    else
+        *p = v;
 }
 
 // Rows of one head, 16-byte chunk by chunk: token t's row of `cpr` chunks from src + t * src_stride to
@@ -33,27 +48,24 @@ __device__ __forceinline__ void store_past(T *p, const T &v)
 // 256 / cpr rows a round, U rounds in flight; the split of a thread's number into (row, chunk) is
 // done once, so the loop is loads, stores and additions (a flat index divided by the row and head
 // counts in 64 bits for every chunk: 15 layers of 4680 x 12 x 128 committed in 372 us, now 337).
-template <int U, bool COMMIT>
+template <int U, bool STREAM, bool COMMIT>
 __device__ __forceinline__ void copy_rows_body(const u32x4 *__restrict__ src, int64_t src_stride, u32x4 *__restrict__ dst, int64_t dst_stride,
                                                int t0, int t_end, int cpr)
 {
     const int r = (int)threadIdx.x / cpr, c = (int)threadIdx.x - r * cpr, rows = 256 / cpr;
     if (r >= rows) return;
     auto put = [&](int t, const u32x4 &v) {
-        if constexpr (COMMIT)
-            store_past(dst + (int64_t)t * dst_stride + c, v);
-        else
-            dst[(int64_t)t * dst_stride + c] = v;
+        store_to<STREAM && COMMIT>(dst + (int64_t)t * dst_stride + c, v);
     };
     int t = t0 + r;
     for (; t + (U - 1) * rows < t_end; t += U * rows) {
         u32x4 v[U];
 #pragma unroll
-        for (int k = 0; k < U; ++k) v[k] = load_once(src + (int64_t)(t + k * rows) * src_stride + c);
+        for (int k = 0; k < U; ++k) v[k] = load_from<STREAM>(src + (int64_t)(t + k * rows) * src_stride + c);
 #pragma unroll
         for (int k = 0; k < U; ++k) put(t + k * rows, v[k]);
     }
-    for (; t < t_end; t += rows) put(t, load_once(src + (int64_t)t * src_stride + c));
+    for (; t < t_end; t += rows) put(t, load_from<STREAM>(src + (int64_t)t * src_stride + c));
 }
 
 // Largest squared key norms: knorm[head][slot][part] = float bits of max_t |k[t,head,:]|^2 over
@@ -135,7 +147,7 @@ __device__ __forceinline__ float e4m3x8_sumsq(const u32x2 &c)
 // h, chunk = ceil(n / parts); 16 tokens per round, one per 16-lane group, U rounds in flight.  The
 // workgroup writes one contiguous piece of the head's region; the H workgroups of a part read
 // neighbouring rows of the source at about the same time.
-template <int U, bool FP8>
+template <int U, bool FP8, bool STREAM>
 __device__ __forceinline__ void k_rows_norm_body(int h, int p, int parts, uint32_t *group_max, const u32x4 *__restrict__ src,
                                                  void *__restrict__ dst, int64_t n, int H, int64_t dst_tokens,
                                                  int64_t tok0, uint32_t *__restrict__ knorm_entry)
@@ -156,10 +168,10 @@ __device__ __forceinline__ void k_rows_norm_body(int h, int p, int parts, uint32
         float ss;
         if constexpr (FP8) {
             const u32x2 codes = bf16x8_to_e4m3(v);
-            store_past(drow8 + (int64_t)tok * 16, codes);
+            store_to<STREAM>(drow8 + (int64_t)tok * 16, codes);
             ss = e4m3x8_sumsq(codes);
         } else {
-            store_past(drow + (int64_t)tok * 16, v);
+            store_to<STREAM>(drow + (int64_t)tok * 16, v);
             ss = bf16x2_sumsq(v[0]) + bf16x2_sumsq(v[1]) + bf16x2_sumsq(v[2]) + bf16x2_sumsq(v[3]);
         }
         const uint32_t tot = __builtin_bit_cast(uint32_t, row16_sum_to_lane15(ss)) & 0x7fffffffu;
@@ -168,11 +180,11 @@ __device__ __forceinline__ void k_rows_norm_body(int h, int p, int parts, uint32
     for (; t + (U - 1) * 16 < t_end; t += U * 16) {
         u32x4 v[U];
 #pragma unroll
-        for (int k = 0; k < U; ++k) v[k] = load_once(srow + (int64_t)(t + k * 16) * H * 16);
+        for (int k = 0; k < U; ++k) v[k] = load_from<STREAM>(srow + (int64_t)(t + k * 16) * H * 16);
 #pragma unroll
         for (int k = 0; k < U; ++k) put(t + k * 16, v[k]);
     }
-    for (; t < t_end; t += 16) put(t, load_once(srow + (int64_t)t * H * 16));
+    for (; t < t_end; t += 16) put(t, load_from<STREAM>(srow + (int64_t)t * H * 16));
     if (c == 15) group_max[g] = best;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -194,7 +206,7 @@ constexpr int V_UNIT_LDS = 8 * 144;
 typedef short commit_s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) commit_s16x4 *commit_lds_s16x4_ptr;
 // FP8: the 16 bytes become 8 E4M3 codes, granules [H][v_tokens/8][128][8] of one byte each.
-template <int U, bool FP8>
+template <int U, bool FP8, bool STREAM>
 __device__ __forceinline__ void v_to_granules_body(int bid, int nblocks, unsigned char *lds, const u32x4 *__restrict__ src,
                                                    void *__restrict__ dst, int64_t n, int H, int64_t v_tokens, int64_t tok0)
 {
@@ -212,7 +224,7 @@ __device__ __forceinline__ void v_to_granules_body(int bid, int nblocks, unsigne
             const int u = u0 + k * stride;
             if (u < units) {
                 const int half = u & 1, h = (u >> 1) % H, g = (u >> 1) / H;
-                v[k] = load_once(src + (((int64_t)g * 8 + (lane >> 3)) * H + h) * 16 + half * 8 + (lane & 7));
+                v[k] = load_from<STREAM>(src + (((int64_t)g * 8 + (lane >> 3)) * H + h) * 16 + half * 8 + (lane & 7));
             }
         }
 #pragma unroll
@@ -229,9 +241,9 @@ __device__ __forceinline__ void v_to_granules_body(int bid, int nblocks, unsigne
                 const s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
                 const int64_t at = ((int64_t)h * gran_per_head + g0 + g) * 128 + half * 64 + lane;
                 if constexpr (FP8)
-                    store_past(static_cast<u32x2 *>(dst) + at, bf16x8_to_e4m3(__builtin_bit_cast(u32x4, both)));
+                    store_to<STREAM>(static_cast<u32x2 *>(dst) + at, bf16x8_to_e4m3(__builtin_bit_cast(u32x4, both)));
                 else
-                    store_past(static_cast<u32x4 *>(dst) + at, __builtin_bit_cast(u32x4, both));
+                    store_to<STREAM>(static_cast<u32x4 *>(dst) + at, __builtin_bit_cast(u32x4, both));
             }
         }
     }
@@ -254,7 +266,7 @@ struct commit_layers {
 // workgroups the first H * parts copy K (workgroup p * H + h: head h, part p) and take the key
 // norms, the rest turn V into granules.
 // FP8: the cache holds E4M3 codes (the source blocks are bf16 either way).
-template <int U, bool FP8>
+template <int U, bool FP8, bool STREAM>
 __global__ __launch_bounds__(256) void store_block_bf16_kernel(const commit_layers layers, int64_t n, int H, int64_t k_tokens,
                                                               int64_t v_tokens, int parts, int cap_blocks)
 {
@@ -264,16 +276,17 @@ __global__ __launch_bounds__(256) void store_block_bf16_kernel(const commit_laye
     const int k_blocks = H * parts;
     if ((int)blockIdx.x < k_blocks) {
         const int h = (int)blockIdx.x % H, p = (int)blockIdx.x / H;
-        k_rows_norm_body<U, FP8>(h, p, parts, group_max, (const u32x4 *)L.k_src, L.k_dst, n, H, k_tokens, L.tok0,
+        k_rows_norm_body<U, FP8, STREAM>(h, p, parts, group_max, (const u32x4 *)L.k_src, L.k_dst, n, H, k_tokens, L.tok0,
                                  L.knorm + ((int64_t)h * cap_blocks + L.slot) * parts + p);
     } else {
-        v_to_granules_body<U, FP8>((int)blockIdx.x - k_blocks, (int)gridDim.x - k_blocks, v_lds, (const u32x4 *)L.v_src, L.v_dst, n, H,
+        v_to_granules_body<U, FP8, STREAM>((int)blockIdx.x - k_blocks, (int)gridDim.x - k_blocks, v_lds, (const u32x4 *)L.v_src, L.v_dst, n, H,
                                    v_tokens, L.tok0);
     }
 }
 
 // The same for fp32 caches, K and V alike plain rows: grid (H * parts, 2 * layers), workgroup
 // p * H + h of (layer, K or V) copies part p of head h's tokens.
+template <bool STREAM>
 __global__ __launch_bounds__(256) void store_block_f32_kernel(const commit_layers layers, int n, int H, int cpr, int64_t cache_tokens, int parts)
 {
     const commit_layer &L = layers.l[blockIdx.y >> 1];
@@ -281,14 +294,14 @@ __global__ __launch_bounds__(256) void store_block_f32_kernel(const commit_layer
     const int h = (int)blockIdx.x % H, p = (int)blockIdx.x / H;
     const int chunk = (n + parts - 1) / parts;
     const int t0 = p * chunk, t_end = n - t0 < chunk ? n : t0 + chunk;
-    copy_rows_body<4, true>((const u32x4 *)(is_v ? L.v_src : L.k_src) + (int64_t)h * cpr, (int64_t)H * cpr,
+    copy_rows_body<4, STREAM, true>((const u32x4 *)(is_v ? L.v_src : L.k_src) + (int64_t)h * cpr, (int64_t)H * cpr,
                       (u32x4 *)(is_v ? L.v_dst : L.k_dst) + ((int64_t)h * cache_tokens + L.tok0) * cpr, cpr, t0, t_end, cpr);
 }
 
 // ---- read-back: resident blocks to the caller's [tokens, H, head_dim] tensors ------------------
 // Bound by HBM, like the commit whose mirror it is: one launch for K and V of up to READ_MAX_BLOCKS
 // blocks (grid y), entry b from physical slot slot[b] to the b-th block of the output.
-// One 4680-token block of 12 heads: 13.5 us (57.5 MB moved, 4.3 TB/s; 30 such commits in one launch
+// One 4680-token block of 12 heads, one of 30 layers': 13.5 us (57.5 MB moved, 4.3 TB/s; 30 such commits in one launch
 // run at 5.8), 26.9 with a launch each for K and V, 64-bit divisions for every chunk and V gathered
 // by 2-byte loads.  10800 tokens of 40 heads: 165 -> 92 us (4.8 TB/s).
 constexpr int READ_MAX_BLOCKS = 64;
@@ -296,6 +309,7 @@ struct read_slots {
     int slot[READ_MAX_BLOCKS];
 };
 
+template <bool STREAM>
 __global__ __launch_bounds__(256) void read_blocks_f32_kernel(const u32x4 *__restrict__ k_region, const u32x4 *__restrict__ v_region,
                                                              u32x4 *__restrict__ k_dst, u32x4 *__restrict__ v_dst, const read_slots slots, int n,
                                                              int H, int cpr, int64_t cache_tokens, int parts)
@@ -305,7 +319,7 @@ __global__ __launch_bounds__(256) void read_blocks_f32_kernel(const u32x4 *__res
     const int h = (int)blockIdx.x % H, p = (int)blockIdx.x / H;
     const int chunk = (n + parts - 1) / parts;
     const int t0 = p * chunk, t_end = n - t0 < chunk ? n : t0 + chunk;
-    copy_rows_body<4, false>((is_v ? v_region : k_region) + ((int64_t)h * cache_tokens + (int64_t)slots.slot[b] * n) * cpr, cpr,
+    copy_rows_body<4, STREAM, false>((is_v ? v_region : k_region) + ((int64_t)h * cache_tokens + (int64_t)slots.slot[b] * n) * cpr, cpr,
                       (is_v ? v_dst : k_dst) + ((int64_t)b * n * H + h) * cpr, (int64_t)H * cpr, t0, t_end, cpr);
 }
 
@@ -330,7 +344,7 @@ __device__ __forceinline__ u32x4 e4m3x8_to_bf16(const u32x2 &c)
 // 16-byte store per lane, 8 rows of 128 contiguous bytes.  Every 16 dimensions start 64 bytes
 // further, so the pieces a read gathers lie in different banks.  LDS: 4 * U * V_READ_LDS bytes.
 constexpr int V_READ_LDS = 64 * 16 + 3 * 64;
-template <int U, bool FP8>
+template <int U, bool FP8, bool STREAM>
 __global__ __launch_bounds__(256) void read_blocks_bf16_kernel(const void *__restrict__ k_region, const void *__restrict__ v_region,
                                                               u32x4 *__restrict__ k_dst, u32x4 *__restrict__ v_dst, const read_slots slots, int n,
                                                               int H, int64_t k_tokens, int64_t v_tokens, int parts)
@@ -355,11 +369,11 @@ __global__ __launch_bounds__(256) void read_blocks_bf16_kernel(const void *__res
         for (; t + (U - 1) * 16 < t_end; t += U * 16) {
             stored v[U];
 #pragma unroll
-            for (int k = 0; k < U; ++k) v[k] = load_once(srow + (int64_t)(t + k * 16) * 16);
+            for (int k = 0; k < U; ++k) v[k] = load_from<STREAM>(srow + (int64_t)(t + k * 16) * 16);
 #pragma unroll
             for (int k = 0; k < U; ++k) drow[(int64_t)(t + k * 16) * H * 16] = as_bf16(v[k]);
         }
-        for (; t < t_end; t += 16) drow[(int64_t)t * H * 16] = as_bf16(load_once(srow + (int64_t)t * 16));
+        for (; t < t_end; t += 16) drow[(int64_t)t * H * 16] = as_bf16(load_from<STREAM>(srow + (int64_t)t * 16));
         return;
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -377,7 +391,7 @@ __global__ __launch_bounds__(256) void read_blocks_bf16_kernel(const void *__res
             const int u = u0 + k * stride;
             if (u < units) {
                 const int half = u & 1, h = (u >> 1) % H, gr = (u >> 1) / H;
-                v[k] = load_once(static_cast<const stored *>(v_region) + ((int64_t)h * gran_per_head + g0 + gr) * 128 + half * 64 + lane);
+                v[k] = load_from<STREAM>(static_cast<const stored *>(v_region) + ((int64_t)h * gran_per_head + g0 + gr) * 128 + half * 64 + lane);
             }
         }
 #pragma unroll

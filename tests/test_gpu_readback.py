@@ -53,3 +53,32 @@ def test_read_back_at_the_edges(gpu_device, dtype, n, H, D, cap, commits):
                     want_k, want_v = want_k.tobytes(), want_v.tobytes()
                 assert synth.raw_bytes(k[:C]) == want_k and synth.raw_bytes(v[:C]) == want_v, (layer, logical)
                 assert (k[C:] == 7.0).all() and (v[C:] == 7.0).all()
+
+
+@pytest.mark.parametrize("dtype,n,H,D,L,cap", [
+    (ifx.IFX_BF16, 1032, 9, 128, 34, 2),
+    (ifx.IFX_FP8_E4M3, 1032, 9, 128, 45, 3),
+    (ifx.IFX_F32, 1033, 9, 40, 54, 2),      # rows of 10 chunks; ragged last round
+])
+def test_copies_past_the_caches(gpu_device, dtype, n, H, D, L, cap):
+    """A commit that moves more than 300 MiB, and a read-back of layers that together hold more than half of that, stream: bit
+    for bit what one layer's commits and read-back, which do not, leave."""
+    dev = gpu_device
+    tdtype = TORCH_DTYPE.get(dtype, torch.bfloat16)
+    io, held = (4, 4) if dtype == ifx.IFX_F32 else (2, 1 if dtype == ifx.IFX_FP8_E4M3 else 2)
+    assert L * n * H * D * 2 * (io + held) > 300 << 20 and L * cap * n * H * D * 2 * held > 150 << 20
+    blocks = [[synth.draw_qkv(23, b, 0, layer, n, H, D, tdtype, dev)[1:] for layer in range(L)] for b in range(2)]
+    order = [0, 1] * cap  # more commits than the ring holds
+    with ifx.KVCache(L, H, D, cap * n, n, dtype) as cache, ifx.KVCache(1, H, D, cap * n, n, dtype) as one:
+        for b in order[:cap + 1]:
+            cache.commit_layers(0, [k for k, _ in blocks[b]], [v for _, v in blocks[b]])
+        for layer in (0, 1, L - 1):
+            one.reset()
+            for b in order[:cap + 1]:
+                one.commit(0, *blocks[b][layer])
+            got, want = ([torch.full((cap * n + 2, H, D), 7.0, dtype=tdtype, device=dev) for _ in range(2)] for _ in range(2))
+            cache.read(layer, *(t[:cap * n] for t in got))
+            one.read(0, *(t[:cap * n] for t in want))
+            torch.cuda.synchronize()
+            for g, w in zip(got, want):
+                assert synth.raw_bytes(g) == synth.raw_bytes(w), layer
