@@ -1095,7 +1095,7 @@ static int attention_impl(ifx_kv_cache *c, int layer, const void *q, const void 
     IFX_HIP(hipGetLastError());
     if (plan.parts > 1) {
         const ifx::combine_args b = {partial, stats, static_cast<__bf16 *>(out), lse, n, H, ifx::attn_split_for(n, H, plan)};
-        hipLaunchKernelGGL(ifx::combine_kernel, dim3((unsigned)(4 * b.split.row_tiles * (H - plan.whole_heads))), dim3(64 * ifx::combine_waves(plan.parts)), 0,
+        hipLaunchKernelGGL(ifx::combine_kernel_of(plan.parts), dim3((unsigned)(4 * b.split.row_tiles * (H - plan.whole_heads))), dim3(64 * ifx::combine_waves(plan.parts)), 0,
                            s, b);
         IFX_HIP(hipGetLastError());
     }

@@ -20,11 +20,20 @@ struct combine_args {
     attn_split split;
 };
 
-constexpr int COMBINE_MOST_WAVES = 4;
-inline int combine_waves(int parts) { return parts < COMBINE_MOST_WAVES ? parts : COMBINE_MOST_WAVES; }
+constexpr int COMBINE_MOST_WAVES = 4, COMBINE_MOST_BATCH = 4;
+inline int combine_waves(int parts) { return parts <= COMBINE_MOST_BATCH ? 1 : COMBINE_MOST_WAVES; }
+inline int combine_batch(int parts)
+{
+    const int each = (parts + combine_waves(parts) - 1) / combine_waves(parts);
+    return each < COMBINE_MOST_BATCH ? each : COMBINE_MOST_BATCH;
+}
 
-// A workgroup = one slab of 32 dimensions of one unit's 32 rows, the parts dealt to its wavefronts; lanes
-// hold what the accumulators held.  The sums are taken in a fixed order, whichever workgroup finished first.
+// A workgroup = one slab of 32 dimensions of one unit's 32 rows, the parts dealt to its wavefronts (up to four: one
+// wavefront, which exchanges nothing); lanes hold what the accumulators held.  BATCH: parts that a wavefront has on their way at
+// once, as many as it takes (four of every wavefront's one or two before, some loaded four times: 30 layers of 1560 x 12 x 10920
+// 3260 -> 3245 us, 800 x 12 x 6400 43.4 -> 42.9, 400 x 2 x 3200 13.1 -> 13.0, x 1 12.4 -> 12.2).  Streaming the partial results past
+// the caches gains nothing.  The sums are taken in a fixed order, whichever workgroup finished first.
+template <int BATCH>
 __global__ __launch_bounds__(64 * COMBINE_MOST_WAVES) void combine_kernel(const combine_args a)
 {
     __shared__ float shared[COMBINE_MOST_WAVES - 1][19][64];
@@ -48,7 +57,6 @@ __global__ __launch_bounds__(64 * COMBINE_MOST_WAVES) void combine_kernel(const 
 #pragma unroll
         for (int r = 0; r < 16; ++r) R[r] = w * R[r] + w_other * value(r);
     };
-    constexpr int BATCH = 4;  // parts on their way at once
     for (int p0 = wave; p0 < a.split.parts; p0 += BATCH * waves) {
         f32x4 v[BATCH][4];
         f32x4 ml[BATCH];
@@ -77,6 +85,16 @@ __global__ __launch_bounds__(64 * COMBINE_MOST_WAVES) void combine_kernel(const 
     if (a.lse != nullptr && sl == 0 && lh == 0 && qi < a.n)
         a.lse[(int64_t)qi * a.H + head] = (m + __builtin_amdgcn_logf(sum_e)) * 0.6931471805599453f;
     store_slab(a.out + ((int64_t)(qi < a.n ? qi : a.n - 1) * a.H + head) * BF_D + 32 * sl, R, 1.0f / l, lh, qi < a.n);
+}
+
+inline void (*combine_kernel_of(int parts))(const combine_args)
+{
+    switch (combine_batch(parts)) {
+    case 1: return combine_kernel<1>;
+    case 2: return combine_kernel<2>;
+    case 3: return combine_kernel<3>;
+    default: return combine_kernel<4>;
+    }
 }
 
 }  // namespace ifx
