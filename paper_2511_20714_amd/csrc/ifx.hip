@@ -157,15 +157,17 @@ f32_kernel_t f32_kernel(int D, bool gather, bool split)
     default: return f32_kernel_of<128>(gather, split);
     }
 }
-f32_kernel_t f32_combine(int D)
+template <int BATCH>
+f32_kernel_t f32_combine_of(int D)
 {
     switch (f32_padded_dim(D)) {
-    case 32: return ifx::combine_f32_kernel<32>;
-    case 64: return ifx::combine_f32_kernel<64>;
-    case 96: return ifx::combine_f32_kernel<96>;
-    default: return ifx::combine_f32_kernel<128>;
+    case 32: return ifx::combine_f32_kernel<32, BATCH>;
+    case 64: return ifx::combine_f32_kernel<64, BATCH>;
+    case 96: return ifx::combine_f32_kernel<96, BATCH>;
+    default: return ifx::combine_f32_kernel<128, BATCH>;
     }
 }
+f32_kernel_t f32_combine(int D, int parts) { return parts <= 4 ? f32_combine_of<4>(D) : f32_combine_of<8>(D); }
 
 // bf16 attention: the instance for a block table or none, an fp8 or a bf16 cache, one or two key groups, heads
 // whose keys are dealt to several workgroups (one key group) or not.
@@ -1089,7 +1091,9 @@ static int attention_impl(ifx_kv_cache *c, int layer, const void *q, const void 
         }
         if (parts > 1) {
             IFX_HIP(hipGetLastError());
-            hipLaunchKernelGGL(f32_combine(D), dim3((unsigned)(((int64_t)n * H * (D / 4) + 255) / 256)), dim3(256), 0, s, a);
+            const int64_t threads = (int64_t)n * H * (D / 4);
+            hipLaunchKernelGGL(f32_combine(D, parts), dim3((unsigned)((threads + ifx::COMBINE_F32_THREADS - 1) / ifx::COMBINE_F32_THREADS)),
+                               dim3(ifx::COMBINE_F32_THREADS), 0, s, a);
         }
     }
     IFX_HIP(hipGetLastError());

@@ -68,10 +68,10 @@ struct attn_f32_args {
 inline int attn_f32_waves(int64_t workgroups) { return workgroups <= 256 ? 8 : 4; }
 
 // Workgroups per row tile that a call's `subs` subtiles of keys are dealt to; a second launch puts their results together
-// (combine_f32_kernel; 5 us, and more as the parts' results grow).  Worth it where row tiles leave CUs, or a CU's
+// (combine_f32_kernel; 3 us, and more as the parts' results grow).  Worth it where row tiles leave CUs, or a CU's
 // slots, empty over a long key run: up to 128 row tiles one workgroup of 8 wavefronts per CU; up to 480 five parts, whose
 // workgroups of 4 fill three slots a CU; up to 700, where some CUs have two workgroups and some three, three parts.
-// Measured, whole and in parts (us): 256 rows x 2 heads x 64, 1024 keys 16.5, 11.8; 2048 keys 27.7, 13.6; 400 x 4 x
+// Measured, whole and in parts (us, with a second launch that took 5): 256 rows x 2 heads x 64, 1024 keys 16.5, 11.8 (now 9.6); 2048 keys 27.7, 13.6; 400 x 4 x
 // 128, 2000 keys 46.2, 29.8; 1560 x 1 x 128, 7800 keys 153, 75; 1560 x 2 x 128, 7800 156, 134; 1040 x 4 x 128, 5200 204,
 // 132; 1560 x 4 x 128, 4680 186, 160; 1560 x 6 x 128, 4680 262, 221; but 1560 x 5 188, 197 and 1560 x 7 263, 274; 64 x 1 x
 // 128, 320 keys 11.7, 12.1; 200 x 30 x 128, 1000 keys 48, 51.  Below: both sides' times (us) as fitted to these.
@@ -429,25 +429,48 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(GATHER ? 2 
 }
 
 // out = sum_p f_p O_p / sum_p f_p l_p, f_p = exp(m_p - max m), parts in their order.  A thread: 4 dimensions of a row.
-template <int DP>
-__global__ __launch_bounds__(256) void combine_f32_kernel(const attn_f32_args a)
+// Bound by latency: references, sums and results of BATCH parts are on their way at once (the references were read
+// one after another before the first result was asked for), and workgroups are single wavefronts, which reach more CUs
+// where rows are few.  Whole calls (us): 256 rows x 2 heads x 64, 1024 keys 11.5 -> 9.6, 200 x 1 x 96, 1000 keys 14.0 -> 11.7, 256 x
+// 8 x 72, 1024 keys 17.9 -> 17.0, 1560 x 12 x 128, 3120 keys 157.7 -> 156.0.  BATCH: 4 for up to four parts (with 8: 17.2 and 25.6
+// instead of 17.0 and 25.4 on 256 x 8 x 72 and 512 x 4 x 128), 8 beyond (with 4: 10.6 and 12.4 on the first two).
+constexpr int COMBINE_F32_THREADS = 64;
+template <int DP, int BATCH>
+__global__ __launch_bounds__(COMBINE_F32_THREADS) void combine_f32_kernel(const attn_f32_args a)
 {
-    const int chunks = a.D / 4, tile_rows = a.tiles.tiles * F32_ROWS;
-    const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t row = g / chunks;  // head-major
-    const int c = (int)(g - row * chunks), h = (int)(row / a.n), i = (int)(row - (int64_t)h * a.n);
-    if (h >= a.H) return;
+    // (parts have rows for the area of one stream to hold: far below 2^32 threads)
+    const unsigned chunks = (unsigned)a.D / 4u, tile_rows = (unsigned)(a.tiles.tiles * F32_ROWS);
+    const unsigned g = blockIdx.x * COMBINE_F32_THREADS + threadIdx.x;
+    const unsigned row = g / chunks;  // head-major
+    const unsigned c = g - row * chunks, h = row / (unsigned)a.n, i = row - h * (unsigned)a.n;
+    if (h >= (unsigned)a.H) return;
     const int64_t first = (int64_t)h * a.parts * tile_rows + i;
+    f32x2 ml[BATCH];
+    f32x4 v[BATCH];
+    auto load = [&](int p0) {  // (past the last part: that one again, not used)
+        auto at = [&](int b) -> int64_t { return first + (int64_t)(p0 + b < a.parts ? p0 + b : a.parts - 1) * tile_rows; };
+#pragma unroll
+        for (int b = 0; b < BATCH; ++b) ml[b] = a.stats[at(b)];
+#pragma unroll
+        for (int b = 0; b < BATCH; ++b) v[b] = *reinterpret_cast<const f32x4 *>(a.partial + at(b) * DP + 4 * c);
+    };
+    load(0);
     float M = -FLT_MAX, sum = 0.f;
     f32x4 o = {0.f, 0.f, 0.f, 0.f};
-    for (int p = 0; p < a.parts; ++p) M = fmaxf(M, a.stats[first + (int64_t)p * tile_rows][0]);
-#pragma unroll 4
-    for (int p = 0; p < a.parts; ++p) {
-        const int64_t at = first + (int64_t)p * tile_rows;
-        const f32x2 ml = a.stats[at];
-        const float f = expf(ml[0] - M);  // 0 for a part without a key that counts
-        sum += f * ml[1];
-        o += f * *reinterpret_cast<const f32x4 *>(a.partial + at * DP + 4 * c);
+#pragma unroll
+    for (int b = 0; b < BATCH; ++b) M = fmaxf(M, ml[b][0]);
+    for (int p = BATCH; p < a.parts; ++p) M = fmaxf(M, a.stats[first + (int64_t)p * tile_rows][0]);
+    for (int p0 = 0;;) {
+#pragma unroll
+        for (int b = 0; b < BATCH; ++b)
+            if (p0 + b < a.parts) {
+                const float f = expf(ml[b][0] - M);  // 0 for a part without a key that counts
+                sum += f * ml[b][1];
+                o += f * v[b];
+            }
+        p0 += BATCH;
+        if (p0 >= a.parts) break;
+        load(p0);
     }
     if (a.lse != nullptr && c == 0) a.lse[(int64_t)i * a.H + h] = (float)((double)M + log((double)sum));
     const float inv = 1.0f / sum;
