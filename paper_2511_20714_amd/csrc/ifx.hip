@@ -364,16 +364,19 @@ bool read_streams(const ifx_kv_cache *c, int64_t blocks)
 }
 
 // fp32, one launch for the blocks of layers [first_layer, first_layer + n_layers), n_layers <= COMMIT_MAX_LAYERS.
+template <int LAYERS>
 int launch_store_blocks_f32(ifx_kv_cache *c, int first_layer, int n_layers, const void *const *k_blks, const void *const *v_blks, hipStream_t s)
 {
-    ifx::commit_layers args = {};
+    ifx::commit_layers<LAYERS> args = {};
     for (int i = 0; i < n_layers; ++i) {
         const int layer = first_layer + i;
         const int64_t slot = c->rings[(size_t)layer].next_slot();
         args.l[i] = ifx::commit_layer{k_blks[i], v_blks[i], c->k_of(layer), c->v_of(layer), nullptr, slot * c->n, (int)slot};
     }
     const int parts = f32_copy_parts(c, (int64_t)c->heads * 2 * n_layers);
-    hipLaunchKernelGGL(commit_streams(c, n_layers) ? ifx::store_block_f32_kernel<true> : ifx::store_block_f32_kernel<false>, dim3((unsigned)(c->heads * parts), (unsigned)(2 * n_layers)), dim3(256), 0, s, args, (int)c->n,
+    void (*const kernel)(const ifx::commit_layers<LAYERS>, int, int, int, int64_t, int) =
+        commit_streams(c, n_layers) ? ifx::store_block_f32_kernel<true, LAYERS> : ifx::store_block_f32_kernel<false, LAYERS>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(c->heads * parts), (unsigned)(2 * n_layers)), dim3(256), 0, s, args, (int)c->n,
                        c->heads, c->head_dim / 4, c->k_tokens, parts);
     IFX_HIP(hipGetLastError());
     return IFX_OK;
@@ -382,6 +385,7 @@ int launch_store_blocks_f32(ifx_kv_cache *c, int first_layer, int n_layers, cons
 // bf16, one launch for the blocks of layers [first_layer, first_layer + n_layers), n_layers <=
 // COMMIT_MAX_LAYERS: each layer's K rows copied to its next slot with the block's largest key norms
 // recorded in the slot's knorm entries, its V turned into granules there.
+template <int LAYERS>
 int launch_store_blocks_bf16(ifx_kv_cache *c, int first_layer, int n_layers, const void *const *k_blks, const void *const *v_blks,
                              hipStream_t s)
 {
@@ -390,7 +394,7 @@ int launch_store_blocks_bf16(ifx_kv_cache *c, int first_layer, int n_layers, con
     // V: a wavefront turns half a granule of one head (8 tokens x 64 dimensions) at a time, 4 in
     // flight: 16 per workgroup and round
     const int v_blocks = grid_for((n / 8) * H * (D / 64), 16, 2048);
-    ifx::commit_layers args = {};
+    ifx::commit_layers<LAYERS> args = {};
     for (int i = 0; i < n_layers; ++i) {
         const int layer = first_layer + i;
         const int64_t slot = c->rings[(size_t)layer].next_slot();
@@ -398,9 +402,9 @@ int launch_store_blocks_bf16(ifx_kv_cache *c, int first_layer, int n_layers, con
     }
     const dim3 grid((unsigned)(H * c->parts + v_blocks), (unsigned)n_layers);
     const bool fp8 = c->dtype == IFX_FP8_E4M3, stream = commit_streams(c, n_layers);
-    void (*const kernel)(const ifx::commit_layers, int64_t, int, int64_t, int64_t, int, int) =
-        fp8 ? stream ? ifx::store_block_bf16_kernel<4, true, true> : ifx::store_block_bf16_kernel<4, true, false>
-            : stream ? ifx::store_block_bf16_kernel<4, false, true> : ifx::store_block_bf16_kernel<4, false, false>;
+    void (*const kernel)(const ifx::commit_layers<LAYERS>, int64_t, int, int64_t, int64_t, int, int) =
+        fp8 ? stream ? ifx::store_block_bf16_kernel<4, true, true, LAYERS> : ifx::store_block_bf16_kernel<4, true, false, LAYERS>
+            : stream ? ifx::store_block_bf16_kernel<4, false, true, LAYERS> : ifx::store_block_bf16_kernel<4, false, false, LAYERS>;
     hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, args, n, H, c->k_tokens, c->v_tokens, c->parts, (int)c->stride_blocks);
     IFX_HIP(hipGetLastError());
     return IFX_OK;
@@ -408,8 +412,12 @@ int launch_store_blocks_bf16(ifx_kv_cache *c, int first_layer, int n_layers, con
 
 int launch_store_blocks(ifx_kv_cache *c, int first_layer, int n_layers, const void *const *k_blks, const void *const *v_blks, hipStream_t s)
 {
-    return c->mfma() ? launch_store_blocks_bf16(c, first_layer, n_layers, k_blks, v_blks, s)
-                     : launch_store_blocks_f32(c, first_layer, n_layers, k_blks, v_blks, s);
+    constexpr int MOST = ifx::COMMIT_MAX_LAYERS;
+    if (c->mfma())
+        return n_layers == 1 ? launch_store_blocks_bf16<1>(c, first_layer, n_layers, k_blks, v_blks, s)
+                             : launch_store_blocks_bf16<MOST>(c, first_layer, n_layers, k_blks, v_blks, s);
+    return n_layers == 1 ? launch_store_blocks_f32<1>(c, first_layer, n_layers, k_blks, v_blks, s)
+                         : launch_store_blocks_f32<MOST>(c, first_layer, n_layers, k_blks, v_blks, s);
 }
 
 }  // namespace
