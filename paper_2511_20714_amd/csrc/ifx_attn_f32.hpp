@@ -74,7 +74,8 @@ inline int attn_f32_waves(int64_t workgroups) { return workgroups <= 256 ? 8 : 4
 // Measured, whole and in parts (us, with a second launch that took 5): 256 rows x 2 heads x 64, 1024 keys 16.5, 11.8 (now 9.6); 2048 keys 27.7, 13.6; 400 x 4 x
 // 128, 2000 keys 46.2, 29.8; 1560 x 1 x 128, 7800 keys 153, 75; 1560 x 2 x 128, 7800 156, 134; 1040 x 4 x 128, 5200 204,
 // 132; 1560 x 4 x 128, 4680 186, 160; 1560 x 6 x 128, 4680 262, 221; but 1560 x 5 188, 197 and 1560 x 7 263, 274; 64 x 1 x
-// 128, 320 keys 11.7, 12.1; 200 x 30 x 128, 1000 keys 48, 51.  Below: both sides' times (us) as fitted to these.
+// 128, 320 keys 11.7, 12.1; 200 x 30 x 128, 1000 keys 48, 51.  With the second launch at 3 us, three parts and more: 104 x 2 x 128, 416 keys
+// 14.6, 12.8; 136 x 8 x 72, 544 keys 14.2, 11.7; 256 x 2 x 96, 512 keys 13.3, 10.7; 344 x 1 x 64, 688 keys 12.3, 9.7.  Below: both sides' times (us) as fitted to these.
 inline int attn_f32_parts(int64_t workgroups, int padded_d, int64_t subs)
 {
     if (workgroups > 700) return 1;
@@ -85,10 +86,11 @@ inline int attn_f32_parts(int64_t workgroups, int padded_d, int64_t subs)
     if (workgroups <= 128) {
         int64_t p = 256 / workgroups;
         if (p > subs / 8) p = subs / 8;
-        const float split = p > 1 ? 11.f + step * (float)((subs + 8 * p - 1) / (8 * p)) : us;
+        // (three parts and more: 9.3, the second launch reading all parts at once; two of 108 tiles were 5 % behind there)
+        const float split = p > 1 ? (p > 2 ? 9.3f : 11.f) + step * (float)((subs + 8 * p - 1) / (8 * p)) : us;
         if (split < us) {
-            us = split;
             parts = (int)p;
+            if (p == 2 || split + 1.7f < us) us = p == 2 ? split : split + 1.7f;
         }
     }
     if (workgroups > 85 && subs >= 40 && 12.f + all < us) parts = workgroups <= 480 ? 5 : 3;
