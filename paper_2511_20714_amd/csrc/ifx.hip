@@ -23,6 +23,7 @@
 #include "ifx_f32_large.hpp"
 #include "ifx_commit.hpp"
 #include "ifx_ring.hpp"
+#include "ifx_stream.hpp"
 
 static_assert(IFX_MAX_KEY_BLOCKS == IFX_MAX_LISTED_BLOCKS, "block table size and its documented limit");
 
@@ -100,6 +101,7 @@ struct ifx_kv_cache {
     area areas[SPLIT_AREAS];
     std::mutex split_mutex;
     std::vector<ifx_ring> rings;
+    mutable ifx::read_history reads;
     bool profile = false;
     std::vector<event_pair> attn_events, commit_events;
 
@@ -353,14 +355,10 @@ int f32_copy_parts(const ifx_kv_cache *c, int64_t rows_of_launch)
     return (int)(most < enough ? most : enough);
 }
 
-// Whether a commit launch of n_layers layers reads and writes past the caches, and a read-back of `blocks` a layer reads past them.
-bool commit_streams(const ifx_kv_cache *c, int n_layers)
+// Bytes that a commit or a read-back of `blocks` blocks moves.
+int64_t copy_bytes(const ifx_kv_cache *c, int64_t blocks)
 {
-    return ifx::commit_streams((int64_t)n_layers * c->n * c->heads * c->head_dim * 2 * (int64_t)(c->io_elem() + c->elem));
-}
-bool read_streams(const ifx_kv_cache *c, int64_t blocks)
-{
-    return ifx::read_streams(blocks * c->layers * c->n * c->heads * c->head_dim * 2 * (int64_t)c->elem);
+    return blocks * c->n * c->heads * c->head_dim * 2 * (int64_t)(c->io_elem() + c->elem);
 }
 
 // fp32, one launch for the blocks of layers [first_layer, first_layer + n_layers), n_layers <= COMMIT_MAX_LAYERS.
@@ -375,7 +373,7 @@ int launch_store_blocks_f32(ifx_kv_cache *c, int first_layer, int n_layers, cons
     }
     const int parts = f32_copy_parts(c, (int64_t)c->heads * 2 * n_layers);
     void (*const kernel)(const ifx::commit_layers<LAYERS>, int, int, int, int64_t, int) =
-        commit_streams(c, n_layers) ? ifx::store_block_f32_kernel<true, LAYERS> : ifx::store_block_f32_kernel<false, LAYERS>;
+        ifx::commit_streams(copy_bytes(c, n_layers)) ? ifx::store_block_f32_kernel<true, LAYERS> : ifx::store_block_f32_kernel<false, LAYERS>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(c->heads * parts), (unsigned)(2 * n_layers)), dim3(256), 0, s, args, (int)c->n,
                        c->heads, c->head_dim / 4, c->k_tokens, parts);
     IFX_HIP(hipGetLastError());
@@ -401,7 +399,7 @@ int launch_store_blocks_bf16(ifx_kv_cache *c, int first_layer, int n_layers, con
         args.l[i] = ifx::commit_layer{k_blks[i], v_blks[i], c->k_of(layer), c->v_of(layer), c->knorm_of(layer), slot * n, (int)slot};
     }
     const dim3 grid((unsigned)(H * c->parts + v_blocks), (unsigned)n_layers);
-    const bool fp8 = c->dtype == IFX_FP8_E4M3, stream = commit_streams(c, n_layers);
+    const bool fp8 = c->dtype == IFX_FP8_E4M3, stream = ifx::commit_streams(copy_bytes(c, n_layers));
     void (*const kernel)(const ifx::commit_layers<LAYERS>, int64_t, int, int64_t, int64_t, int, int) =
         fp8 ? stream ? ifx::store_block_bf16_kernel<4, true, true, LAYERS> : ifx::store_block_bf16_kernel<4, true, false, LAYERS>
             : stream ? ifx::store_block_bf16_kernel<4, false, true, LAYERS> : ifx::store_block_bf16_kernel<4, false, false, LAYERS>;
@@ -708,6 +706,7 @@ int ifx_kv_cache_configure(ifx_kv_cache *c, int64_t block_tokens, int dtype, flo
             c->rings.clear();
             c->rings.reserve((size_t)c->layers);
             for (int l = 0; l < c->layers; ++l) c->rings.emplace_back(c->capacity_tokens / block_tokens);
+            host_ok = c->reads.init(c->layers);
         } catch (...) {
             host_ok = false;
         }
@@ -1105,6 +1104,7 @@ static int attention_impl(ifx_kv_cache *c, int layer, const void *q, const void 
         }
     }
     IFX_HIP(hipGetLastError());
+    if (cached > 0) c->reads.attended(layer, cached * H * D * 2 * (int64_t)c->elem);
     if (plan.parts > 1) {
         const ifx::combine_args b = {partial, stats, static_cast<__bf16 *>(out), lse, n, H, ifx::attn_split_for(n, H, plan)};
         hipLaunchKernelGGL(ifx::combine_kernel_of(plan.parts), dim3((unsigned)(4 * b.split.row_tiles * (H - plan.whole_heads))), dim3(64 * ifx::combine_waves(plan.parts)), 0,
@@ -1286,7 +1286,8 @@ int ifx_kv_cache_read(const ifx_kv_cache *c, int layer, void *k_out, void *v_out
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int n = (int)c->n, H = c->heads;
     const size_t blk_bytes = (size_t)c->n * H * c->head_dim * c->io_elem();
-    const bool stream_past = read_streams(c, ring.resident());
+    const int64_t moves = copy_bytes(c, ring.resident());
+    const bool stream_past = c->reads.read(layer, moves, moves * c->layers);
     // block b of the order asked for comes from slot slot_of_logical(b) or b
     for (int64_t done = 0; done < ring.resident();) {
         const int count = (int)(ring.resident() - done < ifx::READ_MAX_BLOCKS ? ring.resident() - done : ifx::READ_MAX_BLOCKS);

@@ -10,22 +10,7 @@
 
 namespace ifx {
 
-// What streams past the caches (non-temporal accesses, STREAM).  Plain stores leave a commit's destination in the caches,
-// where the attention call after it finds it, and its source stays there for whoever reads it again.  Only of what the
-// memory-side cache cannot hold is nothing found later, and there the dirty lines are in the way: commits that move more
-// than it holds (commit_streams) stream on both sides.  us, plain -> streaming, above the line: 30 layers of 4680 tokens x 12
-// heads 315 -> 297, fp32 20 layers of 2000 x 8 committed and read back 301 -> 276, attention and commit of 10 layers of
-// 3600 x 12 1631 -> 1615, of 6 of 1560 x 40 and of 30 of 1560 x 12 level; below it, attention and commit: 4 layers of 480 x 12
-// 77.6 -> 85.0, 2 of 776 x 8 38.5 -> 40.5, 2 of 1560 x 24 195 -> 204, 12 of 720 x 20 498 -> 509.
-// A read-back's source streams where the caches will not have kept it, because what the layers hold, and as much that
-// it was made from, is more (read_streams): 8 layers of 4680 x 12 committed and read back 195 -> 178 us, 30 711 -> 678; 4,
-// below the line, 81.5 -> 86.  What a read-back or a merge writes is what its caller reads next: never (read-back and a copy of
-// it 23.8 us, 27.3 with streaming stores).
-// The line lies a little above the cache's 256 MiB: 5 layers of 4680 x 12 (274 MiB) committed and read back 111 -> 113, 6
-// (329) 148 -> 135, fp32 10 of 2000 x 8 (313) 143 -> 137.
-constexpr int64_t STREAM_FROM = (int64_t)300 << 20;
-inline bool commit_streams(int64_t bytes_read_and_written) { return bytes_read_and_written > STREAM_FROM; }
-inline bool read_streams(int64_t bytes_all_layers_hold) { return 2 * bytes_all_layers_hold > STREAM_FROM; }
+// STREAM: non-temporal accesses, past the caches (ifx_stream.hpp).
 template <bool STREAM, typename T>
 __device__ __forceinline__ T load_from(const T *p)
 {

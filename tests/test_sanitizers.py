@@ -32,3 +32,9 @@ def test_oracle_under_asan_ubsan(tmp_path):
 
 def test_ring_under_asan_ubsan(tmp_path):
     build_and_run(tmp_path, "g++", [os.path.join(HERE, "sanitize", "ring_san.cpp")], ["-std=c++17"])
+
+
+def test_read_history_under_asan_ubsan(tmp_path):
+    """Which read-backs stream past the caches: layer after layer of more than those hold, and not one layer again and again, two in
+    turn, every one twice, or one that attention has just read."""
+    build_and_run(tmp_path, "g++", [os.path.join(HERE, "sanitize", "stream_san.cpp")], ["-std=c++17", "-pthread"])
