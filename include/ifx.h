@@ -95,7 +95,7 @@ ifx_kv_cache *ifx_kv_cache_create(int layers, int heads, int head_dim, int64_t c
  * resident blocks are read where they lie, out [block_tokens, heads, head_dim]
  * is written.  Calls of this function on one cache may run concurrently.
  * One kernel launch; or, where the rows are too few for the chip and the keys
- * many (ifx_attention_key_parts, ifx_attention_f32_key_parts), two: the keys are dealt to several
+ * many (ifx_attention_key_parts and its like), two: the keys are dealt to several
  * workgroups per row tile and their results, in memory that the cache holds
  * for two streams at a time, put together.  The first two streams that such
  * calls come on have it; another stream gets the memory of one (other than the
@@ -362,10 +362,11 @@ int ifx_ring_grow(ifx_ring *ring, int64_t new_capacity_blocks, int in_place);
  * ifx_attention_key_groups: into how many groups of wavefronts the keys of a bf16 or fp8 cache's
  * calls are dealt, by the rows alone: 1 (up to 256 query rows per workgroup), 2 (up to 128) or 8 (32);
  * IFX_ERR_INVALID_ARG (< 0) if either argument is < 1.
- * ifx_attention_key_parts: to how many workgroups per row tile a bf16 or fp8 call over `cached_tokens`
+ * ifx_attention_key_parts: to how many workgroups per row tile a bf16 cache's call over `cached_tokens`
  * selected cached tokens (and, with_block != 0, the block's own) deals its keys; 1: one launch does it
  * all; more: those of heads *whole_heads and up go to that many, and a second launch puts their
  * results together.  *rows: the most query rows of a workgroup (either pointer may be NULL).
+ * ifx_attention_fp8_key_parts: the same of an fp8 cache's call, whose keys come in parts a little earlier.
  * ifx_attention_f32_key_parts: the same of an fp32 call over `keys` keys, all heads (listed != 0: of a selection).
  * ifx_attention_area_bytes: device memory that a cache of such blocks with room for `capacity_blocks` of them holds for
  * the partial results of one stream's calls: as much as the largest of them takes.
@@ -378,6 +379,7 @@ int ifx_ring_grow(ifx_ring *ring, int64_t new_capacity_blocks, int in_place);
  * ifx_attention_launch_grid, ifx_attention_launch_item: the same with one group. */
 int ifx_attention_key_groups(int block_tokens, int heads);
 int ifx_attention_key_parts(int block_tokens, int heads, int64_t cached_tokens, int with_block, int *whole_heads, int *rows);
+int ifx_attention_fp8_key_parts(int block_tokens, int heads, int64_t cached_tokens, int with_block, int *whole_heads, int *rows);
 int ifx_attention_f32_key_parts(int block_tokens, int heads, int head_dim, int64_t keys, int listed, int *rows);
 int64_t ifx_attention_area_bytes(int block_tokens, int heads, int head_dim, int dtype, int64_t capacity_blocks);
 int ifx_attention_group_grid(int block_tokens, int heads, int groups);

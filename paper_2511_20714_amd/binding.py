@@ -67,6 +67,7 @@ _SIGS = {
     "ifx_ring_grow": (_int, [_vp, _i64, _int]),
     "ifx_attention_key_groups": (_int, [_int, _int]),
     "ifx_attention_key_parts": (_int, [_int, _int, _i64, _int, ctypes.POINTER(_int), ctypes.POINTER(_int)]),
+    "ifx_attention_fp8_key_parts": (_int, [_int, _int, _i64, _int, ctypes.POINTER(_int), ctypes.POINTER(_int)]),
     "ifx_attention_f32_key_parts": (_int, [_int, _int, _int, _i64, _int, ctypes.POINTER(_int)]),
     "ifx_attention_area_bytes": (_i64, [_int, _int, _int, _int, _i64]),
     "ifx_attention_group_grid": (_int, [_int, _int, _int]),
@@ -293,9 +294,16 @@ def ifx_attention_key_groups(block_tokens: int, heads: int) -> int:
 
 
 def ifx_attention_key_parts(block_tokens: int, heads: int, cached_tokens: int, with_block: bool = True):
-    """(workgroups per row tile that a call's keys are dealt to, the heads before those whose keys are, rows of a workgroup)"""
+    """(workgroups per row tile that a bf16 cache's call deals its keys to, the heads before those whose keys are, rows of a workgroup)"""
     whole, rows = _int(), _int()
     parts = _check(lib().ifx_attention_key_parts(block_tokens, heads, cached_tokens, int(bool(with_block)), ctypes.byref(whole), ctypes.byref(rows)))
+    return parts, whole.value, rows.value
+
+
+def ifx_attention_fp8_key_parts(block_tokens: int, heads: int, cached_tokens: int, with_block: bool = True):
+    """The same of an fp8 cache's call."""
+    whole, rows = _int(), _int()
+    parts = _check(lib().ifx_attention_fp8_key_parts(block_tokens, heads, cached_tokens, int(bool(with_block)), ctypes.byref(whole), ctypes.byref(rows)))
     return parts, whole.value, rows.value
 
 

@@ -991,7 +991,7 @@ static int attention_impl(ifx_kv_cache *c, int layer, const void *q, const void 
     unsigned char *area = nullptr;
     int64_t units = 0;
     if (c->mfma()) {
-        plan = ifx::attn_plan_for(n, H, (int)attn_tiles(cached, with_block ? n : 0));
+        plan = ifx::attn_plan_for(n, H, (int)attn_tiles(cached, with_block ? n : 0), c->dtype == IFX_FP8_E4M3);
         if (plan.parts > 1) {
             split_lock.lock();
             units = (int64_t)(H - plan.whole_heads) * plan.parts * ((n + 31) / 32);
@@ -1405,14 +1405,24 @@ int ifx_attention_key_groups(int block_tokens, int heads)
     return ifx::attn_groups_for(block_tokens, heads);
 }
 
-int ifx_attention_key_parts(int block_tokens, int heads, int64_t cached_tokens, int with_block, int *whole_heads, int *rows)
+static int key_parts(int block_tokens, int heads, int64_t cached_tokens, int with_block, bool fp8, int *whole_heads, int *rows)
 {
     if (block_tokens < 1 || heads < 1 || cached_tokens < 0 || cached_tokens > (int64_t)1 << 30)
         return fail(IFX_ERR_INVALID_ARG, "key_parts: block_tokens and heads must be positive, cached_tokens 0 .. 2^30");
-    const ifx::attn_plan p = ifx::attn_plan_for(block_tokens, heads, (int)attn_tiles(cached_tokens, with_block ? block_tokens : 0));
+    const ifx::attn_plan p = ifx::attn_plan_for(block_tokens, heads, (int)attn_tiles(cached_tokens, with_block ? block_tokens : 0), fp8);
     if (whole_heads) *whole_heads = p.whole_heads;
     if (rows) *rows = p.groups == 8 ? ifx::FEW_ROWS : ifx::BF_BM / p.groups;
     return p.parts;
+}
+
+int ifx_attention_key_parts(int block_tokens, int heads, int64_t cached_tokens, int with_block, int *whole_heads, int *rows)
+{
+    return key_parts(block_tokens, heads, cached_tokens, with_block, false, whole_heads, rows);
+}
+
+int ifx_attention_fp8_key_parts(int block_tokens, int heads, int64_t cached_tokens, int with_block, int *whole_heads, int *rows)
+{
+    return key_parts(block_tokens, heads, cached_tokens, with_block, true, whole_heads, rows);
 }
 
 int ifx_attention_f32_key_parts(int block_tokens, int heads, int head_dim, int64_t keys, int listed, int *rows)

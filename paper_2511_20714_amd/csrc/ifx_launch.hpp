@@ -132,16 +132,21 @@ inline attn_plan attn_split_candidate(int n, int heads)
 //    16 x 2400 30 -> 28, 800 x 10 x 6400 39 -> 38, 400 x 5 x 2000 15 -> 20.
 //  - 32-row workgroups are at most half a round: the same with those, whose partial results are fewer.  What a step of
 //    such a workgroup takes is the 128 KiB of keys that its CU's L1 can pass on (45 of 64 bytes per cycle), so only more
-//    CUs shorten it.  Against tiles shared by slabs (few_slab_groups): 1560 x 1 x 10920 41 -> 22, x 2 47 -> 38, 1000 x 2
-//    x 8000 35 -> 21, 680 x 1 x 3400 15.2 -> 13.3, 400 x 2 x 3200 15.0 -> 13.2, 1000 x 4 x 4000 22.3 -> 21.4; level at 10 to 12
-//    steps: 680 x 1 x 2720 13.3 -> 13.0, 1000 x 2 x 3000 16.9 -> 15.3, 552 x 3 x 2760 15.4 -> 14.7, 400 x 5 x 2800 15.3 -> 15.7, 264 x 2 x
-//    2112 11.3 -> 12.1; and behind below: 1000 x 1 x 2000 11.6 -> 13.4, 760 x 3 x 2280 13.4 -> 15.0, 264 x 2 x 792 7.7 -> 10.7.
+//    CUs shorten it.  Against tiles shared by slabs (few_slab_groups), whole -> parts: 1560 x 1 x 3120 14.9 -> 14.1, x 10920 41 ->
+//    22; 1000 x 2 x 3000 15.9 -> 14.9, x 4000 19.0 -> 15.9; 264 x 2 x 3168 14.3 -> 12.7; two to a tile: 760 x 3 x 3800 18.0 -> 16.5,
+//    1424 x 2 x 4272 20.8 -> 19.5, 464 x 6 x 4640 21.7 -> 20.5; level from 9 to 11 steps (two to a tile 12 to 17): 264 x 2 x 2112
+//    11.2 -> 11.8, 552 x 3 x 2760 14.1 -> 14.3, 400 x 5 x 2800 14.7 -> 15.2, 760 x 3 x 3040 15.6 -> 15.5, 1000 x 3 x 4000 19.3 -> 19.3; and
+//    behind below: 1000 x 1 x 2000 11.5 -> 12.8, 400 x 2 x 2000 11.2 -> 12.2, 680 x 1 x 2040 11.3 -> 12.0, 440 x 3 x 2200 12.1 -> 12.9.
+//    A step over codes takes workgroups that share a tile longer (each widens them), so an fp8 cache's keys come in parts a step
+//    or two earlier: 264 x 2 x 2112 12.1 -> 11.4, 216 x 1 x 1944 11.6 -> 11.0, 760 x 3 x 3040 16.7 -> 15.1, 752 x 4 x 3760 19.4 -> 18.7,
+//    360 x 8 x 4320 21.6 -> 20.0; behind: 144 x 1 x 1728 10.8 -> 10.9, 160 x 12 x 1920 11.5 -> 13.7.  Of some 480 calls about the lines
+//    the side taken is the faster one or at most 4 % behind it in all but ten (5 to 7: 264 x 2 x 2112, 136 x 8 x 2584).
 //  - a last round would be nearly empty: whole heads fill the rounds, the keys of the rest go to as many
 //    workgroups as its CUs.  4680 x 14 x 18720 648 -> 496, x 15 653 -> 526, x 16 654 -> 560, x 17 658 -> 595, x 18
 //    675 -> 642; x 28 x 14040 899 -> 753; 10800 x 7 x 32400 1120 -> 981; 1560 x 40 x 10920 379 -> 295; but 1560 x 37
 //    281 -> 275 and 10800 x 6 840 -> 840, where two groups take two rounds.
 // Below: the sides' times (us) as fitted to such measurements.  The tiles are the call's 64-key tiles.
-inline attn_plan attn_plan_for(int n, int heads, int tiles)
+inline attn_plan attn_plan_for(int n, int heads, int tiles, bool fp8)
 {
     const attn_plan whole = {attn_groups_for(n, heads), heads, 1};
     const int row_waves = (n + 31) / 32;
@@ -155,14 +160,16 @@ inline attn_plan attn_plan_for(int n, int heads, int tiles)
     const float few_steps = (float)((tiles + 3) / 4);  // of a wavefront, 32 keys each
     float us = 8.f + tiles * 1.0f;                     // one group
     if (whole.groups == 8) {
-        // (four to a tile: 0.6 to 0.9 a step, the more the fuller the chip; at 0.97 the line lies where parts are level)
         const int sharing = few_slab_groups(n, heads);
         const float busy = rows * (float)sharing / 256.f;
-        us = 5.3f + few_steps * (sharing == 4 ? 0.97f : sharing == 2 ? 0.67f + 0.39f * busy : 1.13f * (1.f + 0.2f * busy * busy));
+        us = sharing == 4   ? 5.1f + few_steps * (fp8 ? 0.81f + 0.09f * busy : 0.73f + 0.12f * busy)
+             : sharing == 2 ? 5.1f + few_steps * (fp8 ? 0.85f + 0.16f * busy : 0.68f + 0.31f * busy)
+                            : 5.3f + few_steps * 1.13f * (1.f + 0.2f * busy * busy);
     } else if (whole.groups == 2) {
         const float busy = (float)((row_waves + 3) / 4 * heads) / 256.f;
         us = 8.f + tiles * (busy <= 0.4f ? 0.52f : 0.52f + 0.4f * (busy - 0.4f));
     }
+    const float us_whole = us;
     us *= 0.95f;
     attn_plan best = whole;
     if (p.parts > 1) {
@@ -175,7 +182,12 @@ inline attn_plan attn_plan_for(int n, int heads, int tiles)
     }
     if (whole.groups == 8) {
         const int workgroups = row_waves * heads, most = tiles / 4, enough = 256 / workgroups, parts = enough < most ? enough : most;
-        if (parts > 1 && 11.f + 1.15f * (float)((tiles + 4 * parts - 1) / (4 * parts)) < us) best = {8, 0, parts};
+        if (parts > 1) {
+            // (against whole calls: fitted where the two are level; against 256-row parts: to the longer runs where those are)
+            const bool few = best.parts > 1 ? 11.f + 1.15f * (float)((tiles + 4 * parts - 1) / (4 * parts)) < us
+                                            : 9.7f + 1.07f * (float)tiles / (float)(4 * parts) + 2.f * rows * (float)parts / 256.f < us_whole;
+            if (few) best = {8, 0, parts};
+        }
     }
     return best;
 }
@@ -206,15 +218,17 @@ inline attn_split attn_split_for(int n, int heads, const attn_plan &p)
     return s;
 }
 
-// Units of partial results that calls over up to `tiles` tiles of keys need.
+// Units of partial results that calls over up to `tiles` tiles of keys need, of either cache.
 inline int64_t attn_split_units(int n, int heads, int64_t tiles)
 {
     const int64_t rows = (n + 31) / 32;
     int64_t most = 0;
     for (int64_t t = 8; t <= tiles; ++t) {
-        const attn_plan p = attn_plan_for(n, heads, (int)t);
-        const int64_t units = p.parts > 1 ? rows * (heads - p.whole_heads) * p.parts : 0;
-        if (units > most) most = units;
+        for (const bool fp8 : {false, true}) {
+            const attn_plan p = attn_plan_for(n, heads, (int)t, fp8);
+            const int64_t units = p.parts > 1 ? rows * (heads - p.whole_heads) * p.parts : 0;
+            if (units > most) most = units;
+        }
     }
     return most;
 }

@@ -304,6 +304,22 @@ def test_key_parts_where_they_pay(n, heads, cached, parts, whole, rows):
             ifx.ifx_attention_key_parts(*bad)
 
 
+@pytest.mark.parametrize("n,heads,cached,bf16,fp8", [
+    (1000, 1, 1000, 1, 1), (400, 2, 1600, 1, 1), (304, 4, 1520, 1, 1), (160, 12, 1760, 1, 1),                          # up to 8 steps
+    (216, 1, 1728, 1, 7), (448, 2, 1792, 1, 8), (680, 1, 1360, 1, 8), (224, 2, 2016, 9, 9), (1000, 1, 2000, 8, 8), (1560, 1, 1560, 5, 5), (1000, 2, 2000, 4, 4),
+    (760, 3, 1520, 1, 1), (760, 3, 2280, 1, 3), (752, 4, 3008, 1, 2),                                                  # two to a tile
+    (760, 3, 3040, 3, 3), (1424, 2, 2848, 2, 2), (464, 6, 4176, 2, 2), (1000, 3, 4000, 2, 2), (528, 7, 3696, 2, 2), (528, 8, 3696, 1, 1),
+])
+def test_shared_row_tiles_or_parts(n, heads, cached, bf16, fp8):
+    """32-row tiles shared by workgroups, or their keys in parts: on either side of the lines of both caches; what a cache holds
+    for partial results has room for either."""
+    assert ifx.ifx_attention_key_parts(n, heads, cached)[::2] == (bf16, 32) and ifx.ifx_attention_fp8_key_parts(n, heads, cached)[::2] == (fp8, 32)
+    holds = ifx.ifx_attention_area_bytes(n, heads, 128, ifx.IFX_FP8_E4M3, cached // n)
+    assert max(bf16, fp8) == 1 or max(bf16, fp8) * heads * ((n + 31) // 32) * (16384 + 512) <= holds
+    with pytest.raises(ifx.IfxError):
+        ifx.ifx_attention_fp8_key_parts(0, heads, cached)
+
+
 @pytest.mark.parametrize("n,heads,head_dim,keys,listed,parts,rows", [
     (256, 2, 64, 1024, False, 8, 16), (256, 2, 64, 256, False, 1, 16), (64, 1, 128, 320, False, 1, 16), (400, 4, 128, 2000, False, 5, 16),
     (800, 3, 128, 1600, False, 5, 16), (400, 10, 128, 1200, False, 1, 16), (100, 16, 64, 500, False, 1, 16),
