@@ -89,8 +89,8 @@ inline int attn_f32_parts(int64_t workgroups, int padded_d, int64_t subs)
         // (three parts and more: 9.3, the second launch reading all parts at once; two of 108 tiles were 5 % behind there)
         const float split = p > 1 ? (p > 2 ? 9.3f : 11.f) + step * (float)((subs + 8 * p - 1) / (8 * p)) : us;
         if (split < us) {
+            us = split;
             parts = (int)p;
-            if (p == 2 || split + 1.7f < us) us = p == 2 ? split : split + 1.7f;
         }
     }
     if (workgroups > 85 && subs >= 40 && 12.f + all < us) parts = workgroups <= 480 ? 5 : 3;

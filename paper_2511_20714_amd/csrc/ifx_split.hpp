@@ -87,10 +87,10 @@ __global__ __launch_bounds__(64 * COMBINE_MOST_WAVES) void combine_kernel(const 
     store_slab(a.out + ((int64_t)(qi < a.n ? qi : a.n - 1) * a.H + head) * BF_D + 32 * sl, R, 1.0f / l, lh, qi < a.n);
 }
 
+// (parts >= 2)
 inline void (*combine_kernel_of(int parts))(const combine_args)
 {
     switch (combine_batch(parts)) {
-    case 1: return combine_kernel<1>;
     case 2: return combine_kernel<2>;
     case 3: return combine_kernel<3>;
     default: return combine_kernel<4>;
