@@ -28,6 +28,14 @@ CASES = [
     (8, 72, 5, 3, 3, None, True),
     (8, 264, 28, 2, 2, None, True),     # 252 workgroups
     (8, 1024, 8, 1, 0, None, True),     # 256, no cached keys
+    # up to here tiles of up to 64 workgroups are shared by four, of up to 128 by two; the same forms where two share, and where none do
+    (8, 8, 100, 200, 203, list(range(199, -1, -1)), True),
+    (8, 24, 70, 67, 67, list(range(66, 0, -1)), True),
+    (8, 40, 45, 3, 5, [2, 0], False),
+    (8, 8, 130, 200, 203, list(range(199, -1, -1)), True),
+    (8, 24, 140, 67, 67, list(range(66, 0, -1)), True),
+    (8, 40, 70, 3, 5, [2, 0], False),
+    (8, 8, 129, 2, 1, None, True),      # seven wavefronts without a key
     # two groups (128-row workgroups)
     (2, 1032, 8, 1, 1, None, True),     # 264 row wavefronts: the first past eight groups
     (2, 168, 43, 2, 2, None, True),     # the fewest rows a head, 6 wavefronts of them; a phase of 5 tiles and 16 keys
@@ -94,6 +102,10 @@ def test_key_groups_at_every_switch(gpu_device, groups, n, H, cap, commits, bloc
 @pytest.mark.parametrize("groups,n,H,cap", [
     (8, 264, 2, 2),
     (8, 8, 3, 9),       # whole blocks that count nothing
+    (8, 264, 8, 2),     # 72 and 135 row tiles, of two workgroups and of one
+    (8, 8, 100, 9),
+    (8, 264, 15, 2),
+    (8, 8, 130, 9),
     (2, 1560, 12, 1),
     (2, 264, 135, 1),   # two rounds of workgroups
     (1, 200, 150, 2),

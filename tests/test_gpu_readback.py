@@ -61,8 +61,8 @@ def test_read_back_at_the_edges(gpu_device, dtype, n, H, D, cap, commits):
     (ifx.IFX_F32, 1033, 9, 40, 54, 2),      # rows of 10 chunks; ragged last round
 ])
 def test_copies_past_the_caches(gpu_device, dtype, n, H, D, L, cap):
-    """A commit that moves more than 300 MiB, and a read-back of layers that together hold more than half of that, stream: bit
-    for bit what one layer's commits and read-back, which do not, leave."""
+    """A commit that moves more than 300 MiB, and the read-backs but the first that go over layers which together move more than
+    that, stream: bit for bit what one layer's commits and read-backs, which do not, leave."""
     dev = gpu_device
     tdtype = TORCH_DTYPE.get(dtype, torch.bfloat16)
     io, held = (4, 4) if dtype == ifx.IFX_F32 else (2, 1 if dtype == ifx.IFX_FP8_E4M3 else 2)
