@@ -372,6 +372,8 @@ int ifx_ring_grow(ifx_ring *ring, int64_t new_capacity_blocks, int in_place);
  * the partial results of one stream's calls: as much as the largest of them takes.
  * ifx_attention_group_grid: workgroups of one attention launch over blocks of `block_tokens` tokens
  * and `heads` heads with `groups` (1, 2, 8) key groups; IFX_ERR_INVALID_ARG (< 0) for anything else.
+ * (8: with one workgroup per 32-row tile.  Calls of up to 128 such tiles launch two for each, of up to 64 four, which share its
+ * output dimensions; and with any groups, calls in parts have a launch of their own shape.)
  * ifx_attention_group_item: what workgroup `workgroup` of that launch does, written to item[0..4]:
  * head, query tile of the head, first query row, wavefronts' worth of rows it holds (32 rows each, up
  * to 8, 4 or 1; 0: the workgroup exits at once, the other entries are then meaningless), XCD it

@@ -31,10 +31,10 @@
 // Measured (1560 rows, 12 heads x 128, 3120 keys): 291 us = 103 TFLOP/s, where the library's plain
 // fp32 matrix product reaches 154 on the same card; 1840 us with fp32 FMA from LDS tiles.  With K
 // straight from memory 393 us; with 32 rows per wavefront (half the bytes per flop, but fewer and
-// larger workgroups) 390 us.  256 rows, 2 heads x 64, 1024 keys: 16.1 us, 18.5 with the block's commit
-// (118 with 32-row workgroups that do not deal the keys out).  Of the 16, the matrix pipes of the 32
-// CUs in use are busy for 8 (28 % of the launch as the counters see it); the rest is the launch and a
-// wavefront's serial chain of scores, maximum and exponentials, eight times.
+// larger workgroups) 390 us.  256 rows, 2 heads x 64, 1024 keys: 16.1 us whole (118 with 32-row workgroups
+// that do not deal the keys out); in eight parts 9.6 to 10.3, 14.5 with the block's commit.  Traced, 7.4 of the
+// attention, 3.2 of putting the parts together and 2.6 of the commit: 256 CUs whose wavefronts take one subtile
+// each, half their cycles at wait counts (a subtile's K, then its V), the matrix pipes 6 % busy.
 #pragma once
 #include <cfloat>
 
@@ -98,8 +98,12 @@ inline int attn_f32_parts(int64_t workgroups, int padded_d, int64_t subs)
 }
 // Which kernel takes a call, and to how many workgroups per row tile its keys are dealt.  attn_f32l_kernel (256-row
 // workgroups, ifx_attn_f32_large.hpp) where its workgroups, in parts, fill the chip for long enough.  Both sides measured (us, this
-// kernel in its parts and that one): 1560 rows x 12 heads x 128, 3120 keys 296, 176; x 16, 4680 keys 594, 339; x 2, 7800 keys
-// 143, 88; x 3, 3120 keys 92, 64; 1560 x 9 x 64, 4680 keys 198, 128.  It takes no selection of blocks.
+// kernel in its parts and that one): 1560 rows x 12 heads x 128, 3120 keys 294, 160; x 16, 4680 keys 591, 309; x 2, 7800 keys
+// 133, 81; x 3, 3120 keys 89, 58; 1560 x 9 x 64, 4680 keys 197, 118; and on the other side 400 x 10 x 128, 1200 keys 30, 39; 800 x 3
+// x 128, 1600 keys 33, 38; 1240 x 1 x 64, 6200 keys 32, 42.  The costs below were fitted when that kernel's tile took 4.6 and 3.0 us (now 4.2
+// and 2.7) and a second launch 4 to 5 (now 3): the line lies on the 16-row kernel's side, where calls near it would gain 10 to 30 %
+// (1368 x 3 x 72, 2736 keys 64, 45; 696 x 6 x 128, 1392 keys 52, 38; 808 x 6 x 40, 2424 keys 43, 38; level at 1568 x 1 x
+// 96, 6272 keys 51, 52 and 600 x 4 x 72, 2400 keys 35, 37).  It takes no selection of blocks.
 struct f32_plan {
     bool large;
     int parts;
@@ -432,8 +436,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(GATHER ? 2 
 
 // out = sum_p f_p O_p / sum_p f_p l_p, f_p = exp(m_p - max m), parts in their order.  A thread: 4 dimensions of a row.
 // Bound by latency: references, sums and results of BATCH parts are on their way at once (the references were read
-// one after another before the first result was asked for), and workgroups are single wavefronts, which reach more CUs
-// where rows are few.  Whole calls (us): 256 rows x 2 heads x 64, 1024 keys 11.5 -> 9.6, 200 x 1 x 96, 1000 keys 14.0 -> 11.7, 256 x
+// one after another before the first result was asked for; those beyond the first BATCH parts still are, and read again with
+// their results), and workgroups are single wavefronts, which reach more CUs where rows are few.  Whole calls (us): 256 rows x 2 heads x 64, 1024 keys 11.5 -> 9.6, 200 x 1 x 96, 1000 keys 14.0 -> 11.7, 256 x
 // 8 x 72, 1024 keys 17.9 -> 17.0, 1560 x 12 x 128, 3120 keys 157.7 -> 156.0.  BATCH: 4 for up to four parts (with 8: 17.2 and 25.6
 // instead of 17.0 and 25.4 on 256 x 8 x 72 and 512 x 4 x 128), 8 beyond (with 4: 10.6 and 12.4 on the first two).
 constexpr int COMBINE_F32_THREADS = 64;

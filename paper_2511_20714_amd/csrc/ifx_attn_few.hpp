@@ -25,11 +25,12 @@
 //   conflicts, 1.40 GB read from the L2s (22 TB/s); wavefronts spend 24 % of their cycles at wait counts,
 //   32 % waiting to issue.  No unit is full: a wavefront has one subtile's loads in flight and
 //   its softmax between two products, and two wavefronts per SIMD do not cover that.
-//   A CU's L1 passes on those 128 KiB a step at 45 of its 64 bytes per cycle.  Where CUs would be idle, 2 or 4 workgroups
+//   A CU's L1 passes on those 128 KiB a step at 45 and more of its 64 bytes per cycle.  Where CUs would be idle, 2 or 4 workgroups
 //   share a row tile, each with all its scores and 2 slabs or 1 of 32 output dimensions (SLABS, few_slab_groups): 96 or 80 KiB
-//   a step, 0.7 to 1.0 us; 264 rows, 2 heads, 792 keys 9.6 -> 7.7 us (21 with one group), four steps and the launch.  Of that
-//   0.2 is a step's scalar work, descriptors made for every copy before, and copies behind the last subtile, which
-//   now touch no memory.  Where tiles are at most half a round and the keys many, those come in parts (SPLIT,
+//   a step, 0.87 and 0.70 us where one workgroup takes 1.13, the same bytes per cycle; over codes 0.95 and 0.85, each workgroup
+//   widening them.  264 rows, 2 heads, 792 keys 9.6 -> 7.7 us (21 with one group), four steps and the launch: matrix pipes 2 % busy,
+//   wavefronts 47 % of their cycles at wait counts.  (Descriptors made once, not for every copy, and copies behind the last
+//   subtile that touch no memory are worth 3 % over codes, and with one workgroup to a bf16 tile nothing.)  Where tiles are at most half a round and the keys many, those come in parts (SPLIT,
 //   attn_plan_for): 1 head x 1560 rows, 10920 keys 54 -> 21.6 us.
 #pragma once
 #include "ifx_attn_bf16.hpp"

@@ -88,9 +88,9 @@ inline int attn_groups_for(int n, int heads)
 // own of the 4 slabs of 32 output dimensions, and reads 256 of a key's 512 bytes for the scores and 64 or 128 for the values.
 // What a step takes there is what one CU's L1 passes on, so on CUs that would be idle the tile ends sooner, and the wavefronts'
 // shares are put together a slab or two at a time; nothing is exchanged between the workgroups.  As many as
-// leave all of them one round on 256 CUs.  us, by one workgroup and shared (with the scalar work of a step also taken down
-// in that change), bf16 cache: 264 rows x 2 heads, 792 keys 9.6 -> 7.7; 1584 keys 12.7 -> 9.8; 88 x 4, 352 7.5 -> 6.2; two to a
-// tile: 136 x 20, 680 9.7 -> 8.4; 760 x 3, 1520 12.9 -> 11.1; 1000 x 4, 2000 15.1 -> 13.7; fp8: 208 x 11, 1664 14.1 -> 11.9.
+// leave all of them one round on 256 CUs.  us, by one workgroup and shared, bf16 cache: 264 rows x 2 heads, 792 keys 9.6 ->
+// 7.7; 1584 keys 12.7 -> 9.9; 88 x 4, 352 7.5 -> 6.4; two to a tile: 136 x 20, 680 9.6 -> 8.4; 760 x 3, 1520 12.9 -> 11.2; 1000
+// x 4, 2000 15.1 -> 14.2; fp8: 208 x 11, 1664 13.6 -> 12.0; 264 x 2, 792 9.3 -> 7.7.
 inline int few_slab_groups(int n, int heads)
 {
     const int64_t workgroups = (int64_t)((n + 31) / 32) * heads;

@@ -4,8 +4,8 @@
 // A launch of its own behind the attention kernel: the stream's order is the only synchronisation.  (Letting the
 // last workgroup of a tile do it was measured on stand-ins of 256 workgroups with 16 KiB each: 6.4 us for the
 // two launches, 15 with agent-scope stores and a counter, 60 with plain stores and a release fence, which
-// writes back the whole L2.)  Bound by the memory-side cache's rate: the partials of 1560 rows x 12 heads in
-// three parts are 29 MB, 7.8 us; 1560 x 1 in five 3.9.
+// writes back the whole L2.)  Bound by the memory-side cache's latency and rate: the partials of 1560 rows x 12 heads in
+// three parts are 29 MB, 7.3 us (wavefronts 64 % of their cycles at wait counts); 1560 x 1 in five 4.0.
 #pragma once
 #include "ifx_attn_bf16.hpp"
 
@@ -30,7 +30,7 @@ inline int combine_batch(int parts)
 
 // A workgroup = one slab of 32 dimensions of one unit's 32 rows, the parts dealt to its wavefronts (up to four: one
 // wavefront, which exchanges nothing); lanes hold what the accumulators held.  BATCH: parts that a wavefront has on their way at
-// once, as many as it takes (four of every wavefront's one or two before, some loaded four times: 30 layers of 1560 x 12 x 10920
+// once, as many as it takes up to four: 16 parts of four wavefronts (four of every wavefront's one or two before, some loaded four times: 30 layers of 1560 x 12 x 10920
 // 3260 -> 3245 us, 800 x 12 x 6400 43.4 -> 42.9, 400 x 2 x 3200 13.1 -> 13.0, x 1 12.4 -> 12.2).  Streaming the partial results past
 // the caches gains nothing.  The sums are taken in a fixed order, whichever workgroup finished first.
 template <int BATCH>
